@@ -37,7 +37,11 @@ namespace {
 
 constexpr int kWave = 64;
 constexpr int kU = kEdgesPerLanePass;  // edges in flight per lane
-constexpr uint32_t kPushBuf = 512;  // per-wavefront LDS staging of next-worklist pushes
+// Per-wavefront LDS staging of next-worklist pushes, in bytes: 1,024 vertex
+// ids or 512 (query, vertex) pairs.  Reservations on the worklist's size
+// counter are what it saves: atomics on one address complete one every 12 ns
+// whoever issues them, so their number, not their latency, bounds a phase.
+constexpr uint32_t kPushBytes = 4096;
 
 __device__ __forceinline__ uint32_t lane_id() {
   return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
@@ -406,7 +410,10 @@ struct Smem {
   uint32_t xcd, xcd_n, n_xcd;  // its XCD, the members on that XCD, the XCDs holding members
   unsigned long long cbase;  // phase 1: first worklist entry of the current claim
   uint32_t clen;             // and its length
-  Entry<M> pbuf[B / kWave][kPushBuf];  // per-wavefront push staging
+  Entry<M> pbuf[B / kWave][kPushBytes / sizeof(Entry<M>)];  // per-wavefront push staging
+  // end of a phase: entries staged per wavefront, the workgroup's reservation
+  alignas(16) uint32_t pcnt[B / kWave];
+  uint32_t pbase;
 };
 
 // The workgroup's index and the workgroup count used for work distribution:
@@ -472,14 +479,11 @@ __device__ void flush_dangling(Acc &acc, Smem<B, Op, M> &sm, unsigned long long 
   acc.dangling = 0;
 }
 
-// Write the staged entries to the next worklist (all lanes call this).
+// Write this wavefront's staged entries to the next worklist from `base` on
+// (all its lanes call this).
 template <class E>
-__device__ __forceinline__ void flush_pushes(const Args &a, int round, Pusher<E> &pu) {
-  if (pu.cnt == 0) return;
+__device__ __forceinline__ void write_pushes(const Args &a, int round, Pusher<E> &pu, uint32_t base) {
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  uint32_t base = 0;
-  if (lane_id() == 0) base = add_relaxed(pu.qn_cnt, pu.cnt);
-  base = __shfl(base, 0);
   for (uint32_t j = lane_id(); j < pu.cnt; j += kWave) {
     const uint32_t idx = base + j;
     if (idx < a.qcap)
@@ -491,16 +495,44 @@ __device__ __forceinline__ void flush_pushes(const Args &a, int round, Pusher<E>
   pu.cnt = 0;
 }
 
-// Stage v for every lane with pred (all lanes of the wavefront call this).
+// Stage v for every lane with pred (all lanes of the wavefront call this).  A
+// full staging area is written out with a reservation of its own.
 template <class E>
 __device__ __forceinline__ void push_wave(bool pred, E v, const Args &a, int round, Pusher<E> &pu, Acc &acc) {
   const unsigned long long m = __ballot(pred);
   if (m == 0ull) return;
   const uint32_t total = (uint32_t)__popcll(m);
-  if (pu.cnt + total > kPushBuf) flush_pushes(a, round, pu);
+  if (pu.cnt + total > kPushBytes / sizeof(E)) {
+    uint32_t base = 0;
+    if (lane_id() == 0) base = add_relaxed(pu.qn_cnt, pu.cnt);
+    write_pushes(a, round, pu, (uint32_t)__shfl(base, 0));
+  }
   if (pred) pu.buf[pu.cnt + bits_below(m)] = v;
   pu.cnt += total;
   if (lane_id() == 0) acc.pushes += total;
+}
+
+// The end of a phase: the whole workgroup writes out what its wavefronts have
+// staged with ONE reservation.  One per wavefront made the phase ends of a
+// launch of 800 to 1,024 workgroups cost 40 to 50 us each (12 ns per atomic on
+// the one counter).  All threads call this; a workgroup barrier separates it
+// from the next call.
+template <int B, class S, class E>
+__device__ __forceinline__ void flush_phase(const Args &a, S &sm, int round, Pusher<E> &pu) {
+  const int w = threadIdx.x / kWave;
+  if (lane_id() == 0) sm.pcnt[w] = pu.cnt;
+  __syncthreads();
+  uint32_t total = 0, before = 0;
+#pragma unroll
+  for (int j = 0; j < B / kWave; ++j) {
+    const uint32_t c = sm.pcnt[j];
+    before += j < w ? c : 0u;
+    total += c;
+  }
+  if (total == 0) return;
+  if (threadIdx.x == 0) sm.pbase = add_relaxed(pu.qn_cnt, total);
+  __syncthreads();
+  if (pu.cnt) write_pushes(a, round, pu, sm.pbase + before);
 }
 
 // log2 of the chunk size of the huge-edge index for a threshold t: the
@@ -865,7 +897,7 @@ __device__ void phase_twc(const Args &a, const Op &op, S &sm, Grid gr, int round
     }
     prof_mark(a, acc, kProfThreadBin, pt);
   }
-  if constexpr (Op::kPush) flush_pushes(a, round, pu);
+  if constexpr (Op::kPush) flush_phase<B>(a, sm, round, pu);
   prof_mark(a, acc, kProfThreadBin, pt);
 }
 
@@ -904,8 +936,12 @@ __device__ void phase_lb(const Args &a, const Op &op, S &sm, Grid gr, int round,
   const uint32_t vh = (uint32_t)(hc >> 32);
   const uint32_t e = (uint32_t)hc;
   if (vh == 0) return;
-  // an overflowed reservation leaves the huge list inconsistent: skip
-  if (ld_relaxed(&a.ctl->overflow) <= (uint32_t)round) return;
+  // an overflowed reservation leaves the huge list inconsistent: skip (one
+  // thread looks, so that the workgroup's waves agree: this phase's own pushes
+  // may overflow meanwhile)
+  if (threadIdx.x == 0) sm.owner = ld_relaxed(&a.ctl->overflow) <= (uint32_t)round;
+  __syncthreads();
+  if (sm.owner) return;
   const uint64_t T = (uint64_t)gr.n * B;
   const uint32_t lane = lane_id();
   const uint64_t g = (uint64_t)gr.id * B + threadIdx.x;
@@ -953,7 +989,7 @@ __device__ void phase_lb(const Args &a, const Op &op, S &sm, Grid gr, int round,
       edges<Op, M>(act, pos, s, src, op, a, tag, round, pu, acc, (int32_t)g);
     }
   }
-  if constexpr (Op::kPush) flush_pushes(a, round, pu);
+  if constexpr (Op::kPush) flush_phase<B>(a, sm, round, pu);
   prof_mark(a, acc, kProfLb, pt);
 }
 
