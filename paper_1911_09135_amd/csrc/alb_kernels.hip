@@ -64,6 +64,25 @@ __device__ __forceinline__ T add_relaxed(T *p, T v) {
   return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Records written in one phase and read in the next go through agent-scope
+// accesses, so that the grid barrier between the phases needs no cache
+// maintenance (see grid_barrier).
+__device__ __forceinline__ void st_hint(int2 *p, int2 h) {
+  st_relaxed((unsigned long long *)p, ((unsigned long long)(uint32_t)h.y << 32) | (uint32_t)h.x);
+}
+__device__ __forceinline__ int2 ld_hint(const int2 *p) {
+  const unsigned long long x = ld_relaxed((const unsigned long long *)p);
+  return make_int2((int32_t)(uint32_t)x, (int32_t)(x >> 32));
+}
+__device__ __forceinline__ void st_rec(int4 *p, int4 r) {
+  st_hint((int2 *)p, make_int2(r.x, r.y));
+  st_hint((int2 *)p + 1, make_int2(r.z, r.w));
+}
+__device__ __forceinline__ int4 ld_rec(const int4 *p) {
+  const int2 lo = ld_hint((const int2 *)p), hi = ld_hint((const int2 *)p + 1);
+  return make_int4(lo.x, lo.y, hi.x, hi.y);
+}
+
 // Overflow is recorded as the first round in which it happened; a workgroup
 // stops at the start of a later round, so every workgroup decides alike.
 __device__ __forceinline__ void flag_overflow(Ctl *c, int round) {
@@ -105,7 +124,9 @@ struct OpBFS {
   __device__ __forceinline__ val_t load_src(long long, int32_t, uint32_t tag, bool &) const {
     return (int32_t)tag - 1;
   }
-  __device__ __forceinline__ pre_t prepare(int32_t, long long dl, val_t, int32_t) const { return {level[dl]}; }
+  __device__ __forceinline__ pre_t prepare(int32_t, long long dl, val_t, int32_t) const {
+    return {ld_relaxed(&level[dl])};
+  }
   __device__ __forceinline__ bool commit(const pre_t &p, int32_t, long long dl, val_t sv, int32_t, int32_t,
                                          uint32_t) const {
     if (p.cur != kInf) return false;
@@ -123,7 +144,7 @@ struct OpBFSFilter : OpBFS {
   const uint32_t *vbits;
   __device__ __forceinline__ pre_t prepare(int32_t, long long dl, val_t, int32_t) const {
     if ((vbits[dl >> 5] >> (dl & 31)) & 1u) return {0};
-    return {level[dl]};
+    return {ld_relaxed(&level[dl])};
   }
 };
 
@@ -163,7 +184,7 @@ struct OpSSSP {  // relaxation: dist[dst] = min(dist[dst], dist[src] + w)
   const int32_t *w;
   int32_t dedup;
   __device__ __forceinline__ val_t load_src(long long sl, int32_t, uint32_t tag, bool &skip) const {
-    return label_of_active(word[sl], tag, skip);
+    return label_of_active(ld_relaxed(&word[sl]), tag, skip);
   }
   // The candidate sv + w saturates at INT32_MAX (the unreached label), which it
   // then cannot lower.  Both terms are in [0, INT32_MAX], so their sum fits in
@@ -172,7 +193,7 @@ struct OpSSSP {  // relaxation: dist[dst] = min(dist[dst], dist[src] + w)
   // it changes no result.
   __device__ __forceinline__ pre_t prepare(int32_t pos, long long dl, val_t sv, int32_t) const {
     const uint32_t c = (uint32_t)sv + (uint32_t)w[pos];
-    return {(int32_t)min(c, (uint32_t)kInf), word[dl]};
+    return {(int32_t)min(c, (uint32_t)kInf), ld_relaxed(&word[dl])};
   }
   __device__ __forceinline__ bool commit(const pre_t &p, int32_t, long long dl, val_t, int32_t, int32_t,
                                          uint32_t tag) const {
@@ -187,7 +208,7 @@ struct OpServe : OpSSSP {
   const int32_t *unit;  // per query slot
   __device__ __forceinline__ pre_t prepare(int32_t pos, long long dl, val_t sv, int32_t q) const {
     const uint32_t c = (uint32_t)sv + (unit[q] ? 1u : (uint32_t)w[pos]);
-    return {(int32_t)min(c, (uint32_t)kInf), word[dl]};
+    return {(int32_t)min(c, (uint32_t)kInf), ld_relaxed(&word[dl])};
   }
 };
 
@@ -200,9 +221,11 @@ struct OpCC {  // min-label propagation
   unsigned long long *word;
   int32_t dedup;
   __device__ __forceinline__ val_t load_src(long long sl, int32_t, uint32_t tag, bool &skip) const {
-    return label_of_active(word[sl], tag, skip);
+    return label_of_active(ld_relaxed(&word[sl]), tag, skip);
   }
-  __device__ __forceinline__ pre_t prepare(int32_t, long long dl, val_t, int32_t) const { return {word[dl]}; }
+  __device__ __forceinline__ pre_t prepare(int32_t, long long dl, val_t, int32_t) const {
+    return {ld_relaxed(&word[dl])};
+  }
   __device__ __forceinline__ bool commit(const pre_t &p, int32_t, long long dl, val_t sv, int32_t, int32_t,
                                          uint32_t tag) const {
     return lower_word(&word[dl], sv, p.cur, tag, dedup);
@@ -216,7 +239,7 @@ struct OpCCFilter : OpCC {
   const uint32_t *vbits;
   __device__ __forceinline__ pre_t prepare(int32_t, long long dl, val_t, int32_t) const {
     if ((vbits[dl >> 5] >> (dl & 31)) & 1u) return {0ull};
-    return {word[dl]};
+    return {ld_relaxed(&word[dl])};
   }
 };
 
@@ -487,7 +510,7 @@ __device__ __forceinline__ void write_pushes(const Args &a, int round, Pusher<E>
   for (uint32_t j = lane_id(); j < pu.cnt; j += kWave) {
     const uint32_t idx = base + j;
     if (idx < a.qcap)
-      pu.qn[idx] = pu.buf[j];
+      st_relaxed(&pu.qn[idx], pu.buf[j]);
     else
       flag_overflow(a.ctl, round);
   }
@@ -587,7 +610,7 @@ __device__ __forceinline__ void reserve_huge(bool huge, int32_t v_or_q, int32_t 
     j = (uint32_t)(base >> 32) + bits_below(hm);
     p = (uint32_t)base + (uint32_t)(incl - mine);
     if (j < a.qcap)
-      a.huge_rec[j] = make_int4((int32_t)p, beg, v_or_q, sv_bits);
+      st_rec(&a.huge_rec[j], make_int4((int32_t)p, beg, v_or_q, sv_bits));
     else
       flag_overflow(a.ctl, round);
   }
@@ -602,7 +625,7 @@ __device__ __forceinline__ void reserve_huge(bool huge, int32_t v_or_q, int32_t 
     const uint64_t c_hi = ((uint64_t)pp + dd - 1) >> hs;
     for (uint64_t c = c_lo + lane; c <= c_hi; c += kWave) {
       if (c < a.hint_cap)
-        a.hint[c] = make_int2((int32_t)jj, (int32_t)(pp + dd));
+        st_hint(&a.hint[c], make_int2((int32_t)jj, (int32_t)(pp + dd)));
       else
         flag_overflow(a.ctl, round);
     }
@@ -758,7 +781,7 @@ __device__ void phase_twc(const Args &a, const Op &op, S &sm, Grid gr, int round
     int32_t c_wave = a.c_wave, c_wg = a.c_wg;  // TWC cutoffs (a batch's queries may have their own)
     if (mine) {
       if constexpr (M) {
-        const unsigned long long e = F[i];
+        const unsigned long long e = ld_relaxed(&F[i]);
         v = (int32_t)(uint32_t)e;
         q = (int32_t)(e >> 32);
         if (a.qthr) thr = a.qthr[q];
@@ -767,7 +790,7 @@ __device__ void phase_twc(const Args &a, const Op &op, S &sm, Grid gr, int round
           c_wg = a.qcut[2 * q + 1];
         }
       } else {
-        v = F ? F[i] : (int32_t)i;
+        v = F ? ld_relaxed(&F[i]) : (int32_t)i;
       }
       beg = a.off[v];
       deg = a.off[v + 1] - beg;
@@ -907,10 +930,10 @@ __device__ void phase_twc(const Args &a, const Op &op, S &sm, Grid gr, int round
 // otherwise an exponential search forward from j0 + 1, then bisection, finds
 // the answer (one probe when every huge degree is at least the chunk size).
 __device__ __forceinline__ uint32_t owner_of(const Args &a, uint32_t vh, uint32_t hs, uint32_t k) {
-  const int2 h = a.hint[k >> hs];
+  const int2 h = ld_hint(&a.hint[k >> hs]);
   if (k < (uint32_t)h.y) return (uint32_t)h.x;  // inside the segment that holds the chunk's first edge
   uint64_t lo = (uint32_t)h.x + 1u, step = 1, hi = lo + 1;
-  while (hi < vh && (uint32_t)a.huge_rec[hi].x <= k) {
+  while (hi < vh && (uint32_t)ld_relaxed(&a.huge_rec[hi].x) <= k) {
     lo = hi;
     step <<= 1;
     hi = lo + step;
@@ -918,7 +941,7 @@ __device__ __forceinline__ uint32_t owner_of(const Args &a, uint32_t vh, uint32_
   if (hi > vh) hi = vh;
   while (hi - lo > 1) {
     const uint64_t mid = lo + ((hi - lo) >> 1);
-    if ((uint32_t)a.huge_rec[mid].x <= k)
+    if ((uint32_t)ld_relaxed(&a.huge_rec[mid].x) <= k)
       lo = mid;
     else
       hi = mid;
@@ -955,7 +978,7 @@ __device__ void phase_lb(const Args &a, const Op &op, S &sm, Grid gr, int round,
     src = 0;
     sv = V(0);
     if (on) {
-      const int4 r = a.huge_rec[owner_of(a, vh, hs, (uint32_t)k)];
+      const int4 r = ld_rec(&a.huge_rec[owner_of(a, vh, hs, (uint32_t)k)]);
       pos = r.y + (int32_t)((uint32_t)k - (uint32_t)r.x);
       src = r.z;
       sv = from_bits<V>(r.w);
@@ -1037,20 +1060,28 @@ __device__ __forceinline__ bool bar_wait(const Args &a, unsigned long long *w, u
   return true;
 }
 
-// Grid-wide barrier among the members of the persistent launch, with one
-// agent-scope release (L2 write-back) per XCD instead of one per workgroup:
-// the write-back covers the whole L2 of the XCD it runs on, whichever CU
-// wrote the lines, and a hundred of them in a row per L2 made the barrier
-// cost grow with the grid.  Every wave first waits until its own memory
-// operations have completed, so after the workgroup barrier all of the
-// workgroup's stores are in its XCD's L2 (the vector L1 writes through).
-// Thread 0 then arrives on its XCD's counter.  The XCD's last arrival does
-// the release, arrives on the root counter, waits for the generation and
-// opens the XCD's flag; the others wait for the flag.  Every workgroup then
-// acquires at agent scope itself (one acquire per XCD followed by an L1-only
-// invalidate elsewhere was tried and gave stale reads).  Counters only grow,
-// so nothing is reset between barriers.
-template <class S>
+// Grid-wide barrier among the members of the persistent launch.  Every wave
+// first waits until its own memory operations have completed; thread 0 then
+// arrives on its XCD's counter, the XCD's last arrival on the root counter,
+// the last of those opens the generation word, which everybody watches.
+// Counters only grow, so nothing is reset between barriers.
+//
+// Two kinds.  Light: no cache maintenance.  For data that one phase writes
+// and a later one reads through agent-scope accesses only: worklists, huge
+// records, chunk index, counters, and label words (updated by atomics).  Such
+// an access is performed at the level the XCDs share, so once the writer has
+// waited for it and arrived, a reader past the barrier sees it.  Plain loads
+// of a label may still return a value from an earlier round, which is why
+// operators read labels with agent-scope loads (they cost what plain loads
+// do: 248-250 G random 8-byte reads/s from a table that the L2 holds, either
+// way).  Full: with an agent-scope release by each XCD's last arrival (the
+// L2 write-back covers every line of that L2 whichever CU wrote it) and an
+// agent-scope acquire by every workgroup, for phases that exchange data by
+// plain loads and stores (PageRank, filter bitmaps, serving).  The acquires
+// of the workgroups of one XCD run one after the other: with them the barrier
+// took 3.5 us among 128 workgroups, 6.7 among 512 and 11.3 among 1,024, without
+// 2.3, 3.0 and 3.9.
+template <bool kFull, class S>
 __device__ bool grid_barrier(const Args &a, S &sm, Grid gr, unsigned long long &epoch, int round,
                              bool sys = false) {
   wait_memory();
@@ -1059,22 +1090,20 @@ __device__ bool grid_barrier(const Args &a, S &sm, Grid gr, unsigned long long &
     unsigned long long *b = a.bar;
     const unsigned long long target = epoch + 1;
     const unsigned long long o1 = add_relaxed(&b[kBarXcdArrive + (size_t)kBarStride * gr.xcd], 1ull);
-    bool ok;
     if ((o1 + 1) % gr.xcd_n == 0) {
       // the XCD's last arrival releases every store its members made before
       // arriving; `sys`: to the host as well (stores into host memory)
-      if (sys)
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
-      else
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      if constexpr (kFull) {
+        if (sys)
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
+        else
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      }
       const unsigned long long o2 = add_relaxed(&b[kBarRoot], 1ull);
       if ((o2 + 1) % gr.n_xcd == 0) st_relaxed(&b[kBarGen], target);
-      ok = bar_wait(a, &b[kBarGen], target, round);
-      if (ok) st_relaxed(&b[kBarXcdFlag + (size_t)kBarStride * gr.xcd], target);
-    } else {
-      ok = bar_wait(a, &b[kBarXcdFlag + (size_t)kBarStride * gr.xcd], target, round);
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    const bool ok = bar_wait(a, &b[kBarGen], target, round);
+    if constexpr (kFull) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     sm.flag = ok ? 1 : 0;
   }
   __syncthreads();
@@ -1408,7 +1437,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
       if (build) {
         build_filter<B, Op>(a, gr, &a.ctl->filt_count[r & 1]);
         bool ok;
-        [[clang::always_inline]] ok = grid_barrier(a, sm, gr, epoch, r);
+        [[clang::always_inline]] ok = grid_barrier<true>(a, sm, gr, epoch, r);
         if (!ok) break;
         if constexpr (std::is_same<Op, OpBFS>::value)
           filtered = true;
@@ -1442,9 +1471,9 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
     uint64_t pb = a.profile ? (uint64_t)wall_clock64() : 0;
     bool ok1;
     if constexpr (F) {
-      [[clang::always_inline]] ok1 = grid_barrier(a, sm, gr, epoch, r);
+      [[clang::always_inline]] ok1 = grid_barrier<Op::kPR>(a, sm, gr, epoch, r);
     } else {
-      ok1 = grid_barrier(a, sm, gr, epoch, r);
+      ok1 = grid_barrier<Op::kPR>(a, sm, gr, epoch, r);
     }
     if (!ok1) break;
     prof_mark(a, acc, kProfBarrier, pb);
@@ -1468,9 +1497,9 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
       pb = a.profile ? (uint64_t)wall_clock64() : 0;
       bool ok2;
       if constexpr (F) {
-        [[clang::always_inline]] ok2 = grid_barrier(a, sm, gr, epoch, r);
+        [[clang::always_inline]] ok2 = grid_barrier<Op::kPR>(a, sm, gr, epoch, r);
       } else {
-        ok2 = grid_barrier(a, sm, gr, epoch, r);
+        ok2 = grid_barrier<Op::kPR>(a, sm, gr, epoch, r);
       }
       if (!ok2) break;
       prof_mark(a, acc, kProfBarrier, pb);
@@ -1479,7 +1508,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
     if (a.prof_wg) prof_round_edges(a, acc, prof_last, gr.id, r);
     if constexpr (Op::kPR) {
       phase_pr_update<B>(a, gr, ld_relaxed(&a.ctl->dangling[r & 1]));
-      if (!grid_barrier(a, sm, gr, epoch, r)) break;
+      if (!grid_barrier<true>(a, sm, gr, epoch, r)) break;
     }
   }
   if (gr.id == 0 && threadIdx.x == 0) {
@@ -1682,7 +1711,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
       phase_twc<B, Op, true>(a, op, sm, gr, r, round_frontier<true>(a, r), nF, qn, qn_cnt, &a.ctl->huge[r & 1],
                              thr, hs, acc);
     if (gr.id == 0 && threadIdx.x == 0) open_admit(a, r, nF);
-    if (!grid_barrier(a, sm, gr, epoch, r)) break;
+    if (!grid_barrier<true>(a, sm, gr, epoch, r)) break;
     if (ld_relaxed(&a.ctl->open_exit[r & 1])) break;
     if (gr.id == 0) open_complete<B>(a, r, &s_cnt);
     const uint32_t k = ld_relaxed(&a.ctl->admit_n[r & 1]);
@@ -1696,7 +1725,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
     if ((hc >> 32) != 0) phase_lb<B, Op, true>(a, op, sm, gr, r, hc, qn, qn_cnt, hs, acc);
     // a round that wrote finished labels into host memory releases them at
     // system scope on every XCD before workgroup 0 publishes the slots
-    if (!grid_barrier(a, sm, gr, epoch, r, nc != 0)) break;
+    if (!grid_barrier<true>(a, sm, gr, epoch, r, nc != 0)) break;
     if (tl) a.ctl->tl[4 * r + 2] = (unsigned long long)wall_clock64();
     if (nc && gr.id == 0 && threadIdx.x == 0) open_publish(a, r, nc);
   }
@@ -1907,7 +1936,7 @@ __device__ void pull_lb(const Args &a, Grid gr, unsigned long long hc, uint32_t 
       int32_t v = -1;
       unsigned long long x = 0;
       if (act) {
-        const int4 r = a.huge_rec[owner_of(a, vh, hs, (uint32_t)k)];
+        const int4 r = ld_rec(&a.huge_rec[owner_of(a, vh, hs, (uint32_t)k)]);
         v = r.z;
         x = to_fix(a.contrib[a.tcol[r.y + (int32_t)((uint32_t)k - (uint32_t)r.x)]]);
       }
@@ -1965,14 +1994,14 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
       st_relaxed(&a.ctl->dangling[(it + 1) & 1], 0ull);
     }
     pull_gather<B>(a, sm, gr, it, a.threshold, hs, acc);
-    if (!grid_barrier(a, sm, gr, epoch, it)) break;
+    if (!grid_barrier<true>(a, sm, gr, epoch, it)) break;
     const unsigned long long hc = ld_relaxed(&a.ctl->huge[it & 1]);
     if ((hc >> 32) != 0) {
       pull_lb<B>(a, gr, hc, hs, acc);
-      if (!grid_barrier(a, sm, gr, epoch, it)) break;
+      if (!grid_barrier<true>(a, sm, gr, epoch, it)) break;
     }
     pull_update<B>(a, sm, gr, it, acc);
-    if (!grid_barrier(a, sm, gr, epoch, it)) break;
+    if (!grid_barrier<true>(a, sm, gr, epoch, it)) break;
   }
   if (gr.id == 0 && threadIdx.x == 0) {
     st_relaxed(&a.ctl->rounds, (uint32_t)it);
