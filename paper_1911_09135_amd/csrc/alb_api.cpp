@@ -639,11 +639,14 @@ void fill_stats(alb_stats *st, const Ctl &c, int rounds, int launches, int64_t T
   st->kernel_launches = launches;
   st->launched_threads = T;
   st->huge_threshold = threshold;
-  st->frontier_vertices = (int64_t)c.st_frontier;
-  st->edges_examined = (int64_t)(c.st_edges_twc + c.st_edges_lb);
-  st->huge_vertices = (int64_t)c.st_huge_v;
-  st->huge_edges = (int64_t)c.st_edges_lb;
-  st->pushes = (int64_t)c.st_pushes;
+  unsigned long long sum[kStats] = {0};
+  for (int x = 0; x < kStatXcds; ++x)
+    for (int k = 0; k < kStats; ++k) sum[k] += c.stat[x][k].v;
+  st->frontier_vertices = (int64_t)sum[kStFrontier];
+  st->edges_examined = (int64_t)(sum[kStEdgesTwc] + sum[kStEdgesLb]);
+  st->huge_vertices = (int64_t)sum[kStHugeV];
+  st->huge_edges = (int64_t)sum[kStEdgesLb];
+  st->pushes = (int64_t)sum[kStPushes];
   st->device_ms = ms_all;
   st->kernel_ms = ms_k;
 }
@@ -833,14 +836,14 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
         HIP_TRY(hipMemcpyAsync(ws->h_ctl, ws->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, stream));
         HIP_TRY(hipStreamSynchronize(stream));
         if (ws->h_ctl->overflow != 0xffffffffu) break;
-        if (ws->h_ctl->qcount[r % 3] == 0) break;
+        if (ws->h_ctl->qcount[r % 3].v == 0) break;
       }
       HIP_TRY(launch_twc(job.op, wg, grid, a, stream));
       ++launches;
       HIP_TRY(hipMemcpyAsync(ws->h_ctl, ws->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, stream));
       HIP_TRY(hipStreamSynchronize(stream));
       if (ws->h_ctl->overflow != 0xffffffffu) break;
-      if ((ws->h_ctl->huge[r & 1] >> 32) != 0) {  // launch the LB kernel only when imbalance was found
+      if ((ws->h_ctl->huge[r & 1].v >> 32) != 0) {  // launch the LB kernel only when imbalance was found
         HIP_TRY(launch_lb(job.op, wg, grid, a, stream));
         ++launches;
       }
@@ -870,7 +873,7 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
       if (prof.p) print_skew(prof.p, std::min(rounds, kTimeline), (int)std::min<uint32_t>(c.n_members, kProfMembers));
     }
   }
-  if (!job.all_rounds && job.max_rounds > 1 && rounds >= job.max_rounds && c.qcount[rounds % 3] != 0)
+  if (!job.all_rounds && job.max_rounds > 1 && rounds >= job.max_rounds && c.qcount[rounds % 3].v != 0)
     return fail(ALB_E_DEVICE, "no convergence within %d rounds", job.max_rounds);
 
   if (st) fill_stats(st, c, rounds, launches, T, threshold, ws->ev[0], ws->ev[1], ws->ev[2]);
@@ -1120,7 +1123,7 @@ alb_status finish_batch(alb_graph g, const BatchJob &j, BatchWs *ws, int32_t *co
     return fail(ALB_E_OVERFLOW, "a worklist exceeded its capacity of %u entries in round %u", j.a.qcap, c.overflow);
   const int rounds = (int)c.rounds;
   if (getenv("ALB_TIMELINE")) print_timeline(c, (int)j.op, rounds, (long long)c.threshold_used, g->clock_khz);
-  if (rounds >= j.a.max_rounds && c.qcount[rounds % 3] != 0)
+  if (rounds >= j.a.max_rounds && c.qcount[rounds % 3].v != 0)
     return fail(ALB_E_DEVICE, "no convergence within %d rounds", j.a.max_rounds);
   if (!j.o.out_on_device) {  // straight from the staging area into each query's host array
     for (int32_t q = 0; q < j.count; ++q)
@@ -1859,8 +1862,8 @@ alb_status alb_trace_round(alb_graph g, const int32_t *frontier, int64_t nf, con
   }
   Workspace *ws = ro.ws;
   const Ctl &c = *ws->h_ctl;
-  const uint32_t vh = (uint32_t)(c.huge[0] >> 32), ehuge = (uint32_t)c.huge[0];
-  const uint32_t nn = std::min(c.qcount[1], ro.qcap);
+  const uint32_t vh = (uint32_t)(c.huge[0].v >> 32), ehuge = (uint32_t)c.huge[0].v;
+  const uint32_t nn = std::min(c.qcount[1].v, ro.qcap);
   std::vector<int4> hr(vh);
   bool ok = true;
   ok = ok && hipMemcpy(bins, d_bins, (size_t)nf, hipMemcpyDeviceToHost) == hipSuccess;

@@ -85,29 +85,37 @@ struct OpenShared {
   int32_t fin[kOpenRing];                // slot of completion i at fin[i % kOpenRing]
 };
 
+// A word that many workgroups update by atomics, on a cache line of its own:
+// atomics on one 64-byte block complete one every 12 ns, whichever of its
+// words they address, while blocks do not disturb each other.
+template <class T>
+struct alignas(128) Line {
+  T v;
+};
+
+// Statistics summed over rounds.  Every workgroup adds to the words of its own
+// XCD (a hundred of them on each instead of all workgroups on one).
+constexpr int kStatXcds = 8;  // XCC_ID modulo this
+enum { kStFrontier = 0, kStEdgesTwc, kStEdgesLb, kStHugeV, kStPushes, kStats };
+
 // Per-call control block in device memory.  Counters rotate by round so that
 // one round can clear the counter two rounds ahead without a separate launch.
 struct Ctl {
-  uint32_t qcount[3];             // worklist sizes: round r reads [r % 3], pushes into [(r + 1) % 3]
-  uint32_t overflow;              // first round in which a worklist overflowed (0xffffffff: none)
-  unsigned long long huge[2];     // round r: (count << 32) | edge total of the huge worklist, [r & 1]
-  uint32_t rounds;                // rounds completed (written by workgroup 0)
-  uint32_t pad0;
-  unsigned long long dangling[2]; // PageRank: rank mass without out-edges (fixed point), iteration it in [it & 1]
-  alignas(256) unsigned long long chunk[3]; // worklist entries claimed in phase 1 of round r: [r % 3]
-  alignas(256) uint32_t abort;    // a barrier wait timed out; every workgroup leaves
+  Line<uint32_t> qcount[3];          // worklist sizes: round r reads [r % 3], pushes into [(r + 1) % 3]
+  Line<unsigned long long> huge[2];  // round r: (count << 32) | edge total of the huge worklist, [r & 1]
+  Line<unsigned long long> dangling[2]; // PageRank: rank mass without out-edges (fixed point), iteration it in [it & 1]
+  Line<unsigned long long> chunk[3]; // worklist entries claimed in phase 1 of round r: [r % 3]
+  alignas(128) uint32_t overflow;    // first round in which a worklist overflowed (0xffffffff: none)
+  uint32_t rounds;                   // rounds completed (written by workgroup 0)
+  uint32_t abort;                 // a barrier wait timed out; every workgroup leaves
   uint32_t diag_round;            // round of the wait that timed out
   unsigned long long diag_seen;   // generation it observed
   unsigned long long diag_target; // generation it waited for
-  unsigned long long members;     // persistent launch: tickets taken (top bit: membership closed)
-  uint32_t n_members;             // member count, published when membership closes
-  uint32_t pad1;
   long long threshold_used;       // huge threshold the persistent launch used
-  alignas(256) unsigned long long st_frontier;  // statistics, summed over rounds
-  unsigned long long st_edges_twc;
-  unsigned long long st_edges_lb;
-  unsigned long long st_huge_v;
-  unsigned long long st_pushes;
+  alignas(128) uint32_t leader;   // persistent launch: first members of their XCD that have asked to lead
+  alignas(128) uint32_t n_members;   // member count, published when membership closes ...
+  uint32_t xcd_members[kBarXcds];    // ... and how many of them each XCD holds
+  Line<unsigned long long> stat[kStatXcds][kStats];
   // per-round timeline of the persistent launch (first kTimeline rounds):
   // wall-clock ticks at round start, after the inspection/TWC phase and after
   // the execution phase, and (worklist size | huge count << 32)
@@ -119,7 +127,7 @@ struct Ctl {
   // and when member 0 left the round loop
   unsigned long long t_begin, t_end;
   // reached-vertex filter: vertices whose bit the build of round r set, at [r & 1]
-  unsigned long long filt_count[2];
+  Line<unsigned long long> filt_count[2];
   // continuous serving (member 0's bookkeeping): requests taken, slots
   // admitted in round r, its exit decision and the slots it converts
   // (finished in round r - 1), each at [r & 1] (a slow member may still read

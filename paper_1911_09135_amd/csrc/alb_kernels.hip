@@ -51,6 +51,12 @@ __device__ __forceinline__ uint32_t bits_below(unsigned long long m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
+// The XCD (accelerator complex die, one L2) the calling wave runs on: the
+// XCC_ID hardware register, bits [3:0].
+__device__ __forceinline__ uint32_t xcd_id() {
+  return __builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20) & (uint32_t)(kBarXcds - 1);
+}
+
 template <class T>
 __device__ __forceinline__ T ld_relaxed(T *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -424,7 +430,7 @@ struct Smem {
   V sv[kU * B];
   int32_t src[(Op::kNeedSrc || M) ? kU * B : 1];
   int32_t wsum[B / kWave];
-  unsigned long long ured[B / kWave][5];
+  unsigned long long ured[B / kWave][kStats];
   unsigned long long dred[B / kWave];
   int32_t owner, obeg, odeg, ov;
   V osv;
@@ -462,23 +468,20 @@ template <int B, class Op, bool M>
 __device__ void flush_stats(Acc &acc, Smem<B, Op, M> &sm, Ctl *c) {
   const uint32_t lane = lane_id();
   const int w = threadIdx.x / kWave;
-  unsigned long long v[5] = {acc.frontier, acc.edges_twc, acc.edges_lb, acc.huge_v, acc.pushes};
+  unsigned long long v[kStats] = {acc.frontier, acc.edges_twc, acc.edges_lb, acc.huge_v, acc.pushes};
 #pragma unroll
-  for (int k = 0; k < 5; ++k) {
+  for (int k = 0; k < kStats; ++k) {
 #pragma unroll
     for (int d = kWave / 2; d > 0; d >>= 1) v[k] += __shfl_xor(v[k], d);
     if (lane == 0) sm.ured[w][k] = v[k];
   }
   __syncthreads();
+  if (threadIdx.x < kStats) {
+    unsigned long long t = 0;
+    for (int j = 0; j < B / kWave; ++j) t += sm.ured[j][threadIdx.x];
+    if (t) add_relaxed(&c->stat[xcd_id() % kStatXcds][threadIdx.x].v, t);
+  }
   if (threadIdx.x == 0) {
-    unsigned long long t[5] = {0, 0, 0, 0, 0};
-    for (int j = 0; j < B / kWave; ++j)
-      for (int k = 0; k < 5; ++k) t[k] += sm.ured[j][k];
-    if (t[0]) add_relaxed(&c->st_frontier, t[0]);
-    if (t[1]) add_relaxed(&c->st_edges_twc, t[1]);
-    if (t[2]) add_relaxed(&c->st_edges_lb, t[2]);
-    if (t[3]) add_relaxed(&c->st_huge_v, t[3]);
-    if (t[4]) add_relaxed(&c->st_pushes, t[4]);
     for (int k = 0; k < kProfParts; ++k)
       if (acc.prof[k]) add_relaxed(&c->prof[k], acc.prof[k]);
   }
@@ -764,7 +767,7 @@ __device__ void phase_twc(const Args &a, const Op &op, S &sm, Grid gr, int round
   const uint32_t lane = lane_id();
   const int32_t gt = (int32_t)(gr.id * B + tid);
   const uint32_t tag = (uint32_t)round + 1u;
-  unsigned long long *claim = &a.ctl->chunk[round % 3];
+  unsigned long long *claim = &a.ctl->chunk[round % 3].v;
   Pusher<Entry<M>> pu{sm.pbuf[tid / kWave], 0u, qn, qn_cnt};
   uint64_t pt = a.profile ? (uint64_t)wall_clock64() : 0;
   Claims cl(nF, gr, B);
@@ -1029,12 +1032,6 @@ __device__ void phase_pr_update(const Args &a, Grid gr, unsigned long long dangl
   }
 }
 
-// The XCD (accelerator complex die, one L2) the calling wave runs on: the
-// XCC_ID hardware register, bits [3:0].
-__device__ __forceinline__ uint32_t xcd_id() {
-  return __builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20) & (uint32_t)(kBarXcds - 1);
-}
-
 // Wait until every memory operation this wave issued has completed; also a
 // compiler barrier, so no load or store moves across it.
 __device__ __forceinline__ void wait_memory() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
@@ -1046,7 +1043,9 @@ __device__ __forceinline__ bool bar_wait(const Args &a, unsigned long long *w, u
   Ctl *c = a.ctl;
   const uint64_t t0 = (uint64_t)wall_clock64();
   unsigned long long seen;
-  while ((seen = ld_relaxed(w)) < target) {
+  for (uint32_t look = 0; (seen = ld_relaxed(w)) < target; ++look) {
+    __builtin_amdgcn_s_sleep(1);
+    if (look % 16 != 15) continue;  // the rest costs another round trip
     if (ld_relaxed(&c->abort)) return false;
     if ((uint64_t)wall_clock64() - t0 > a.timeout_ticks) {
       st_relaxed(&c->diag_seen, seen);
@@ -1055,7 +1054,6 @@ __device__ __forceinline__ bool bar_wait(const Args &a, unsigned long long *w, u
       st_relaxed(&c->abort, 1u);
       return false;
     }
-    __builtin_amdgcn_s_sleep(1);
   }
   return true;
 }
@@ -1123,7 +1121,7 @@ __device__ __forceinline__ Entry<M> *round_next(const Args &a, int r) {
 
 __device__ __forceinline__ uint32_t round_size(const Args &a, int r) {
   if (a.all_rounds) return (uint32_t)a.n;
-  const uint32_t c = ld_relaxed(&a.ctl->qcount[r % 3]);
+  const uint32_t c = ld_relaxed(&a.ctl->qcount[r % 3].v);
   return c < a.qcap ? c : a.qcap;
 }
 
@@ -1137,87 +1135,89 @@ __device__ __forceinline__ int64_t round_threshold(const Args &a, uint32_t nF, u
 
 // Clear the counters ahead (nobody reads or writes them this round).
 __device__ __forceinline__ void clear_ahead(const Args &a, int r) {
-  st_relaxed(&a.ctl->chunk[(r + 1) % 3], 0ull);
-  st_relaxed(&a.ctl->qcount[(r + 2) % 3], 0u);
-  st_relaxed(&a.ctl->huge[(r + 1) & 1], 0ull);
-  st_relaxed(&a.ctl->dangling[(r + 1) & 1], 0ull);
+  st_relaxed(&a.ctl->chunk[(r + 1) % 3].v, 0ull);
+  st_relaxed(&a.ctl->qcount[(r + 2) % 3].v, 0u);
+  st_relaxed(&a.ctl->huge[(r + 1) & 1].v, 0ull);
+  st_relaxed(&a.ctl->dangling[(r + 1) & 1].v, 0ull);
 }
 
 // Membership of the persistent launch.  The grid may be larger than what the
 // device can hold at once, so co-residency is not assumed: every workgroup
-// takes a ticket from ctl->members when it starts; the holder of ticket 0
-// closes membership (sets the top bit) once all workgroups have joined or
-// no new one has joined for join_window_ticks, and publishes the member
-// count.  A workgroup whose ticket shows the closed bit is not a member and
-// leaves at once.  Members are running when they join and never leave before
-// the end, so every barrier among them completes.  Each member also counts
-// itself on its XCD, for the barrier.  Returns false for a non-member; *gr
-// gets (ticket, member count, XCD, members on that XCD, XCDs in use).
+// takes a ticket from its XCD's counter when it starts (one counter for all
+// would take 12 ns per workgroup, 10 us for 800).  The XCDs' first ticket
+// holders elect a leader, which closes membership (sets the counters' top
+// bits) once all workgroups have joined or no new one has joined for
+// join_window_ticks, and publishes the member counts.  A workgroup whose
+// ticket shows the closed bit is not a member and leaves at once.  Members are
+// running when they join and never leave before the end, so every barrier
+// among them completes.  Returns false for a non-member; *gr gets (index,
+// member count, XCD, members on that XCD, XCDs in use).  Indices go round the
+// XCDs: all first tickets, then all second ones, and so on.
 template <class S>
 __device__ bool join_members(const Args &a, S &sm, Grid *gr) {
   constexpr unsigned long long kClosed = 1ull << 63;
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < kWave) {  // the first wavefront; lane k looks after XCD k's counter
     Ctl *c = a.ctl;
-    const unsigned long long t = add_relaxed(&c->members, 1ull);
-    uint32_t member = (t & kClosed) ? 0u : 1u;
+    const uint32_t lane = lane_id();
     const uint32_t x = xcd_id();
-    if (member) add_relaxed(&a.bar[kBarXcdMembers + (size_t)kBarStride * x], 1ull);
-    if (member && t == 0) {
-      unsigned long long seen = 1;
+    unsigned long long t = 0;
+    if (lane == 0) t = add_relaxed(&a.bar[kBarXcdMembers + (size_t)kBarStride * x], 1ull);
+    t = __shfl(t, 0);
+    const bool member = (t & kClosed) == 0;
+    uint32_t lead = 1;
+    if (lane == 0 && member && t == 0) lead = add_relaxed(&c->leader, 1u);
+    lead = __shfl(lead, 0);
+    if (member && lead == 0) {
+      unsigned long long *mine = &a.bar[kBarXcdMembers + (size_t)kBarStride * (lane % kBarXcds)];
+      unsigned long long seen = 0, cnt = 0;
       uint64_t t_last = (uint64_t)wall_clock64();
-      st_relaxed(&c->t_begin, (unsigned long long)t_last);
+      if (lane == 0) st_relaxed(&c->t_begin, (unsigned long long)t_last);
       for (;;) {
-        const unsigned long long cur = ld_relaxed(&c->members);
-        if (cur >= (unsigned long long)gridDim.x) break;
-        const uint64_t now = (uint64_t)wall_clock64();
-        if (cur != seen) {
-          seen = cur;
+        cnt = lane < (uint32_t)kBarXcds ? ld_relaxed(mine) : 0ull;
+        unsigned long long tot = cnt;
+#pragma unroll
+        for (int d = kBarXcds / 2; d > 0; d >>= 1) tot += __shfl_xor(tot, d);
+        tot = __shfl(tot, 0);
+        if (tot >= (unsigned long long)gridDim.x) break;
+        const uint64_t now = (uint64_t)__shfl((unsigned long long)wall_clock64(), 0);
+        if (tot != seen) {
+          seen = tot;
           t_last = now;
         } else if (now - t_last > a.join_window_ticks) {
+          if (lane < (uint32_t)kBarXcds)
+            cnt = __hip_atomic_fetch_or(mine, kClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           break;
         }
         __builtin_amdgcn_s_sleep(1);
       }
-      const unsigned long long prev =
-          __hip_atomic_fetch_or(&c->members, kClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      st_relaxed(&c->n_members, (uint32_t)prev);
+      uint32_t n = (uint32_t)cnt;
+      if (lane < (uint32_t)kBarXcds) st_relaxed(&c->xcd_members[lane], n);
+#pragma unroll
+      for (int d = kBarXcds / 2; d > 0; d >>= 1) n += __shfl_xor(n, d);
+      wait_memory();  // the counts are in memory before the total announces them
+      if (lane == 0) st_relaxed(&c->n_members, n);
     }
-    uint32_t n = 0, xn = 1, nx = 1;
+    uint32_t n = 0, cnt = 0;
     if (member) {
       while ((n = ld_relaxed(&c->n_members)) == 0) __builtin_amdgcn_s_sleep(1);
-      if ((uint32_t)t >= n) member = 0;  // cannot happen: tickets below the closing count are members
-      // every member registers its XCD right after its ticket: wait until all
-      // n have, then the per-XCD counts are final (a bounded wait; past the
-      // barrier time-out the launch is aborted)
-      const uint64_t t0 = (uint64_t)wall_clock64();
-      for (;;) {
-        unsigned long long tot = 0;
-        nx = 0;
-        for (int k = 0; k < kBarXcds; ++k) {
-          const unsigned long long v = ld_relaxed(&a.bar[kBarXcdMembers + (size_t)kBarStride * k]);
-          tot += v;
-          nx += v ? 1u : 0u;
-        }
-        if (tot >= n) break;
-        if ((uint64_t)wall_clock64() - t0 > a.timeout_ticks) {
-          st_relaxed(&c->abort, 1u);
-          break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-      }
-      xn = (uint32_t)ld_relaxed(&a.bar[kBarXcdMembers + (size_t)kBarStride * x]);
-      if (xn == 0 || nx == 0) {  // only after an abort: keep the barrier arithmetic defined
-        xn = 1;
-        nx = 1;
-      }
+      cnt = lane < (uint32_t)kBarXcds ? ld_relaxed(&c->xcd_members[lane]) : 0u;
     }
+    // members before this one: those with smaller tickets, and equal ones on earlier XCDs
+    const uint32_t tk = (uint32_t)t;
+    uint32_t before = min(cnt, tk) + (lane < x && cnt > tk ? 1u : 0u);
+#pragma unroll
+    for (int d = kBarXcds / 2; d > 0; d >>= 1) before += __shfl_xor(before, d);
+    const uint32_t used = (uint32_t)__popcll(__ballot(cnt != 0));
+    const uint32_t xn = __shfl(cnt, (int)x);
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    sm.flag = (int32_t)member;
-    sm.ticket = (uint32_t)t;
-    sm.members = n;
-    sm.xcd = x;
-    sm.xcd_n = xn;
-    sm.n_xcd = nx;
+    if (lane == 0) {
+      sm.flag = member ? 1 : 0;
+      sm.ticket = before;
+      sm.members = n;
+      sm.xcd = x;
+      sm.xcd_n = xn;
+      sm.n_xcd = used;
+    }
   }
   __syncthreads();
   const bool member = sm.flag != 0;
@@ -1233,6 +1233,33 @@ __device__ bool join_members(const Args &a, S &sm, Grid *gr) {
 // ---------------------------------------------------------------------------
 // Kernels.
 // ---------------------------------------------------------------------------
+
+// The control block of a launch whose round 0 has nfront0 worklist entries
+// (one thread).
+__device__ void reset_ctl(const Args &a, uint32_t nfront0) {
+  Ctl *c = a.ctl;
+  for (int k = 0; k < 3; ++k) {
+    c->qcount[k].v = k == 0 ? nfront0 : 0u;
+    c->chunk[k].v = 0;
+  }
+  for (int k = 0; k < 2; ++k) {
+    c->huge[k].v = 0;
+    c->dangling[k].v = 0;
+    c->filt_count[k].v = 0;
+  }
+  c->overflow = 0xffffffffu;
+  c->abort = 0;
+  c->rounds = 0;
+  for (int x = 0; x < kStatXcds; ++x)
+    for (int k = 0; k < kStats; ++k) c->stat[x][k].v = 0;
+  c->leader = 0;
+  c->n_members = 0;
+  c->diag_seen = c->diag_target = 0;
+  c->diag_round = 0;
+  c->threshold_used = a.threshold;
+  for (int k = 0; k < kProfParts; ++k) c->prof[k] = 0;
+  c->t_begin = c->t_end = 0;
+}
 
 __global__ void k_init(Args a, int op, int32_t source, uint32_t nfront0) {
   const uint32_t stride = gridDim.x * blockDim.x;
@@ -1250,27 +1277,7 @@ __global__ void k_init(Args a, int op, int32_t source, uint32_t nfront0) {
   }
   for (size_t i = t; i < kBarWords; i += stride) a.bar[i] = 0ull;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    Ctl *c = a.ctl;
-    c->qcount[0] = nfront0;
-    c->qcount[1] = 0;
-    c->qcount[2] = 0;
-    c->chunk[0] = c->chunk[1] = c->chunk[2] = 0;
-    c->overflow = 0xffffffffu;
-    c->huge[0] = 0;
-    c->huge[1] = 0;
-    c->abort = 0;
-    c->rounds = 0;
-    c->st_frontier = c->st_edges_twc = c->st_edges_lb = c->st_huge_v = c->st_pushes = 0;
-    c->dangling[0] = 0;
-    c->dangling[1] = 0;
-    c->filt_count[0] = c->filt_count[1] = 0;
-    c->members = 0;
-    c->n_members = 0;
-    c->diag_seen = c->diag_target = 0;
-    c->diag_round = 0;
-    c->threshold_used = a.threshold;
-    for (int k = 0; k < kProfParts; ++k) c->prof[k] = 0;
-    c->t_begin = c->t_end = 0;
+    reset_ctl(a, nfront0);
     if (source >= 0 && op != OP_RECORD) ((int32_t *)a.q0)[0] = source;
   }
 }
@@ -1291,25 +1298,7 @@ __global__ void k_init_batch(Args a, int op) {
     if (op == OP_SSSP) a.word[i] = (unsigned long long)(uint32_t)kInf << 32;
   }
   for (size_t i = t; i < kBarWords; i += stride) a.bar[i] = 0ull;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    Ctl *c = a.ctl;
-    c->qcount[0] = (uint32_t)a.nq;
-    c->qcount[1] = c->qcount[2] = 0;
-    c->chunk[0] = c->chunk[1] = c->chunk[2] = 0;
-    c->overflow = 0xffffffffu;
-    c->huge[0] = c->huge[1] = 0;
-    c->abort = 0;
-    c->rounds = 0;
-    c->st_frontier = c->st_edges_twc = c->st_edges_lb = c->st_huge_v = c->st_pushes = 0;
-    c->dangling[0] = c->dangling[1] = 0;
-    c->members = 0;
-    c->n_members = 0;
-    c->diag_seen = c->diag_target = 0;
-    c->diag_round = 0;
-    c->threshold_used = a.threshold;
-    for (int k = 0; k < kProfParts; ++k) c->prof[k] = 0;
-    c->t_begin = c->t_end = 0;
-  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) reset_ctl(a, (uint32_t)a.nq);
 }
 
 // Batch set-up, part 2: query q's source gets label 0 and is entry q of the
@@ -1344,9 +1333,9 @@ __global__ __launch_bounds__(B) void k_twc(Args a, Op op) {
   const Grid gr{blockIdx.x, gridDim.x};
   const int64_t thr = round_threshold(a, nF, (uint64_t)gr.n * B);
   phase_twc<B, Op, false>(a, op, sm, gr, r, round_frontier<false>(a, r), nF, round_next<false>(a, r),
-                          &a.ctl->qcount[(r + 1) % 3],
-                   &a.ctl->huge[r & 1], thr, hint_shift(thr), acc);
-  if constexpr (Op::kPR) flush_dangling<B, Op>(acc, sm, &a.ctl->dangling[r & 1]);
+                          &a.ctl->qcount[(r + 1) % 3].v,
+                   &a.ctl->huge[r & 1].v, thr, hint_shift(thr), acc);
+  if constexpr (Op::kPR) flush_dangling<B, Op>(acc, sm, &a.ctl->dangling[r & 1].v);
   flush_stats<B, Op>(acc, sm, a.ctl);
 }
 
@@ -1355,17 +1344,17 @@ __global__ __launch_bounds__(B) void k_lb(Args a, Op op) {
   __shared__ Smem<B, Op> sm;
   Acc acc;
   const int r = a.round;
-  const unsigned long long hc = ld_relaxed(&a.ctl->huge[r & 1]);
+  const unsigned long long hc = ld_relaxed(&a.ctl->huge[r & 1].v);
   const int64_t thr = round_threshold(a, round_size(a, r), (uint64_t)gridDim.x * B);
   phase_lb<B, Op, false>(a, op, sm, Grid{blockIdx.x, gridDim.x}, r, hc, round_next<false>(a, r),
-                         &a.ctl->qcount[(r + 1) % 3],
+                         &a.ctl->qcount[(r + 1) % 3].v,
                   hint_shift(thr), acc);
   flush_stats<B, Op>(acc, sm, a.ctl);
 }
 
 template <int B>
 __global__ __launch_bounds__(B) void k_pr_update(Args a) {
-  phase_pr_update<B>(a, Grid{blockIdx.x, gridDim.x}, ld_relaxed(&a.ctl->dangling[a.round & 1]));
+  phase_pr_update<B>(a, Grid{blockIdx.x, gridDim.x}, ld_relaxed(&a.ctl->dangling[a.round & 1].v));
   if (blockIdx.x == 0 && threadIdx.x == 0) st_relaxed(&a.ctl->rounds, (uint32_t)a.round + 1u);
 }
 
@@ -1433,23 +1422,23 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
       }
       // the next round's count: nobody reads it before then (this round's
       // members read [r & 1] right after the build's barrier)
-      if (gr.id == 0 && threadIdx.x == 0) st_relaxed(&a.ctl->filt_count[(r + 1) & 1], 0ull);
+      if (gr.id == 0 && threadIdx.x == 0) st_relaxed(&a.ctl->filt_count[(r + 1) & 1].v, 0ull);
       if (build) {
-        build_filter<B, Op>(a, gr, &a.ctl->filt_count[r & 1]);
+        build_filter<B, Op>(a, gr, &a.ctl->filt_count[r & 1].v);
         bool ok;
         [[clang::always_inline]] ok = grid_barrier<true>(a, sm, gr, epoch, r);
         if (!ok) break;
         if constexpr (std::is_same<Op, OpBFS>::value)
           filtered = true;
         else
-          filtered = 2 * ld_relaxed(&a.ctl->filt_count[r & 1]) >= (unsigned long long)a.n;
+          filtered = 2 * ld_relaxed(&a.ctl->filt_count[r & 1].v) >= (unsigned long long)a.n;
       }
     }
     const bool tl = gr.id == 0 && threadIdx.x == 0 && r < kTimeline;
     if (gr.id == 0 && threadIdx.x == 0) clear_ahead(a, r);
     if (tl) a.ctl->tl[4 * r] = (unsigned long long)wall_clock64();
     Entry<M> *qn = round_next<M>(a, r);
-    uint32_t *qn_cnt = &a.ctl->qcount[(r + 1) % 3];
+    uint32_t *qn_cnt = &a.ctl->qcount[(r + 1) % 3].v;
     const int64_t thr = round_threshold(a, nF, (uint64_t)gr.n * B);
     // batch with per-query thresholds: chunk index sized for the smallest one
     const uint32_t hs = hint_shift(M && a.qthr ? a.qthr_min : thr);
@@ -1458,16 +1447,16 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
         using FOp = typename Filtered<Op>::type;
         const FOp fop = Filtered<Op>::make(op, a);
         [[clang::always_inline]] phase_twc<B, FOp, M>(a, fop, sm, gr, r, round_frontier<M>(a, r), nF, qn, qn_cnt,
-                                                      &a.ctl->huge[r & 1], thr, hs, acc);
+                                                      &a.ctl->huge[r & 1].v, thr, hs, acc);
       } else {
         [[clang::always_inline]] phase_twc<B, Op, M>(a, op, sm, gr, r, round_frontier<M>(a, r), nF, qn, qn_cnt,
-                                                     &a.ctl->huge[r & 1], thr, hs, acc);
+                                                     &a.ctl->huge[r & 1].v, thr, hs, acc);
       }
     } else {
-      phase_twc<B, Op, M>(a, op, sm, gr, r, round_frontier<M>(a, r), nF, qn, qn_cnt, &a.ctl->huge[r & 1], thr, hs,
+      phase_twc<B, Op, M>(a, op, sm, gr, r, round_frontier<M>(a, r), nF, qn, qn_cnt, &a.ctl->huge[r & 1].v, thr, hs,
                           acc);
     }
-    if constexpr (Op::kPR) flush_dangling<B, Op>(acc, sm, &a.ctl->dangling[r & 1]);
+    if constexpr (Op::kPR) flush_dangling<B, Op>(acc, sm, &a.ctl->dangling[r & 1].v);
     uint64_t pb = a.profile ? (uint64_t)wall_clock64() : 0;
     bool ok1;
     if constexpr (F) {
@@ -1477,7 +1466,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
     }
     if (!ok1) break;
     prof_mark(a, acc, kProfBarrier, pb);
-    const unsigned long long hc = ld_relaxed(&a.ctl->huge[r & 1]);
+    const unsigned long long hc = ld_relaxed(&a.ctl->huge[r & 1].v);
     if (tl) {
       a.ctl->tl[4 * r + 1] = (unsigned long long)wall_clock64();
       a.ctl->tl[4 * r + 3] = (unsigned long long)nF | ((hc >> 32) << 32);
@@ -1507,7 +1496,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
     if (tl) a.ctl->tl[4 * r + 2] = (unsigned long long)wall_clock64();
     if (a.prof_wg) prof_round_edges(a, acc, prof_last, gr.id, r);
     if constexpr (Op::kPR) {
-      phase_pr_update<B>(a, gr, ld_relaxed(&a.ctl->dangling[r & 1]));
+      phase_pr_update<B>(a, gr, ld_relaxed(&a.ctl->dangling[r & 1].v));
       if (!grid_barrier<true>(a, sm, gr, epoch, r)) break;
     }
   }
@@ -1661,7 +1650,7 @@ __device__ void open_prepare(const Args &a, Grid gr, int B, int r, uint32_t k, u
   }
   if (k && gr.id == 0 && threadIdx.x == 0) {
     unsigned long long *F = (unsigned long long *)(((r + 1) & 1) ? a.q1 : a.q0);
-    const uint32_t at = add_relaxed(&a.ctl->qcount[(r + 1) % 3], k);  // beside the cyclic phase's pushes
+    const uint32_t at = add_relaxed(&a.ctl->qcount[(r + 1) % 3].v, k);  // beside the cyclic phase's pushes
     for (uint32_t i = 0; i < k; ++i) {
       const int32_t slot = admit[i];
       if (at + i < a.qcap)
@@ -1704,11 +1693,11 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
     if (gr.id == 0 && threadIdx.x == 0) clear_ahead(a, r);
     if (tl) a.ctl->tl[4 * r] = (unsigned long long)wall_clock64();
     Entry<true> *qn = round_next<true>(a, r);
-    uint32_t *qn_cnt = &a.ctl->qcount[(r + 1) % 3];
+    uint32_t *qn_cnt = &a.ctl->qcount[(r + 1) % 3].v;
     const int64_t thr = round_threshold(a, nF, (uint64_t)gr.n * B);
     const uint32_t hs = hint_shift(thr);
     if (nF)
-      phase_twc<B, Op, true>(a, op, sm, gr, r, round_frontier<true>(a, r), nF, qn, qn_cnt, &a.ctl->huge[r & 1],
+      phase_twc<B, Op, true>(a, op, sm, gr, r, round_frontier<true>(a, r), nF, qn, qn_cnt, &a.ctl->huge[r & 1].v,
                              thr, hs, acc);
     if (gr.id == 0 && threadIdx.x == 0) open_admit(a, r, nF);
     if (!grid_barrier<true>(a, sm, gr, epoch, r)) break;
@@ -1717,7 +1706,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
     const uint32_t k = ld_relaxed(&a.ctl->admit_n[r & 1]);
     const uint32_t nc = ld_relaxed(&a.ctl->conv_n[r & 1]);
     open_prepare<Op>(a, gr, B, r, k, nc);
-    const unsigned long long hc = nF ? ld_relaxed(&a.ctl->huge[r & 1]) : 0ull;
+    const unsigned long long hc = nF ? ld_relaxed(&a.ctl->huge[r & 1].v) : 0ull;
     if (tl) {
       a.ctl->tl[4 * r + 1] = (unsigned long long)wall_clock64();
       a.ctl->tl[4 * r + 3] = (unsigned long long)nF | ((hc >> 32) << 32);
@@ -1750,21 +1739,7 @@ __global__ void k_init_open(Args a) {
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     Ctl *c = a.ctl;
-    c->qcount[0] = c->qcount[1] = c->qcount[2] = 0;
-    c->chunk[0] = c->chunk[1] = c->chunk[2] = 0;
-    c->overflow = 0xffffffffu;
-    c->huge[0] = c->huge[1] = 0;
-    c->abort = 0;
-    c->rounds = 0;
-    c->st_frontier = c->st_edges_twc = c->st_edges_lb = c->st_huge_v = c->st_pushes = 0;
-    c->dangling[0] = c->dangling[1] = 0;
-    c->members = 0;
-    c->n_members = 0;
-    c->diag_seen = c->diag_target = 0;
-    c->diag_round = 0;
-    c->threshold_used = a.threshold;
-    for (int k = 0; k < kProfParts; ++k) c->prof[k] = 0;
-    c->t_begin = c->t_end = 0;
+    reset_ctl(a, 0u);
     c->open_head = 0;
     c->admit_n[0] = c->admit_n[1] = 0;
     c->open_done = 0;
@@ -1829,7 +1804,7 @@ __device__ void pull_gather(const Args &a, Smem<B, OpPRPull> &sm, Grid gr, int i
   const uint32_t nF = (uint32_t)a.n;
   Claims cl(nF, gr, B);
   for (;;) {
-    if (tid == 0) cl.next(&a.ctl->chunk[it % 3], nF, gr, B, sm.cbase, sm.clen);
+    if (tid == 0) cl.next(&a.ctl->chunk[it % 3].v, nF, gr, B, sm.cbase, sm.clen);
     __syncthreads();
     const unsigned long long base = sm.cbase;
     const uint32_t C = sm.clen;
@@ -1844,7 +1819,7 @@ __device__ void pull_gather(const Args &a, Smem<B, OpPRPull> &sm, Grid gr, int i
     }
     // inspection by in-degree (Algorithm 1); huge vertices wait for phase 2
     const bool huge = deg > 0 && (int64_t)deg >= thr;
-    reserve_huge(huge, v, beg, deg, 0, a, it, &a.ctl->huge[it & 1], hs, acc);
+    reserve_huge(huge, v, beg, deg, 0, a, it, &a.ctl->huge[it & 1].v, hs, acc);
     if (huge) deg = 0;
     acc.frontier += mine;
     acc.edges_twc += (unsigned long long)deg;
@@ -1964,7 +1939,7 @@ template <int B>
 __device__ void pull_update(const Args &a, Smem<B, OpPRPull> &sm, Grid gr, int it, Acc &acc) {
   const double d = (double)a.damping;
   const double N = (double)a.n;
-  const unsigned long long dfix = ld_relaxed(&a.ctl->dangling[it & 1]);
+  const unsigned long long dfix = ld_relaxed(&a.ctl->dangling[it & 1].v);
   const double base = (1.0 - d) / N + d * ((double)dfix * kFixInv) / N;
   for (uint32_t v = gr.id * B + threadIdx.x; v < (uint32_t)a.n; v += gr.n * B) {
     const float r = (float)(base + d * ((double)a.acc[v] * kFixInv));
@@ -1974,7 +1949,7 @@ __device__ void pull_update(const Args &a, Smem<B, OpPRPull> &sm, Grid gr, int i
     a.contrib[v] = od > 0 ? r / (float)od : 0.0f;
     if (od == 0) acc.dangling += to_fix(r);
   }
-  flush_dangling<B, OpPRPull>(acc, sm, &a.ctl->dangling[(it + 1) & 1]);
+  flush_dangling<B, OpPRPull>(acc, sm, &a.ctl->dangling[(it + 1) & 1].v);
 }
 
 template <int B>
@@ -1989,13 +1964,13 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
   int it = 0;
   for (; it < a.max_rounds; ++it) {
     if (gr.id == 0 && threadIdx.x == 0) {
-      st_relaxed(&a.ctl->chunk[(it + 1) % 3], 0ull);
-      st_relaxed(&a.ctl->huge[(it + 1) & 1], 0ull);
-      st_relaxed(&a.ctl->dangling[(it + 1) & 1], 0ull);
+      st_relaxed(&a.ctl->chunk[(it + 1) % 3].v, 0ull);
+      st_relaxed(&a.ctl->huge[(it + 1) & 1].v, 0ull);
+      st_relaxed(&a.ctl->dangling[(it + 1) & 1].v, 0ull);
     }
     pull_gather<B>(a, sm, gr, it, a.threshold, hs, acc);
     if (!grid_barrier<true>(a, sm, gr, epoch, it)) break;
-    const unsigned long long hc = ld_relaxed(&a.ctl->huge[it & 1]);
+    const unsigned long long hc = ld_relaxed(&a.ctl->huge[it & 1].v);
     if ((hc >> 32) != 0) {
       pull_lb<B>(a, gr, hc, hs, acc);
       if (!grid_barrier<true>(a, sm, gr, epoch, it)) break;
@@ -2028,7 +2003,7 @@ __global__ __launch_bounds__(256) void k_pull_prepare(Args a) {
   if (threadIdx.x == 0) {
     unsigned long long t = 0;
     for (int j = 0; j < 256 / kWave; ++j) t += part[j];
-    if (t) add_relaxed(&a.ctl->dangling[0], t);
+    if (t) add_relaxed(&a.ctl->dangling[0].v, t);
   }
 }
 
