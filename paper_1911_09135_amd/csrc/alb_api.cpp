@@ -59,8 +59,14 @@ struct Workspace {
   int4 *huge_rec = nullptr;
   unsigned long long *bar = nullptr, *word = nullptr, *acc = nullptr;
   float *rank = nullptr;
+  // two control blocks and sets of barrier words, used in turn by persistent
+  // launches (the host loop uses the first); `turn` is the next launch's, and
+  // `cleared` says that the launch before has zeroed it
   Ctl *ctl = nullptr;
-  Ctl *h_ctl = nullptr;  // pinned host mirror
+  int turn = 0;
+  bool cleared = false;
+  Ctl *h_ctl = nullptr;  // pinned host mirror (host loop, profiling)
+  Result *h_res = nullptr;  // pinned, behind it: a persistent launch's result
   hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
   size_t bytes = 0;
 
@@ -104,7 +110,8 @@ struct BatchWs {
   // one copy uploads a batch's tables
   unsigned char *tab = nullptr, *h_tab = nullptr;
   Ctl *ctl = nullptr;
-  Ctl *h_ctl = nullptr;
+  Ctl *h_ctl = nullptr;  // pinned host mirror (profiling)
+  Result *h_res = nullptr;  // pinned, behind it: the launch's result
   hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
   size_t bytes = 0;
 
@@ -308,13 +315,14 @@ alb_status ws_fill(Workspace *w, int32_t n, const Needs &nd) {
   HIP_TRY(dalloc(&w->q1, nd.qcap, w->bytes));
   HIP_TRY(dalloc(&w->huge_rec, nd.qcap, w->bytes));
   HIP_TRY(dalloc(&w->hint, nd.hint_cap, w->bytes));
-  HIP_TRY(dalloc(&w->bar, kBarWords, w->bytes));
+  HIP_TRY(dalloc(&w->bar, 2 * kBarWords, w->bytes));
   HIP_TRY(dalloc(&w->word, (size_t)n, w->bytes));
   HIP_TRY(dalloc(&w->labels, (size_t)n, w->bytes));
   HIP_TRY(dalloc(&w->rank, (size_t)n, w->bytes));
   HIP_TRY(dalloc(&w->acc, (size_t)n, w->bytes));
-  HIP_TRY(dalloc(&w->ctl, 1, w->bytes));
-  HIP_TRY(palloc(&w->h_ctl, sizeof(Ctl)));
+  HIP_TRY(dalloc(&w->ctl, 2, w->bytes));
+  HIP_TRY(palloc(&w->h_ctl, sizeof(Ctl) + sizeof(Result)));
+  w->h_res = (Result *)(w->h_ctl + 1);
   for (auto &e : w->ev) HIP_TRY(hipEventCreate(&e));
   return ALB_OK;
 }
@@ -385,7 +393,8 @@ alb_status bws_fill(BatchWs *w, const BatchNeeds &nd) {
   HIP_TRY(dalloc(&w->tab, kBatchTableBytes * (size_t)nd.nq, w->bytes));
   HIP_TRY(palloc(&w->h_tab, kBatchTableBytes * (size_t)std::max(nd.nq, 1)));
   HIP_TRY(dalloc(&w->ctl, 1, w->bytes));
-  HIP_TRY(palloc(&w->h_ctl, sizeof(Ctl)));
+  HIP_TRY(palloc(&w->h_ctl, sizeof(Ctl) + sizeof(Result)));
+  w->h_res = (Result *)(w->h_ctl + 1);
   for (auto &e : w->ev) HIP_TRY(hipEventCreate(&e));
   return ALB_OK;
 }
@@ -570,6 +579,7 @@ struct Job {
 struct RunOut {
   Workspace *ws = nullptr;
   uint32_t qcap = 0;
+  const Ctl *ctl = nullptr;     // the run's control block (device)
   int32_t *d_labels = nullptr;  // where labels ended up on the device
   float *d_rank = nullptr;
   hipStream_t stream = nullptr;
@@ -579,7 +589,9 @@ void zero_stats(alb_stats *st) {
   if (st) std::memset(st, 0, sizeof *st);
 }
 
-alb_status abort_error(const Ctl &c) {
+// (of a control block or a result block)
+template <class C>
+alb_status abort_error(const C &c) {
   return fail(ALB_E_DEVICE,
               "a grid barrier wait timed out in round %u (%llu of %llu arrivals seen, %u members); the device "
               "run was abandoned",
@@ -628,27 +640,29 @@ void print_skew(const uint32_t *d_counts, int rounds, int members) {
                    (double)mx * members / (double)sum);
 }
 
-void fill_stats(alb_stats *st, const Ctl &c, int rounds, int launches, int64_t T, int64_t threshold, hipEvent_t e0,
-                hipEvent_t e1, hipEvent_t e2) {
-  float ms_all = 0.f, ms_k = 0.f;
-  if (e0 && e1 && e2) {  // (untimed without events)
-    (void)hipEventElapsedTime(&ms_all, e0, e2);
-    (void)hipEventElapsedTime(&ms_k, e1, e2);
-  }
+void fill_stats(alb_stats *st, const unsigned long long (&sum)[kStats], int rounds, int launches, int64_t T,
+                int64_t threshold, double device_ms, double kernel_ms) {
   st->rounds = rounds;
   st->kernel_launches = launches;
   st->launched_threads = T;
   st->huge_threshold = threshold;
-  unsigned long long sum[kStats] = {0};
-  for (int x = 0; x < kStatXcds; ++x)
-    for (int k = 0; k < kStats; ++k) sum[k] += c.stat[x][k].v;
   st->frontier_vertices = (int64_t)sum[kStFrontier];
   st->edges_examined = (int64_t)(sum[kStEdgesTwc] + sum[kStEdgesLb]);
   st->huge_vertices = (int64_t)sum[kStHugeV];
   st->huge_edges = (int64_t)sum[kStEdgesLb];
   st->pushes = (int64_t)sum[kStPushes];
-  st->device_ms = ms_all;
-  st->kernel_ms = ms_k;
+  st->device_ms = device_ms;
+  st->kernel_ms = kernel_ms;
+}
+
+double event_ms(hipEvent_t from, hipEvent_t to) {
+  float ms = 0.f;
+  (void)hipEventElapsedTime(&ms, from, to);
+  return ms;
+}
+
+double ticks_ms(alb_graph g, unsigned long long from, unsigned long long to) {
+  return to > from ? (double)(to - from) / (double)g->clock_khz : 0.0;
 }
 
 // Worklist capacity and chunk-index entries a call needs, and whether it
@@ -743,6 +757,8 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
   a.hint_cap = ws->hint_cap;
   a.bar = ws->bar;
   a.ctl = ws->ctl;
+  a.source = job.source;
+  a.nfront0 = job.nfront0;
   a.threshold = threshold;
   a.c_wave = o.wave_cutoff;
   a.c_wg = o.wg_cutoff;
@@ -809,74 +825,103 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
     HIP_TRY(hipMemsetAsync(prof.p, 0, nb, stream));
     a.prof_wg = prof.p;
   }
-  if (ws->ev[0]) HIP_TRY(hipEventRecord(ws->ev[0], stream));
-  if (job.op == OP_PR_PULL) {
-    HIP_TRY(launch_init(OP_PR, a, -1, job.nfront0, stream));
-    HIP_TRY(launch_pull_prepare(a, stream));
-  } else {
-    HIP_TRY(launch_init(job.op, a, job.source, job.nfront0, stream));
+  if (launch == ALB_LAUNCH_PERSISTENT && job.max_rounds > 0) {
+    // one launch does everything, from the labels' initialisation to the
+    // outputs, and writes its result block into pinned memory
+    if (!fixed) {
+      a.bar = ws->bar + (size_t)ws->turn * kBarWords;
+      a.ctl = ws->ctl + ws->turn;
+      a.clear_bar = ws->bar + (size_t)(1 - ws->turn) * kBarWords;
+      a.clear_ctl = ws->ctl + (1 - ws->turn);
+      a.result = ws->h_res;
+      ws->h_res->done = 0;
+    } else {
+      a.result = &ws->ctl->result;
+    }
+    if (fixed || !ws->cleared) HIP_TRY(launch_clear(a, stream));
+    ws->cleared = false;  // until this launch is known to have cleared the other one
+    if (job.op == OP_PR_PULL)
+      HIP_TRY(launch_pull_pr(wg, grid, a, stream));
+    else
+      HIP_TRY(launch_persistent(job.op, wg, grid, a, stream));
+    Result res;
+    if (fixed) HIP_TRY(hipMemcpyAsync(&res, a.result, sizeof(Result), hipMemcpyDeviceToHost, stream));
+    HIP_TRY(hipStreamSynchronize(stream));
+    if (!fixed) res = *ws->h_res;
+    if (!res.done) return fail(ALB_E_DEVICE, "the persistent launch ended without a result");
+    if (res.abort) return abort_error(res);
+    T = (int64_t)res.n_members * wg;
+    if (res.overflow != 0xffffffffu)
+      return fail(ALB_E_OVERFLOW, "a worklist exceeded its capacity of %u entries in round %u", a.qcap, res.overflow);
+    if (!fixed) {
+      ws->turn = 1 - ws->turn;
+      ws->cleared = true;
+    }
+    ro.ctl = a.ctl;
+    if (a.profile) {  // profiling aid: per-round phase times on stderr
+      HIP_TRY(hipMemcpyAsync(ws->h_ctl, a.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, stream));
+      HIP_TRY(hipStreamSynchronize(stream));
+      print_timeline(*ws->h_ctl, (int)job.op, (int)res.rounds, res.threshold_used, g->clock_khz);
+      if (prof.p)
+        print_skew(prof.p, std::min((int)res.rounds, kTimeline), (int)std::min<uint32_t>(res.n_members, kProfMembers));
+    }
+    if (!job.all_rounds && job.max_rounds > 1 && (int)res.rounds >= job.max_rounds && res.left != 0)
+      return fail(ALB_E_DEVICE, "no convergence within %d rounds", job.max_rounds);
+    if (st)
+      fill_stats(st, res.stat, (int)res.rounds, 1, T, res.threshold_used,
+                 fixed ? 0.0 : ticks_ms(g, res.t_begin, res.t_end),
+                 fixed ? 0.0 : ticks_ms(g, res.t_rounds, res.t_end));
+    return ALB_OK;
   }
-  if (ws->ev[1]) HIP_TRY(hipEventRecord(ws->ev[1], stream));
 
+  // host loop (and runs of no round at all)
+  ws->cleared = false;
+  if (ws->ev[0]) HIP_TRY(hipEventRecord(ws->ev[0], stream));
+  HIP_TRY(launch_init(job.op == OP_PR_PULL ? OP_PR : job.op, a, stream));
+  if (ws->ev[1]) HIP_TRY(hipEventRecord(ws->ev[1], stream));
   int launches = 0;
   int rounds = 0;
-  if (launch == ALB_LAUNCH_PERSISTENT) {
-    if (job.max_rounds > 0) {
-      if (job.op == OP_PR_PULL)
-        HIP_TRY(launch_pull_pr(wg, grid, a, stream));
-      else
-        HIP_TRY(launch_persistent(job.op, wg, grid, a, stream));
-      launches = 1;
-    }
-  } else {
-    for (int r = 0; r < job.max_rounds; ++r) {
-      a.round = r;
-      if (!job.all_rounds) {
-        // the worklist for round r is known on the device; stop if empty
-        HIP_TRY(hipMemcpyAsync(ws->h_ctl, ws->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, stream));
-        HIP_TRY(hipStreamSynchronize(stream));
-        if (ws->h_ctl->overflow != 0xffffffffu) break;
-        if (ws->h_ctl->qcount[r % 3].v == 0) break;
-      }
-      HIP_TRY(launch_twc(job.op, wg, grid, a, stream));
-      ++launches;
+  for (int r = 0; r < job.max_rounds; ++r) {
+    a.round = r;
+    if (!job.all_rounds && r > 0) {
+      // the worklist for round r is known on the device; stop if empty
       HIP_TRY(hipMemcpyAsync(ws->h_ctl, ws->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, stream));
       HIP_TRY(hipStreamSynchronize(stream));
       if (ws->h_ctl->overflow != 0xffffffffu) break;
-      if ((ws->h_ctl->huge[r & 1].v >> 32) != 0) {  // launch the LB kernel only when imbalance was found
-        HIP_TRY(launch_lb(job.op, wg, grid, a, stream));
-        ++launches;
-      }
-      if (job.op == OP_PR) {
-        HIP_TRY(launch_pr_update(wg, grid, a, stream));
-        ++launches;
-      }
-      rounds = r + 1;
+      if (ws->h_ctl->qcount[r % 3].v == 0) break;
     }
+    HIP_TRY(launch_twc(job.op, wg, grid, a, stream));
+    ++launches;
+    HIP_TRY(hipMemcpyAsync(ws->h_ctl, ws->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, stream));
+    HIP_TRY(hipStreamSynchronize(stream));
+    if (ws->h_ctl->overflow != 0xffffffffu) break;
+    if ((ws->h_ctl->huge[r & 1].v >> 32) != 0) {  // launch the LB kernel only when imbalance was found
+      HIP_TRY(launch_lb(job.op, wg, grid, a, stream));
+      ++launches;
+    }
+    if (job.op == OP_PR) {
+      HIP_TRY(launch_pr_update(wg, grid, a, stream));
+      ++launches;
+    }
+    rounds = r + 1;
   }
   if (job.op == OP_SSSP || job.op == OP_CC || job.op == OP_KCORE) HIP_TRY(launch_finish(job.op, a, stream));
   if (ws->ev[2]) HIP_TRY(hipEventRecord(ws->ev[2], stream));
   HIP_TRY(hipMemcpyAsync(ws->h_ctl, ws->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, stream));
   HIP_TRY(hipStreamSynchronize(stream));
   const Ctl &c = *ws->h_ctl;
-  if (c.abort) return abort_error(c);
-  if (launch == ALB_LAUNCH_PERSISTENT && launches) {
-    T = (int64_t)c.n_members * wg;
-    threshold = c.threshold_used;
-  }
+  ro.ctl = a.ctl;
   if (c.overflow != 0xffffffffu)
     return fail(ALB_E_OVERFLOW, "a worklist exceeded its capacity of %u entries in round %u", a.qcap, c.overflow);
-  if (launch == ALB_LAUNCH_PERSISTENT) {
-    rounds = (int)c.rounds;
-    if (getenv("ALB_TIMELINE")) {  // profiling aid: per-round phase times on stderr
-      print_timeline(c, (int)job.op, rounds, (long long)threshold, g->clock_khz);
-      if (prof.p) print_skew(prof.p, std::min(rounds, kTimeline), (int)std::min<uint32_t>(c.n_members, kProfMembers));
-    }
-  }
   if (!job.all_rounds && job.max_rounds > 1 && rounds >= job.max_rounds && c.qcount[rounds % 3].v != 0)
     return fail(ALB_E_DEVICE, "no convergence within %d rounds", job.max_rounds);
-
-  if (st) fill_stats(st, c, rounds, launches, T, threshold, ws->ev[0], ws->ev[1], ws->ev[2]);
+  if (st) {
+    unsigned long long sum[kStats] = {0};
+    for (int x = 0; x < kStatXcds; ++x)
+      for (int k = 0; k < kStats; ++k) sum[k] += c.stat[x][k].v;
+    fill_stats(st, sum, rounds, launches, T, threshold, ws->ev[0] ? event_ms(ws->ev[0], ws->ev[2]) : 0.0,
+               ws->ev[1] ? event_ms(ws->ev[1], ws->ev[2]) : 0.0);
+  }
   return ALB_OK;
 }
 
@@ -1058,6 +1103,9 @@ alb_status upload_batch(BatchJob &j, BatchWs *ws) {
   a.hint_cap = ws->hint_cap;
   a.bar = ws->bar;
   a.ctl = ws->ctl;
+  a.result = ws->h_res;
+  a.source = -1;
+  a.nfront0 = (uint32_t)j.count;
   if (j.op == OP_BFS) a.level = (int32_t *)ws->word;
   if (j.op == OP_SSSP) a.word = ws->word;
   // the tables of this batch, packed with stride count: int64 arrays first,
@@ -1092,14 +1140,13 @@ alb_status upload_batch(BatchJob &j, BatchWs *ws) {
   return ALB_OK;
 }
 
-// The device work of one batch: initialise labels and seed the sources, run
-// every round in one persistent launch, write the outputs, and copy the
-// control block to the pinned mirror.
-alb_status enqueue_batch(const BatchJob &j, BatchWs *ws, hipStream_t st) {
+// The device work of one batch: initialise labels and the first worklist, run
+// every round in one persistent launch (which writes its result block into
+// pinned memory), write the outputs.
+alb_status enqueue_batch(const BatchJob &j, hipStream_t st) {
   HIP_TRY(launch_init_batch(j.op, j.a, st));
   HIP_TRY(launch_batch(j.op, j.o.wg_size, j.grid, j.a, st));
   HIP_TRY(launch_finish_batch(j.op, j.a, j.max_n, st));
-  HIP_TRY(hipMemcpyAsync(ws->h_ctl, ws->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
   return ALB_OK;
 }
 
@@ -1112,9 +1159,12 @@ struct LaunchWindow {
 thread_local LaunchWindow g_window;
 
 // After the stream reached the end of enqueue_batch: errors, host outputs, stats.
+// (`whole_ms`: the batch's device time measured outside, or negative for the launch's own.)
 alb_status finish_batch(alb_graph g, const BatchJob &j, BatchWs *ws, int32_t *const *outs, alb_stats *st,
-                        hipEvent_t e0, hipEvent_t e1, hipEvent_t e2) {
-  const Ctl &c = *ws->h_ctl;
+                        double whole_ms) {
+  const Result &c = *ws->h_res;
+  g_window.valid = false;
+  if (!c.done) return fail(ALB_E_DEVICE, "the persistent launch ended without a result");
   g_window.valid = c.t_begin != 0 && c.t_end >= c.t_begin;
   g_window.begin_ms = (double)c.t_begin / (double)g->clock_khz;
   g_window.end_ms = (double)c.t_end / (double)g->clock_khz;
@@ -1122,8 +1172,12 @@ alb_status finish_batch(alb_graph g, const BatchJob &j, BatchWs *ws, int32_t *co
   if (c.overflow != 0xffffffffu)
     return fail(ALB_E_OVERFLOW, "a worklist exceeded its capacity of %u entries in round %u", j.a.qcap, c.overflow);
   const int rounds = (int)c.rounds;
-  if (getenv("ALB_TIMELINE")) print_timeline(c, (int)j.op, rounds, (long long)c.threshold_used, g->clock_khz);
-  if (rounds >= j.a.max_rounds && c.qcount[rounds % 3].v != 0)
+  if (j.a.profile) {
+    HIP_TRY(hipMemcpyAsync(ws->h_ctl, ws->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, j.stream));
+    HIP_TRY(hipStreamSynchronize(j.stream));
+    print_timeline(*ws->h_ctl, (int)j.op, rounds, (long long)c.threshold_used, g->clock_khz);
+  }
+  if (rounds >= j.a.max_rounds && c.left != 0)
     return fail(ALB_E_DEVICE, "no convergence within %d rounds", j.a.max_rounds);
   if (!j.o.out_on_device) {  // straight from the staging area into each query's host array
     for (int32_t q = 0; q < j.count; ++q)
@@ -1132,8 +1186,10 @@ alb_status finish_batch(alb_graph g, const BatchJob &j, BatchWs *ws, int32_t *co
     HIP_TRY(hipStreamSynchronize(j.stream));
   }
   if (st)
-    fill_stats(st, c, rounds, 1, (int64_t)c.n_members * j.o.wg_size,
-               j.per_query_thr ? -1 : (int64_t)c.threshold_used, e0, e1, e2);
+    fill_stats(st, c.stat, rounds, 1, (int64_t)c.n_members * j.o.wg_size,
+               j.per_query_thr ? -1 : (int64_t)c.threshold_used,
+               whole_ms >= 0 ? whole_ms : ticks_ms(g, c.t_init, c.t_end),
+               whole_ms >= 0 ? whole_ms : ticks_ms(g, c.t_rounds, c.t_end));
   return ALB_OK;
 }
 
@@ -1167,15 +1223,11 @@ alb_status run_batch(alb_graph g, OpKind op, int32_t count, const int32_t *membe
   s = upload_batch(j, ws);
   if (s != ALB_OK) return s;
   const hipStream_t stream = j.stream;
-  HIP_TRY(hipEventRecord(ws->ev[0], stream));
-  HIP_TRY(launch_init_batch(op, j.a, stream));
-  HIP_TRY(hipEventRecord(ws->ev[1], stream));
-  HIP_TRY(launch_batch(op, j.o.wg_size, j.grid, j.a, stream));
-  HIP_TRY(launch_finish_batch(op, j.a, j.max_n, stream));
-  HIP_TRY(hipEventRecord(ws->ev[2], stream));
-  HIP_TRY(hipMemcpyAsync(ws->h_ctl, ws->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, stream));
+  ws->h_res->done = 0;
+  s = enqueue_batch(j, stream);
+  if (s != ALB_OK) return s;
   HIP_TRY(hipStreamSynchronize(stream));
-  return finish_batch(g, j, ws, outs, st, ws->ev[0], ws->ev[1], ws->ev[2]);
+  return finish_batch(g, j, ws, outs, st, -1.0);
 }
 
 // --------------------------------------------------------------------------
@@ -1234,11 +1286,12 @@ alb_status time_batch(alb_graph g, OpKind op, int32_t count, const int32_t *memb
   double t[4];
   for (int rep = 0; rep < 4; ++rep) {
     HIP_TRY(hipEventRecord(ws->ev[0], j.stream));
-    s = enqueue_batch(j, ws, j.stream);
+    ws->h_res->done = 0;
+    s = enqueue_batch(j, j.stream);
     if (s != ALB_OK) return s;
     HIP_TRY(hipEventRecord(ws->ev[2], j.stream));
     HIP_TRY(hipStreamSynchronize(j.stream));
-    s = finish_batch(g, j, ws, nullptr, nullptr, ws->ev[0], ws->ev[0], ws->ev[2]);
+    s = finish_batch(g, j, ws, nullptr, nullptr, -1.0);
     if (s != ALB_OK) return s;
     float f = 0.f;
     HIP_TRY(hipEventElapsedTime(&f, ws->ev[0], ws->ev[2]));
@@ -1715,7 +1768,7 @@ alb_status alb_sssp_noalloc(alb_graph g, int32_t source, int32_t *dist, const al
   ws.word = (unsigned long long *)(b + p_word);
   ws.ctl = (Ctl *)(b + p_ctl);
   Ctl host_ctl;
-  ws.h_ctl = &host_ctl;
+  ws.h_ctl = &host_ctl;  // (host loop)
   WsGuard guard{nullptr, nullptr};
   RunOut ro;
   s = run_job(g, job, o, dist, stats, guard, ro, &ws);
@@ -1861,6 +1914,11 @@ alb_status alb_trace_round(alb_graph g, const int32_t *frontier, int64_t nf, con
     return s;
   }
   Workspace *ws = ro.ws;
+  if ((e = hipMemcpy(ws->h_ctl, ro.ctl, sizeof(Ctl), hipMemcpyDeviceToHost)) != hipSuccess) {
+    free_all();
+    zero_stats(stats);
+    return fail(ALB_E_DEVICE, "hipMemcpy: %s", hipGetErrorString(e));
+  }
   const Ctl &c = *ws->h_ctl;
   const uint32_t vh = (uint32_t)(c.huge[0].v >> 32), ehuge = (uint32_t)c.huge[0].v;
   const uint32_t nn = std::min(c.qcount[1].v, ro.qcap);
@@ -2197,7 +2255,7 @@ alb_status plan_create(alb_graph g, int32_t algo, int32_t count, const int32_t *
   if (e != hipSuccess) return bail(fail(ALB_E_DEVICE, "hipStreamCreate: %s", hipGetErrorString(e)));
   e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
   if (e == hipSuccess) {
-    s = enqueue_batch(p->j, &p->ws, cs);
+    s = enqueue_batch(p->j, cs);
     hipError_t e2 = hipStreamEndCapture(cs, &p->graph);
     if (s == ALB_OK && e2 != hipSuccess) s = fail(ALB_E_DEVICE, "hipStreamEndCapture: %s", hipGetErrorString(e2));
   } else {
@@ -2239,11 +2297,12 @@ alb_status alb_batch_plan_run(alb_plan p, alb_stats *stats) {
   std::lock_guard<std::mutex> lk(p->mu);
   HIP_TRY(hipSetDevice(p->g->device));
   const hipStream_t st = p->j.stream;
+  p->ws.h_res->done = 0;
   HIP_TRY(hipEventRecord(p->ws.ev[0], st));
   HIP_TRY(hipGraphLaunch(p->exec, st));
   HIP_TRY(hipEventRecord(p->ws.ev[2], st));
   HIP_TRY(hipStreamSynchronize(st));
-  alb_status s = finish_batch(p->g, p->j, &p->ws, p->outs.data(), stats, p->ws.ev[0], p->ws.ev[0], p->ws.ev[2]);
+  alb_status s = finish_batch(p->g, p->j, &p->ws, p->outs.data(), stats, event_ms(p->ws.ev[0], p->ws.ev[2]));
   if (s != ALB_OK) zero_stats(stats);
   return s;
 }

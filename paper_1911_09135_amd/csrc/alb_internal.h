@@ -31,7 +31,10 @@ constexpr int kBarXcds = 16;
 constexpr int kBarStride = 32;  // uint64 words per line
 constexpr int kBarRoot = 0, kBarGen = kBarStride, kBarXcdArrive = 2 * kBarStride;
 constexpr int kBarXcdMembers = kBarXcdArrive + kBarXcds * kBarStride;
-constexpr size_t kBarWords = (size_t)kBarXcdMembers + (size_t)kBarXcds * kBarStride;
+// Leaving the launch: the same two levels of counters, with nobody waiting.
+constexpr int kBarXcdOut = kBarXcdMembers + kBarXcds * kBarStride;
+constexpr int kBarRootOut = kBarXcdOut + kBarXcds * kBarStride;
+constexpr size_t kBarWords = (size_t)kBarRootOut + kBarStride;
 
 // Huge-worklist chunk index: edge index k of the round's huge edges lies in
 // chunk k >> hint_shift; hint[c] holds the huge-list slot that owns the first
@@ -98,6 +101,23 @@ struct alignas(128) Line {
 constexpr int kStatXcds = 8;  // XCC_ID modulo this
 enum { kStFrontier = 0, kStEdgesTwc, kStEdgesLb, kStHugeV, kStPushes, kStats };
 
+// What the host needs to know of a persistent launch, written by the last
+// workgroup to leave it: into pinned host memory, or into Ctl::result.
+struct Result {
+  uint32_t done;         // 1 once the rest is valid (the host clears it before the launch)
+  uint32_t overflow;     // as in Ctl
+  uint32_t abort;
+  uint32_t diag_round;
+  unsigned long long diag_seen, diag_target;
+  uint32_t rounds;
+  uint32_t n_members;
+  uint32_t left;         // entries of the worklist after the last round
+  uint32_t pad;
+  long long threshold_used;
+  unsigned long long t_init, t_begin, t_rounds, t_end;  // see Ctl
+  unsigned long long stat[kStats];
+};
+
 // Per-call control block in device memory.  Counters rotate by round so that
 // one round can clear the counter two rounds ahead without a separate launch.
 struct Ctl {
@@ -123,9 +143,11 @@ struct Ctl {
   // with Args::profile: wall-clock ticks summed over workgroups, per part of
   // the round (see kProf*)
   unsigned long long prof[8];
-  // persistent launch: device wall-clock ticks when its first member joined
-  // and when member 0 left the round loop
-  unsigned long long t_begin, t_end;
+  // persistent launch: device wall-clock ticks when its separate set-up
+  // kernel began (0: it sets itself up), when its first member joined, when
+  // its first round began and when member 0 left the round loop
+  unsigned long long t_init, t_begin, t_rounds, t_end;
+  Result result;
   // reached-vertex filter: vertices whose bit the build of round r set, at [r & 1]
   Line<unsigned long long> filt_count[2];
   // continuous serving (member 0's bookkeeping): requests taken, slots
@@ -163,6 +185,16 @@ struct Args {
   uint32_t hint_cap;
   unsigned long long *bar;  // grid barrier words (kBarWords)
   Ctl *ctl;
+  // Persistent launches of one query set themselves up: labels, source, and
+  // (clear_ctl, clear_bar) the zeroed control block and barrier words of the
+  // workspace's next launch, which this launch does not touch otherwise.  Two
+  // sets are used in turn, because workgroups that find membership closed
+  // may start late and still take their ticket.
+  int32_t source;
+  Ctl *clear_ctl;
+  unsigned long long *clear_bar;
+  Result *result;       // written when the persistent launch ends
+  uint32_t nfront0;     // entries of round 0's worklist
   int64_t threshold;    // huge iff degree >= threshold (and degree >= 1); persistent: < 0 = launched threads
   int32_t c_wave;       // TWC cutoffs
   int32_t c_wg;
@@ -220,17 +252,18 @@ struct Args {
 };
 
 // Host-callable launchers (alb_kernels.hip).  All return the launch status.
-hipError_t launch_init(OpKind op, const Args &a, int32_t source, uint32_t nfront0, hipStream_t s);
+// Host loop: labels, control block and barrier words.
+hipError_t launch_init(OpKind op, const Args &a, hipStream_t s);
+// Zeroed control block and barrier words for a persistent launch of one query.
+hipError_t launch_clear(const Args &a, hipStream_t s);
 hipError_t launch_twc(OpKind op, int wg, int grid, const Args &a, hipStream_t s);
 hipError_t launch_lb(OpKind op, int wg, int grid, const Args &a, hipStream_t s);
 hipError_t launch_pr_update(int wg, int grid, const Args &a, hipStream_t s);
-// Pull PageRank: every iteration in one persistent launch (after launch_init
-// with OP_PR and launch_pull_prepare).
+// Pull PageRank: every iteration in one persistent launch.
 hipError_t launch_pull_pr(int wg, int grid, const Args &a, hipStream_t s);
-hipError_t launch_pull_prepare(const Args &a, hipStream_t s);
 hipError_t pull_occupancy(int wg, int *blocks_per_cu);
 hipError_t launch_persistent(OpKind op, int wg, int grid, const Args &a, hipStream_t s);
-// SSSP / CC: out[v] = word[v] >> 32; k-core: out[v] = (level[v] >= k).
+// Host loop.  SSSP / CC: out[v] = word[v] >> 32; k-core: out[v] = (level[v] >= k).
 hipError_t launch_finish(OpKind op, const Args &a, hipStream_t s);
 // Workgroups of `wg` threads that fit on one CU for the persistent kernel of
 // `op`, by the runtime's occupancy calculator (an upper bound: the launch

@@ -122,6 +122,7 @@ __device__ __forceinline__ V from_bits(int32_t x) {
 // Every active vertex of round r has level r, so no source level is read.
 struct OpBFS {
   using val_t = int32_t;
+  static constexpr int kKind = OP_BFS;
   struct pre_t {
     int32_t cur;
   };
@@ -181,6 +182,7 @@ __device__ __forceinline__ int32_t label_of_active(unsigned long long w, uint32_
 
 struct OpSSSP {  // relaxation: dist[dst] = min(dist[dst], dist[src] + w)
   using val_t = int32_t;
+  static constexpr int kKind = OP_SSSP;
   struct pre_t {
     int32_t cand;
     unsigned long long cur;
@@ -220,6 +222,7 @@ struct OpServe : OpSSSP {
 
 struct OpCC {  // min-label propagation
   using val_t = int32_t;
+  static constexpr int kKind = OP_CC;
   struct pre_t {
     unsigned long long cur;
   };
@@ -284,6 +287,7 @@ struct Filtered<OpCC> {
 // remaining degree that other lanes are already lowering.
 struct OpKCore {
   using val_t = int32_t;
+  static constexpr int kKind = OP_KCORE;
   struct pre_t {};
   static constexpr bool kPush = true, kNeedSrc = false, kRecord = false, kPR = false, kBatch = false;
   int32_t *rem;
@@ -332,6 +336,7 @@ struct Filtered<OpKCore> {
 
 struct OpPR {  // acc[dst] += rank[src] / outdeg(src): fp32 contribution, exact fixed-point sum
   using val_t = float;
+  static constexpr int kKind = OP_PR;
   struct pre_t {};
   static constexpr bool kPush = false, kNeedSrc = false, kRecord = false, kPR = true, kBatch = false;
   const float *rank;
@@ -349,6 +354,7 @@ struct OpPR {  // acc[dst] += rank[src] / outdeg(src): fp32 contribution, exact 
 
 struct OpRecord {  // counts each processed edge and the thread that took it; pushes every destination
   using val_t = int32_t;
+  static constexpr int kKind = OP_RECORD;
   struct pre_t {};
   static constexpr bool kPush = true, kNeedSrc = true, kRecord = true, kPR = false, kBatch = false;
   int32_t *hits;
@@ -1121,6 +1127,7 @@ __device__ __forceinline__ Entry<M> *round_next(const Args &a, int r) {
 
 __device__ __forceinline__ uint32_t round_size(const Args &a, int r) {
   if (a.all_rounds) return (uint32_t)a.n;
+  if (r == 0) return a.nfront0;
   const uint32_t c = ld_relaxed(&a.ctl->qcount[r % 3].v);
   return c < a.qcap ? c : a.qcap;
 }
@@ -1234,12 +1241,10 @@ __device__ bool join_members(const Args &a, S &sm, Grid *gr) {
 // Kernels.
 // ---------------------------------------------------------------------------
 
-// The control block of a launch whose round 0 has nfront0 worklist entries
-// (one thread).
-__device__ void reset_ctl(const Args &a, uint32_t nfront0) {
-  Ctl *c = a.ctl;
+// The control block before a launch (one thread).
+__device__ void reset_ctl(Ctl *c) {
   for (int k = 0; k < 3; ++k) {
-    c->qcount[k].v = k == 0 ? nfront0 : 0u;
+    c->qcount[k].v = 0;
     c->chunk[k].v = 0;
   }
   for (int k = 0; k < 2; ++k) {
@@ -1256,29 +1261,39 @@ __device__ void reset_ctl(const Args &a, uint32_t nfront0) {
   c->n_members = 0;
   c->diag_seen = c->diag_target = 0;
   c->diag_round = 0;
-  c->threshold_used = a.threshold;
+  c->threshold_used = 0;
   for (int k = 0; k < kProfParts; ++k) c->prof[k] = 0;
-  c->t_begin = c->t_end = 0;
+  c->t_init = c->t_begin = c->t_rounds = c->t_end = 0;
 }
 
-__global__ void k_init(Args a, int op, int32_t source, uint32_t nfront0) {
+// Vertex v's label before a traversal.
+template <class T>
+__device__ __forceinline__ void init_label(const Args &a, int op, T v) {
+  if (op == OP_BFS) st_relaxed(&a.level[v], (int32_t)v == a.source ? 0 : kInf);
+  if (op == OP_SSSP)
+    st_relaxed(&a.word[v], (unsigned long long)(uint32_t)((int32_t)v == a.source ? 0 : kInf) << 32);
+  if (op == OP_CC) st_relaxed(&a.word[v], (unsigned long long)v << 32);
+  if (op == OP_KCORE) st_relaxed(&a.level[v], a.off[v + 1] - a.off[v]);
+  if (op == OP_PR) {
+    a.rank[v] = 1.0f / (float)a.n;
+    a.acc[v] = 0ull;
+  }
+}
+
+__global__ void k_clear(Args a) {
+  const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
+  for (size_t i = t; i < kBarWords; i += gridDim.x * blockDim.x) a.bar[i] = 0ull;
+  if (t == 0) reset_ctl(a.ctl);
+}
+
+__global__ void k_init(Args a, int op) {
   const uint32_t stride = gridDim.x * blockDim.x;
   const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-  const float r0 = 1.0f / (float)a.n;
-  for (uint32_t v = t; v < (uint32_t)a.n; v += stride) {
-    if (op == OP_BFS) a.level[v] = ((int32_t)v == source) ? 0 : kInf;
-    if (op == OP_SSSP) a.word[v] = (unsigned long long)(uint32_t)((int32_t)v == source ? 0 : kInf) << 32;
-    if (op == OP_CC) a.word[v] = (unsigned long long)v << 32;
-    if (op == OP_KCORE) a.level[v] = a.off[v + 1] - a.off[v];
-    if (op == OP_PR) {
-      a.rank[v] = r0;
-      a.acc[v] = 0ull;
-    }
-  }
+  for (uint32_t v = t; v < (uint32_t)a.n; v += stride) init_label(a, op, v);
   for (size_t i = t; i < kBarWords; i += stride) a.bar[i] = 0ull;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    reset_ctl(a, nfront0);
-    if (source >= 0 && op != OP_RECORD) ((int32_t *)a.q0)[0] = source;
+  if (t == 0) {
+    reset_ctl(a.ctl);
+    if (a.source >= 0 && op != OP_RECORD) ((int32_t *)a.q0)[0] = a.source;
   }
 }
 
@@ -1288,29 +1303,24 @@ __global__ void k_finish(Args a, int op) {
     a.out[v] = op == OP_KCORE ? (int32_t)(a.level[v] >= a.kcore_k) : (int32_t)(a.word[v] >> 32);
 }
 
-// Batch set-up, part 1: every label of every query to INF, barrier words and
-// the control block cleared (the sources are seeded by k_seed_batch after).
+// Batch set-up: every label of every query to INF, the first worklist (query
+// q's source is entry q; the launch gives it label 0), barrier words and
+// control block.
 __global__ void k_init_batch(Args a, int op) {
   const size_t stride = (size_t)gridDim.x * blockDim.x;
   const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t == 0) {
+    const unsigned long long now = (unsigned long long)wall_clock64();
+    reset_ctl(a.ctl);
+    a.ctl->t_init = now;
+  }
   for (size_t i = t; i < (size_t)a.nlabels; i += stride) {
     if (op == OP_BFS) a.level[i] = kInf;
     if (op == OP_SSSP) a.word[i] = (unsigned long long)(uint32_t)kInf << 32;
   }
+  for (size_t q = t; q < (size_t)a.nq; q += stride)
+    ((unsigned long long *)a.q0)[q] = ((unsigned long long)q << 32) | (uint32_t)a.qsrc[q];
   for (size_t i = t; i < kBarWords; i += stride) a.bar[i] = 0ull;
-  if (blockIdx.x == 0 && threadIdx.x == 0) reset_ctl(a, (uint32_t)a.nq);
-}
-
-// Batch set-up, part 2: query q's source gets label 0 and is entry q of the
-// first worklist.
-__global__ void k_seed_batch(Args a, int op) {
-  for (int32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < a.nq; q += gridDim.x * blockDim.x) {
-    const int32_t s = a.qsrc[q];
-    const long long l = a.qoff[q] + s;
-    if (op == OP_BFS) a.level[l] = 0;
-    if (op == OP_SSSP) a.word[l] = 0ull;
-    ((unsigned long long *)a.q0)[q] = ((unsigned long long)(uint32_t)q << 32) | (uint32_t)s;
-  }
 }
 
 // Batch outputs: query blockIdx.y, its vertices strided over blockIdx.x.
@@ -1321,6 +1331,85 @@ __global__ void k_finish_batch(Args a, int op) {
   int32_t *out = a.qout[q];
   for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x)
     out[v] = op == OP_BFS ? a.level[base + v] : (int32_t)(a.word[base + v] >> 32);
+}
+
+// The set-up a persistent launch does itself, followed by a grid barrier.
+template <int B, class Op, bool M>
+__device__ __forceinline__ void set_up(const Args &a, Grid gr) {
+  const uint32_t t = gr.id * B + threadIdx.x, stride = gr.n * B;
+  if constexpr (M) {
+    for (uint32_t q = t; q < (uint32_t)a.nq; q += stride) {
+      const long long l = a.qoff[q] + a.qsrc[q];
+      if constexpr (std::is_same<Op, OpBFS>::value)
+        st_relaxed(&a.level[l], 0);
+      else
+        st_relaxed(&a.word[l], 0ull);
+    }
+  } else {
+    if (t == 0 && a.source >= 0) st_relaxed((int32_t *)a.q0, a.source);
+    for (uint32_t v = t; v < (uint32_t)a.n; v += stride) init_label(a, (int)Op::kKind, v);
+  }
+  if (a.clear_ctl) {
+    for (size_t i = t; i < kBarWords; i += stride) a.clear_bar[i] = 0ull;
+    if (t == B - 1) reset_ctl(a.clear_ctl);
+  }
+}
+
+// The labels of a converged single-query launch as int32 outputs.
+template <int B, class Op>
+__device__ __forceinline__ void write_out(const Args &a, Grid gr) {
+  if constexpr (std::is_same<Op, OpSSSP>::value || std::is_same<Op, OpCC>::value) {
+    for (uint32_t v = gr.id * B + threadIdx.x; v < (uint32_t)a.n; v += gr.n * B)
+      a.out[v] = (int32_t)(ld_relaxed(&a.word[v]) >> 32);
+  } else if constexpr (std::is_same<Op, OpKCore>::value) {
+    for (uint32_t v = gr.id * B + threadIdx.x; v < (uint32_t)a.n; v += gr.n * B)
+      a.out[v] = (int32_t)(ld_relaxed(&a.level[v]) >= a.kcore_k);
+  }
+}
+
+// The end of a persistent launch, after the workgroup's statistics: the last
+// workgroup to leave sums them up and writes the result block (a copy of the
+// control block by the host took 8 to 10 us of a call).
+template <class S>
+__device__ __forceinline__ void leave(const Args &a, S &sm, Grid gr) {
+  wait_memory();
+  __syncthreads();
+  if (threadIdx.x < kWave) {
+    uint32_t last = 0;
+    if (threadIdx.x == 0) {
+      const unsigned long long o1 = add_relaxed(&a.bar[kBarXcdOut + (size_t)kBarStride * gr.xcd], 1ull);
+      if (o1 + 1 == gr.xcd_n) last = add_relaxed(&a.bar[kBarRootOut], 1ull) + 1 == gr.n_xcd;
+    }
+    last = __shfl(last, 0);
+    if (last) {
+      Ctl *c = a.ctl;
+      Result *o = a.result;
+      const uint32_t lane = lane_id();
+      if (lane < kStats) {
+        unsigned long long t = 0;
+#pragma unroll
+        for (int x = 0; x < kStatXcds; ++x) t += ld_relaxed(&c->stat[x][lane].v);
+        o->stat[lane] = t;
+      }
+      if (lane == 0) {
+        const uint32_t rounds = ld_relaxed(&c->rounds);
+        o->overflow = ld_relaxed(&c->overflow);
+        o->abort = ld_relaxed(&c->abort);
+        o->diag_round = ld_relaxed(&c->diag_round);
+        o->diag_seen = ld_relaxed(&c->diag_seen);
+        o->diag_target = ld_relaxed(&c->diag_target);
+        o->rounds = rounds;
+        o->n_members = gr.n;
+        o->left = ld_relaxed(&c->qcount[rounds % 3].v);
+        o->threshold_used = ld_relaxed(&c->threshold_used);
+        o->t_init = ld_relaxed(&c->t_init);
+        o->t_begin = ld_relaxed(&c->t_begin);
+        o->t_rounds = ld_relaxed(&c->t_rounds);
+        o->t_end = (unsigned long long)wall_clock64();
+        o->done = 1;
+      }
+    }
+  }
 }
 
 template <int B, class Op>
@@ -1397,11 +1486,22 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
   if (!joined) return;
   if (a.threshold < 0) a.threshold = (int64_t)gr.n * B;  // the launched thread count (the paper's rule)
   unsigned long long epoch = 0, prof_last = 0;
+  set_up<B, Op, M>(a, gr);
+  bool ok;
+  if constexpr (F) {
+    [[clang::always_inline]] ok = grid_barrier<Op::kPR>(a, sm, gr, epoch, 0);
+  } else {
+    ok = grid_barrier<Op::kPR>(a, sm, gr, epoch, 0);
+  }
+  if (gr.id == 0 && threadIdx.x == 0) st_relaxed(&a.ctl->t_rounds, (unsigned long long)wall_clock64());
   uint64_t reached = 0;  // BFS: vertices in the worklists so far (each is in exactly one round's)
   bool filtered = false;  // the filter bitmap is in use
   int r = 0;
-  for (; r < a.max_rounds; ++r) {
-    if (ld_relaxed(&a.ctl->overflow) < (uint32_t)r) break;  // set in an earlier round: seen by all alike
+  for (; ok && r < a.max_rounds; ++r) {
+    if (ld_relaxed(&a.ctl->overflow) < (uint32_t)r) {  // set in an earlier round: seen by all alike
+      ok = false;
+      break;
+    }
     const uint32_t nF = round_size(a, r);
     if (nF == 0) break;
     if constexpr (F) {
@@ -1425,7 +1525,6 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
       if (gr.id == 0 && threadIdx.x == 0) st_relaxed(&a.ctl->filt_count[(r + 1) & 1].v, 0ull);
       if (build) {
         build_filter<B, Op>(a, gr, &a.ctl->filt_count[r & 1].v);
-        bool ok;
         [[clang::always_inline]] ok = grid_barrier<true>(a, sm, gr, epoch, r);
         if (!ok) break;
         if constexpr (std::is_same<Op, OpBFS>::value)
@@ -1458,13 +1557,12 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
     }
     if constexpr (Op::kPR) flush_dangling<B, Op>(acc, sm, &a.ctl->dangling[r & 1].v);
     uint64_t pb = a.profile ? (uint64_t)wall_clock64() : 0;
-    bool ok1;
     if constexpr (F) {
-      [[clang::always_inline]] ok1 = grid_barrier<Op::kPR>(a, sm, gr, epoch, r);
+      [[clang::always_inline]] ok = grid_barrier<Op::kPR>(a, sm, gr, epoch, r);
     } else {
-      ok1 = grid_barrier<Op::kPR>(a, sm, gr, epoch, r);
+      ok = grid_barrier<Op::kPR>(a, sm, gr, epoch, r);
     }
-    if (!ok1) break;
+    if (!ok) break;
     prof_mark(a, acc, kProfBarrier, pb);
     const unsigned long long hc = ld_relaxed(&a.ctl->huge[r & 1].v);
     if (tl) {
@@ -1484,13 +1582,12 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
         phase_lb<B, Op, M>(a, op, sm, gr, r, hc, qn, qn_cnt, hs, acc);
       }
       pb = a.profile ? (uint64_t)wall_clock64() : 0;
-      bool ok2;
       if constexpr (F) {
-        [[clang::always_inline]] ok2 = grid_barrier<Op::kPR>(a, sm, gr, epoch, r);
+        [[clang::always_inline]] ok = grid_barrier<Op::kPR>(a, sm, gr, epoch, r);
       } else {
-        ok2 = grid_barrier<Op::kPR>(a, sm, gr, epoch, r);
+        ok = grid_barrier<Op::kPR>(a, sm, gr, epoch, r);
       }
-      if (!ok2) break;
+      if (!ok) break;
       prof_mark(a, acc, kProfBarrier, pb);
     }
     if (tl) a.ctl->tl[4 * r + 2] = (unsigned long long)wall_clock64();
@@ -1505,11 +1602,15 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
     st_relaxed(&a.ctl->threshold_used, (long long)a.threshold);
     st_relaxed(&a.ctl->t_end, (unsigned long long)wall_clock64());
   }
+  if constexpr (!M) {
+    if (ok) write_out<B, Op>(a, gr);
+  }
   if constexpr (F) {
     [[clang::always_inline]] flush_stats<B, Op>(acc, sm, a.ctl);
   } else {
     flush_stats<B, Op>(acc, sm, a.ctl);
   }
+  leave(a, sm, gr);
 }
 
 // ---------------------------------------------------------------------------
@@ -1739,7 +1840,7 @@ __global__ void k_init_open(Args a) {
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     Ctl *c = a.ctl;
-    reset_ctl(a, 0u);
+    reset_ctl(c);
     c->open_head = 0;
     c->admit_n[0] = c->admit_n[1] = 0;
     c->open_done = 0;
@@ -1764,6 +1865,7 @@ __global__ void k_init_open(Args a) {
 // ---------------------------------------------------------------------------
 struct OpPRPull {  // type facts for Smem only; the pull phases do the work
   using val_t = float;
+  static constexpr int kKind = OP_PR;
   struct pre_t {};
   static constexpr bool kPush = false, kNeedSrc = false, kRecord = false, kPR = true, kBatch = false;
 };
@@ -1961,8 +2063,19 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
   if (a.threshold < 0) a.threshold = (int64_t)gr.n * B;
   const uint32_t hs = hint_shift(a.threshold);
   unsigned long long epoch = 0;
+  // set-up: ranks, sums, the first contributions and the first dangling mass
+  set_up<B, OpPRPull, false>(a, gr);
+  for (uint32_t v = gr.id * B + threadIdx.x; v < (uint32_t)a.n; v += gr.n * B) {
+    const float r0 = 1.0f / (float)a.n;
+    const int32_t od = a.off[v + 1] - a.off[v];
+    a.contrib[v] = od > 0 ? r0 / (float)od : 0.0f;
+    if (od == 0) acc.dangling += to_fix(r0);
+  }
+  flush_dangling<B, OpPRPull>(acc, sm, &a.ctl->dangling[0].v);
+  const bool ok = grid_barrier<true>(a, sm, gr, epoch, 0);
+  if (gr.id == 0 && threadIdx.x == 0) st_relaxed(&a.ctl->t_rounds, (unsigned long long)wall_clock64());
   int it = 0;
-  for (; it < a.max_rounds; ++it) {
+  for (; ok && it < a.max_rounds; ++it) {
     if (gr.id == 0 && threadIdx.x == 0) {
       st_relaxed(&a.ctl->chunk[(it + 1) % 3].v, 0ull);
       st_relaxed(&a.ctl->huge[(it + 1) & 1].v, 0ull);
@@ -1983,28 +2096,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
     st_relaxed(&a.ctl->threshold_used, (long long)a.threshold);
   }
   flush_stats<B, OpPRPull>(acc, sm, a.ctl);
-}
-
-// Pull set-up after k_init: contributions of the initial ranks and the
-// initial dangling mass (block sums, one atomic per workgroup).
-__global__ __launch_bounds__(256) void k_pull_prepare(Args a) {
-  __shared__ unsigned long long part[256 / kWave];
-  unsigned long long x = 0;
-  const float r0 = 1.0f / (float)a.n;
-  for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < (uint32_t)a.n; v += gridDim.x * blockDim.x) {
-    const int32_t od = a.off[v + 1] - a.off[v];
-    a.contrib[v] = od > 0 ? r0 / (float)od : 0.0f;
-    if (od == 0) x += to_fix(r0);
-  }
-#pragma unroll
-  for (int d = kWave / 2; d > 0; d >>= 1) x += __shfl_xor(x, d);
-  if (lane_id() == 0) part[threadIdx.x / kWave] = x;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned long long t = 0;
-    for (int j = 0; j < 256 / kWave; ++j) t += part[j];
-    if (t) add_relaxed(&a.ctl->dangling[0].v, t);
-  }
+  leave(a, sm, gr);
 }
 
 // ---------------------------------------------------------------------------
@@ -2116,12 +2208,17 @@ hipError_t by_wg(OpKind op, int wg, Xs... xs) {
 
 bool supported_wg(int wg) { return wg == 64 || wg == 256 || wg == 1024; }
 
-hipError_t launch_init(OpKind op, const Args &a, int32_t source, uint32_t nfront0, hipStream_t s) {
+hipError_t launch_init(OpKind op, const Args &a, hipStream_t s) {
   const int threads = 256;
   int blocks = (int)(((int64_t)a.n + threads - 1) / threads);
   if (blocks > 4096) blocks = 4096;
   if (blocks < 128) blocks = 128;
-  hipLaunchKernelGGL(k_init, dim3(blocks), dim3(threads), 0, s, a, (int)op, source, nfront0);
+  hipLaunchKernelGGL(k_init, dim3(blocks), dim3(threads), 0, s, a, (int)op);
+  return hipGetLastError();
+}
+
+hipError_t launch_clear(const Args &a, hipStream_t s) {
+  hipLaunchKernelGGL(k_clear, dim3(8), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -2157,10 +2254,6 @@ hipError_t launch_init_batch(OpKind op, const Args &a, hipStream_t s) {
   if (blocks > 8192) blocks = 8192;
   if (blocks < 128) blocks = 128;
   hipLaunchKernelGGL(k_init_batch, dim3((unsigned)blocks), dim3(threads), 0, s, a, (int)op);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int sblocks = (a.nq + threads - 1) / threads;
-  hipLaunchKernelGGL(k_seed_batch, dim3(sblocks < 1 ? 1 : sblocks), dim3(threads), 0, s, a, (int)op);
   return hipGetLastError();
 }
 
@@ -2199,14 +2292,6 @@ hipError_t launch_pull_pr(int wg, int grid, const Args &a, hipStream_t s) {
     case 1024: hipLaunchKernelGGL(k_pull_pr<1024>, dim3(grid), dim3(1024), 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_pull_prepare(const Args &a, hipStream_t s) {
-  int blocks = (int)(((int64_t)a.n + 255) / 256);
-  if (blocks > 2048) blocks = 2048;
-  if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(k_pull_prepare, dim3(blocks), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
