@@ -623,8 +623,20 @@ __device__ __forceinline__ void reserve_huge(bool huge, int32_t v_or_q, int32_t 
     else
       flag_overflow(a.ctl, round);
   }
-  // chunk index: chunk c's first edge c << hs lies in [p, p + deg)
-  unsigned long long rem = hm;
+  // chunk index: chunk c's first edge c << hs lies in [p, p + deg).  A lane
+  // writes up to two entries itself; longer runs are shared by the wavefront.
+  const uint64_t my_lo = ((uint64_t)p + (1ull << hs) - 1) >> hs;
+  const uint64_t my_hi = huge ? (((uint64_t)p + (uint32_t)deg - 1) >> hs) + 1 : 0;  // one past the last
+  const bool few = my_hi <= my_lo + 2;
+  if (few) {
+    for (uint64_t c = my_lo; c < my_hi; ++c) {
+      if (c < a.hint_cap)
+        st_hint(&a.hint[c], make_int2((int32_t)j, (int32_t)(p + (uint32_t)deg)));
+      else
+        flag_overflow(a.ctl, round);
+    }
+  }
+  unsigned long long rem = __ballot(huge && !few);
   while (rem) {
     const int l = __ffsll(rem) - 1;
     rem &= rem - 1;
@@ -727,6 +739,21 @@ __device__ __forceinline__ uint32_t twc_chunk(uint32_t nF, uint32_t wgs, int B) 
   return (uint32_t)c;
 }
 
+// The fixed first run's length.  A worklist that fits in one run of `fill`
+// entries per workgroup (the entries whose edges, at the graph's mean degree,
+// fill one pass of the workgroup) is split over as many workgroups as it
+// fills, and over 96 if it fills fewer: a run's time is a chain of dependent
+// loads, about the same for 2 entries as for one full pass, while every
+// pass beyond the first and every long list in the same run adds to it (RMAT-14
+// BFS: 2,498 entries in runs of 64 took 18.8 us, in runs of 27 14.7); but each
+// workgroup with pushes also costs its 12 ns at the worklist counter, so a
+// low-degree graph's runs are long (a grid of mean degree 4: 256 entries).
+__device__ __forceinline__ uint32_t first_run(uint32_t nF, uint32_t wgs, int B, uint32_t fill) {
+  if ((uint64_t)nF > (uint64_t)fill * wgs) return twc_chunk(nF, wgs, B);
+  const uint32_t used = max((nF + fill - 1) / fill, min(wgs, 96u));
+  return max(1u, (nF + used - 1) / used);
+}
+
 // Workgroups take runs of consecutive worklist entries one at a time, so a
 // run that takes long does not hold up work queued behind it.  The first run
 // of workgroup g is fixed (entries [g * C0, (g + 1) * C0)) and needs no
@@ -742,8 +769,8 @@ struct Claims {
   uint32_t C0, len;
   unsigned long long S, nxt, seen;
   bool first;
-  __device__ Claims(uint32_t nF, Grid gr, int B)
-      : C0(twc_chunk(nF, gr.n, B)), len(C0), S((unsigned long long)gr.n * C0),
+  __device__ Claims(uint32_t nF, Grid gr, int B, uint32_t fill)
+      : C0(first_run(nF, gr.n, B, fill)), len(C0), S((unsigned long long)gr.n * C0),
         nxt((unsigned long long)gr.id * C0), seen(S), first(true) {}
   // Publish the next run as (*base, *n); *base >= nF means no more work.
   __device__ void next(unsigned long long *claim, uint32_t nF, Grid gr, int B, unsigned long long &base,
@@ -776,7 +803,7 @@ __device__ void phase_twc(const Args &a, const Op &op, S &sm, Grid gr, int round
   unsigned long long *claim = &a.ctl->chunk[round % 3].v;
   Pusher<Entry<M>> pu{sm.pbuf[tid / kWave], 0u, qn, qn_cnt};
   uint64_t pt = a.profile ? (uint64_t)wall_clock64() : 0;
-  Claims cl(nF, gr, B);
+  Claims cl(nF, gr, B, a.run_fill);
   for (;;) {
     if (tid == 0) cl.next(claim, nF, gr, B, sm.cbase, sm.clen);
     __syncthreads();
@@ -1904,7 +1931,7 @@ __device__ void pull_gather(const Args &a, Smem<B, OpPRPull> &sm, Grid gr, int i
   const int tid = threadIdx.x;
   const uint32_t lane = lane_id();
   const uint32_t nF = (uint32_t)a.n;
-  Claims cl(nF, gr, B);
+  Claims cl(nF, gr, B, a.run_fill);
   for (;;) {
     if (tid == 0) cl.next(&a.ctl->chunk[it % 3].v, nF, gr, B, sm.cbase, sm.clen);
     __syncthreads();
