@@ -215,6 +215,7 @@ struct Args {
   int32_t *level;       // BFS levels; k-core: remaining degrees
   uint32_t *vbits;      // BFS, CC: room for the filter bitmap (ceil(n / 32) words), or null: no filter
   int32_t kcore_k;      // k-core: k
+  uint32_t *hot;        // k-core: bitmap of the vertices with many edges (ceil(n / 32) words)
   unsigned long long *word;  // SSSP / CC: (label << 32) | tag, tag = 1 + last round that lowered it
   int32_t *out;         // SSSP / CC: int32 labels written by the finishing kernel
   float *rank;          // PageRank: fp32 ranks

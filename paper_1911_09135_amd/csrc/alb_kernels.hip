@@ -126,7 +126,7 @@ struct OpBFS {
   struct pre_t {
     int32_t cur;
   };
-  static constexpr bool kPush = true, kNeedSrc = false, kRecord = false, kPR = false, kBatch = true;
+  static constexpr bool kPush = true, kNeedSrc = false, kRecord = false, kPR = false, kBatch = true, kHot = false;
   int32_t *level;
   __device__ __forceinline__ val_t load_src(long long, int32_t, uint32_t tag, bool &) const {
     return (int32_t)tag - 1;
@@ -187,7 +187,7 @@ struct OpSSSP {  // relaxation: dist[dst] = min(dist[dst], dist[src] + w)
     int32_t cand;
     unsigned long long cur;
   };
-  static constexpr bool kPush = true, kNeedSrc = false, kRecord = false, kPR = false, kBatch = true;
+  static constexpr bool kPush = true, kNeedSrc = false, kRecord = false, kPR = false, kBatch = true, kHot = false;
   unsigned long long *word;
   const int32_t *w;
   int32_t dedup;
@@ -226,7 +226,7 @@ struct OpCC {  // min-label propagation
   struct pre_t {
     unsigned long long cur;
   };
-  static constexpr bool kPush = true, kNeedSrc = false, kRecord = false, kPR = false, kBatch = false;
+  static constexpr bool kPush = true, kNeedSrc = false, kRecord = false, kPR = false, kBatch = false, kHot = false;
   unsigned long long *word;
   int32_t dedup;
   __device__ __forceinline__ val_t load_src(long long sl, int32_t, uint32_t tag, bool &skip) const {
@@ -285,21 +285,77 @@ struct Filtered<OpCC> {
 // at most once.  Round 0 inspects every vertex (no worklist) and takes those
 // with fewer than k edges, judged by the CSR degree rather than the
 // remaining degree that other lanes are already lowering.
+//
+// Decrements of one hub complete one every 12 ns, whoever issues them (Zipf
+// graph of 1M vertices, k = 16: round 0's 4.9M decrements took 0.75 ms, the
+// 60,000 of the largest hub alone 0.72).  Neighbours of at least kHotDegree
+// edges, marked in a bitmap at set-up, are therefore counted in a table in
+// LDS and lowered once per workgroup at the end of its phase; a vertex whose
+// slot another holds takes the plain path.  Below that degree a hub costs a
+// round 12 us at most, and marking more would only fill the table.
+constexpr int32_t kHotDegree = 1024;
+constexpr uint32_t kHotSlots = 1024, kHotNone = 0xffffffffu;  // slots: a multiple of every workgroup size
+struct HotTable {
+  uint32_t key[kHotSlots], cnt[kHotSlots];
+};
+__device__ __forceinline__ HotTable &hot_table() {
+  __shared__ HotTable t;
+  return t;
+}
+template <int B>
+__device__ __forceinline__ void hot_clear() {
+  for (uint32_t i = threadIdx.x; i < kHotSlots; i += B) {
+    hot_table().key[i] = kHotNone;
+    hot_table().cnt[i] = 0;
+  }
+  __syncthreads();
+}
+
 struct OpKCore {
   using val_t = int32_t;
   static constexpr int kKind = OP_KCORE;
-  struct pre_t {};
-  static constexpr bool kPush = true, kNeedSrc = false, kRecord = false, kPR = false, kBatch = false;
+  struct pre_t {
+    uint32_t hot;
+  };
+  static constexpr bool kPush = true, kNeedSrc = false, kRecord = false, kPR = false, kBatch = false, kHot = true;
   int32_t *rem;
   int32_t k;
+  const uint32_t *hot;
   __device__ __forceinline__ val_t load_src(long long, int32_t deg, uint32_t tag, bool &skip) const {
     if (tag == 1u) skip = deg >= k;
     return 0;
   }
-  __device__ __forceinline__ pre_t prepare(int32_t, long long, val_t, int32_t) const { return {}; }
-  __device__ __forceinline__ bool commit(const pre_t &, int32_t, long long dl, val_t, int32_t, int32_t,
+  __device__ __forceinline__ pre_t prepare(int32_t, long long dl, val_t, int32_t) const {
+    return {(hot[dl >> 5] >> (dl & 31)) & 1u};
+  }
+  __device__ __forceinline__ bool commit(const pre_t &p, int32_t, long long dl, val_t, int32_t, int32_t,
                                          uint32_t) const {
+    if (p.hot) {
+      HotTable &t = hot_table();
+      const uint32_t v = (uint32_t)dl, i = (v * 2654435761u) >> 22;
+      static_assert(kHotSlots == 1u << 10, "the hash keeps ten bits");
+      uint32_t owner = __hip_atomic_load(&t.key[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      if (owner == kHotNone) {
+        const uint32_t was = atomicCAS(&t.key[i], kHotNone, v);
+        owner = was == kHotNone ? v : was;
+      }
+      if (owner == v) {
+        atomicAdd(&t.cnt[i], 1u);
+        return false;
+      }
+    }
     return __hip_atomic_fetch_add(&rem[dl], -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == k;
+  }
+  // slot i's count (at a phase's end): does its vertex leave the core?
+  __device__ __forceinline__ bool settle(uint32_t i, int32_t &v) const {
+    HotTable &t = hot_table();
+    const int32_t c = (int32_t)t.cnt[i];
+    v = (int32_t)t.key[i];
+    t.key[i] = kHotNone;
+    if (c == 0) return false;
+    t.cnt[i] = 0;
+    const int32_t old = __hip_atomic_fetch_add(&rem[v], -c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return old >= k && old - c < k;
   }
 };
 
@@ -310,15 +366,15 @@ struct OpKCore {
 struct OpKCoreFilter : OpKCore {
   const uint32_t *vbits;
   struct pre_t {
+    OpKCore::pre_t core;
     bool gone;
   };
-  __device__ __forceinline__ pre_t prepare(int32_t, long long dl, val_t, int32_t) const {
-    return {((vbits[dl >> 5] >> (dl & 31)) & 1u) != 0u};
+  __device__ __forceinline__ pre_t prepare(int32_t pos, long long dl, val_t sv, int32_t src) const {
+    return {OpKCore::prepare(pos, dl, sv, src), ((vbits[dl >> 5] >> (dl & 31)) & 1u) != 0u};
   }
-  __device__ __forceinline__ bool commit(const pre_t &p, int32_t, long long dl, val_t, int32_t, int32_t,
-                                         uint32_t) const {
-    if (p.gone) return false;
-    return __hip_atomic_fetch_add(&rem[dl], -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == k;
+  __device__ __forceinline__ bool commit(const pre_t &p, int32_t pos, long long dl, val_t sv, int32_t src, int32_t gt,
+                                         uint32_t tag) const {
+    return !p.gone && OpKCore::commit(p.core, pos, dl, sv, src, gt, tag);
   }
 };
 template <>
@@ -328,6 +384,7 @@ struct Filtered<OpKCore> {
     type f;
     f.rem = op.rem;
     f.k = op.k;
+    f.hot = op.hot;
     f.vbits = a.vbits;
     return f;
   }
@@ -338,7 +395,7 @@ struct OpPR {  // acc[dst] += rank[src] / outdeg(src): fp32 contribution, exact 
   using val_t = float;
   static constexpr int kKind = OP_PR;
   struct pre_t {};
-  static constexpr bool kPush = false, kNeedSrc = false, kRecord = false, kPR = true, kBatch = false;
+  static constexpr bool kPush = false, kNeedSrc = false, kRecord = false, kPR = true, kBatch = false, kHot = false;
   const float *rank;
   unsigned long long *acc;
   __device__ __forceinline__ val_t load_src(long long sl, int32_t deg, uint32_t, bool &) const {
@@ -356,7 +413,7 @@ struct OpRecord {  // counts each processed edge and the thread that took it; pu
   using val_t = int32_t;
   static constexpr int kKind = OP_RECORD;
   struct pre_t {};
-  static constexpr bool kPush = true, kNeedSrc = true, kRecord = true, kPR = false, kBatch = false;
+  static constexpr bool kPush = true, kNeedSrc = true, kRecord = true, kPR = false, kBatch = false, kHot = false;
   int32_t *hits;
   int32_t *thread_of;
   __device__ __forceinline__ val_t load_src(long long, int32_t, uint32_t, bool &) const { return 0; }
@@ -391,7 +448,7 @@ OpPR make_op<OpPR>(const Args &a) { return OpPR{a.rank, a.acc}; }
 template <>
 OpRecord make_op<OpRecord>(const Args &a) { return OpRecord{a.hits, a.thread_of}; }
 template <>
-OpKCore make_op<OpKCore>(const Args &a) { return OpKCore{a.level, a.kcore_k}; }
+OpKCore make_op<OpKCore>(const Args &a) { return OpKCore{a.level, a.kcore_k, a.hot}; }
 
 // ---------------------------------------------------------------------------
 // Per-thread statistics, shared memory, work-distribution grid, push staging.
@@ -565,6 +622,19 @@ __device__ __forceinline__ void flush_phase(const Args &a, S &sm, int round, Pus
   if (threadIdx.x == 0) sm.pbase = add_relaxed(pu.qn_cnt, total);
   __syncthreads();
   if (pu.cnt) write_pushes(a, round, pu, sm.pbase + before);
+}
+
+// A phase's end, before flush_phase: the hot counts become decrements and pushes.
+template <int B, class Op, class E>
+__device__ __forceinline__ void settle_hot(const Args &a, const Op &op, int round, Pusher<E> &pu, Acc &acc) {
+  if constexpr (Op::kHot) {
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < kHotSlots; i += B) {
+      int32_t v;
+      const bool p = op.settle(i, v);
+      push_wave<E>(p, (E)v, a, round, pu, acc);
+    }
+  }
 }
 
 // log2 of the chunk size of the huge-edge index for a threshold t: the
@@ -956,6 +1026,7 @@ __device__ void phase_twc(const Args &a, const Op &op, S &sm, Grid gr, int round
     }
     prof_mark(a, acc, kProfThreadBin, pt);
   }
+  settle_hot<B>(a, op, round, pu, acc);
   if constexpr (Op::kPush) flush_phase<B>(a, sm, round, pu);
   prof_mark(a, acc, kProfThreadBin, pt);
 }
@@ -1048,6 +1119,7 @@ __device__ void phase_lb(const Args &a, const Op &op, S &sm, Grid gr, int round,
       edges<Op, M>(act, pos, s, src, op, a, tag, round, pu, acc, (int32_t)g);
     }
   }
+  settle_hot<B>(a, op, round, pu, acc);
   if constexpr (Op::kPush) flush_phase<B>(a, sm, round, pu);
   prof_mark(a, acc, kProfLb, pt);
 }
@@ -1117,6 +1189,9 @@ __device__ bool grid_barrier(const Args &a, S &sm, Grid gr, unsigned long long &
                              bool sys = false) {
   wait_memory();
   __syncthreads();
+  if constexpr (!kFull) {
+    if (gr.n == 1) return true;  // a lone workgroup
+  }
   if (threadIdx.x == 0) {
     unsigned long long *b = a.bar;
     const unsigned long long target = epoch + 1;
@@ -1300,7 +1375,13 @@ __device__ __forceinline__ void init_label(const Args &a, int op, T v) {
   if (op == OP_SSSP)
     st_relaxed(&a.word[v], (unsigned long long)(uint32_t)((int32_t)v == a.source ? 0 : kInf) << 32);
   if (op == OP_CC) st_relaxed(&a.word[v], (unsigned long long)v << 32);
-  if (op == OP_KCORE) st_relaxed(&a.level[v], a.off[v + 1] - a.off[v]);
+  if (op == OP_KCORE) {  // the wavefront's lanes hold 64 consecutive vertices from a multiple of 64 on
+    const int32_t deg = a.off[v + 1] - a.off[v];
+    st_relaxed(&a.level[v], deg);
+    const unsigned long long hot = __ballot(deg >= kHotDegree);
+    const uint32_t lane = lane_id(), x = (uint32_t)v / kWave * 2u + lane;
+    if (lane < 2 && x < ((uint32_t)a.n + 31u) / 32u) st_relaxed(&a.hot[x], (uint32_t)(hot >> (32 * lane)));
+  }
   if (op == OP_PR) {
     a.rank[v] = 1.0f / (float)a.n;
     a.acc[v] = 0ull;
@@ -1442,6 +1523,7 @@ __device__ __forceinline__ void leave(const Args &a, S &sm, Grid gr) {
 template <int B, class Op>
 __global__ __launch_bounds__(B) void k_twc(Args a, Op op) {
   __shared__ Smem<B, Op> sm;
+  if constexpr (Op::kHot) hot_clear<B>();
   Acc acc;
   const int r = a.round;
   const uint32_t nF = round_size(a, r);
@@ -1458,6 +1540,7 @@ __global__ __launch_bounds__(B) void k_twc(Args a, Op op) {
 template <int B, class Op>
 __global__ __launch_bounds__(B) void k_lb(Args a, Op op) {
   __shared__ Smem<B, Op> sm;
+  if constexpr (Op::kHot) hot_clear<B>();
   Acc acc;
   const int r = a.round;
   const unsigned long long hc = ld_relaxed(&a.ctl->huge[r & 1].v);
@@ -1514,6 +1597,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
   if (a.threshold < 0) a.threshold = (int64_t)gr.n * B;  // the launched thread count (the paper's rule)
   unsigned long long epoch = 0, prof_last = 0;
   set_up<B, Op, M>(a, gr);
+  if constexpr (Op::kHot) hot_clear<B>();
   bool ok;
   if constexpr (F) {
     [[clang::always_inline]] ok = grid_barrier<Op::kPR>(a, sm, gr, epoch, 0);
@@ -1894,7 +1978,7 @@ struct OpPRPull {  // type facts for Smem only; the pull phases do the work
   using val_t = float;
   static constexpr int kKind = OP_PR;
   struct pre_t {};
-  static constexpr bool kPush = false, kNeedSrc = false, kRecord = false, kPR = true, kBatch = false;
+  static constexpr bool kPush = false, kNeedSrc = false, kRecord = false, kPR = true, kBatch = false, kHot = false;
 };
 
 // Fixed-point contributions of up to kU in-edges per lane, loads issued first.
