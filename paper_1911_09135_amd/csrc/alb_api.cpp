@@ -65,12 +65,15 @@ struct Workspace {
   Ctl *ctl = nullptr;
   int turn = 0;
   bool cleared = false;
+  void *tiles = nullptr;  // PageRank in tiles: its layout (made when first needed)
+  size_t tiles_bytes = 0;
   Ctl *h_ctl = nullptr;  // pinned host mirror (host loop, profiling)
   Result *h_res = nullptr;  // pinned, behind it: a persistent launch's result
   hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
   size_t bytes = 0;
 
   void release() {
+    (void)hipFree(tiles);
     (void)hipFree(q0);
     (void)hipFree(q1);
     (void)hipFree(huge_rec);
@@ -551,9 +554,11 @@ alb_status resident_workgroups(alb_graph g, OpKind op, int wg, int *out, bool ba
   auto it = g_res.find(key);
   if (it == g_res.end()) {
     int per_cu = 0;
-    HIP_TRY(open    ? open_occupancy(op, wg, &per_cu)
-            : batch ? batch_occupancy(op, wg, &per_cu)
-                    : op == OP_PR_PULL ? pull_occupancy(wg, &per_cu) : persistent_occupancy(op, wg, &per_cu));
+    HIP_TRY(open                ? open_occupancy(op, wg, &per_cu)
+            : batch             ? batch_occupancy(op, wg, &per_cu)
+            : op == OP_PR_TILES ? pr_tiles_occupancy(&per_cu)
+            : op == OP_PR_PULL  ? pull_occupancy(wg, &per_cu)
+                                : persistent_occupancy(op, wg, &per_cu));
     if (per_cu < 1) return fail(ALB_E_DEVICE, "persistent kernel does not fit on a CU with wg_size %d", wg);
     it = g_res.emplace(key, per_cu * g->cus).first;
   }
@@ -674,6 +679,46 @@ double ticks_ms(alb_graph g, unsigned long long from, unsigned long long to) {
   return to > from ? (double)(to - from) / (double)g->clock_khz : 0.0;
 }
 
+// Whether push PageRank goes over the in-edges in tiles.  Where the handle
+// holds them, always; else they are laid out first, which pays from about two
+// iterations on large graphs and ten on the smallest.  Measured (us a call of 2 /
+// 10 iterations, tiles against bins): RMAT-8 72 / 115 against 58 / 172, RMAT-12
+// 131 / 231 against 88 / 321, RMAT-14 192 / 293 against 168 / 721, RMAT-16 374 /
+// 489 against 485 / 2,295, Zipf 1M 654 / 1,367 against 1,360 / 6,644, RMAT-20
+// 2,226 / 3,142 against 4,372 / 21,714.
+bool push_in_tiles(alb_graph g, int32_t iterations) {
+  return g->d_toff || iterations >= 10 || (iterations >= 2 && (int64_t)iterations * g->m >= (int64_t)1 << 19);
+}
+
+// The balancer's default settings (a call that asks for others gets the bins and the cyclic distribution it sets).
+bool default_balance(const alb_options &o) {
+  return o.mode == ALB_MODE_ALB && o.huge_threshold == ALB_THRESHOLD_DEFAULT && o.distribution == 0 &&
+         o.wg_size == 256 && o.wave_cutoff == 64 && o.wg_cutoff == 256 && o.grid_wgs == 0 &&
+         o.launch != ALB_LAUNCH_HOST_LOOP;
+}
+
+// Make sure that ws holds `bytes` of tile layout; false if the device has no
+// room for it (the call then takes the bins).
+bool reserve_tiles(Workspace *ws, size_t bytes) {
+  if (ws->tiles_bytes >= bytes) return true;
+  (void)hipFree(ws->tiles);
+  ws->bytes -= ws->tiles_bytes;
+  ws->tiles = nullptr;
+  ws->tiles_bytes = 0;
+  // (a quarter of what is free at most, so that calls which ran beside other
+  // programs' or handles' memory still do)
+  size_t free_bytes = 0, total = 0;
+  unsigned char *p = nullptr;
+  if (hipMemGetInfo(&free_bytes, &total) != hipSuccess || bytes > free_bytes / 4 ||
+      dalloc(&p, bytes, ws->bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  ws->tiles = p;
+  ws->tiles_bytes = bytes;
+  return true;
+}
+
 // Worklist capacity and chunk-index entries a call needs, and whether it
 // suppresses duplicate pushes.
 Needs job_needs(alb_graph g, const Job &job, const alb_options &o, bool *dedup_out) {
@@ -708,6 +753,9 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
   if (rs != ALB_OK) return rs;
   int launch = o.launch;
   if (launch == ALB_LAUNCH_AUTO) launch = ALB_LAUNCH_PERSISTENT;
+  // PageRank in tiles takes no balancer settings: it is the default ones' path
+  const bool in_tiles = (job.op == OP_PR_PULL || (job.op == OP_PR && push_in_tiles(g, job.max_rounds))) &&
+                        job.max_rounds > 0 && default_balance(o) && !fixed;
   const int grid = o.grid_wgs > 0                ? o.grid_wgs
                    : o.grid_wgs == ALB_GRID_ALL ? resident
                                                 : auto_grid(g->m, wg, resident);
@@ -810,6 +858,70 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
     a.toff = g->d_toff;
     a.tcol = g->d_tcol;
   }
+  int pr_grid = 0;  // PageRank in tiles: its workgroups
+  Transpose tr;
+  std::memset(&tr, 0, sizeof tr);
+  if (in_tiles) {
+    const uint64_t items = (uint64_t)g->n + (uint64_t)g->m;
+    const uint32_t tiles = (uint32_t)((items + kTileItems - 1) / kTileItems);
+    size_t at = 0;
+    auto take = [&](size_t bytes) {
+      const size_t p = at;
+      at += (bytes + 255) & ~(size_t)255;
+      return p;
+    };
+    const size_t p_row = take(sizeof(uint32_t) * ((size_t)tiles + 1));
+    size_t p_lrow, p_toff = 0, p_tcol = 0, p_hist = 0, p_start = 0, p_cursor = 0;
+    bool fits = true;
+    const bool transpose = !g->d_toff;
+    if (transpose) {
+      const auto bins_of = [&](int bits) { return ((uint64_t)g->n + (1u << bits) - 1) >> bits; };
+      tr.bits = kBinBitsMin;
+      while (tr.bits < kBinBits && bins_of(tr.bits) > (uint64_t)kBinsWanted) ++tr.bits;
+      while (tr.bits < kBinBitsMax && bins_of(tr.bits) > (uint64_t)kBinsMax) ++tr.bits;
+      const uint64_t bins = bins_of(tr.bits);
+      fits = bins <= (uint64_t)kBinsMax;
+      tr.bins = (uint32_t)bins;
+      p_lrow = take(sizeof(uint2) * (size_t)g->m);  // the pairs, and once they are sorted the tiles' rows
+      p_toff = take(sizeof(int32_t) * ((size_t)g->n + 1));
+      p_tcol = take(sizeof(int32_t) * (size_t)g->m);
+      p_hist = take(sizeof(uint32_t) * (size_t)kTransposeWgs * tr.bins);
+      p_start = take(sizeof(uint32_t) * ((size_t)tr.bins + 1));
+      p_cursor = take(sizeof(uint32_t) * (size_t)tr.bins);
+    } else {
+      p_lrow = take(sizeof(uint16_t) * (size_t)g->m);
+    }
+    if (fits && reserve_tiles(ws, at)) {
+      int held = 0;
+      rs = resident_workgroups(g, OP_PR_TILES, kTileWg, &held);
+      if (rs != ALB_OK) return rs;
+      pr_grid = (int)std::min<uint32_t>((uint32_t)held, tiles);
+      unsigned char *b = (unsigned char *)ws->tiles;
+      a.n_tiles = tiles;
+      a.tile_row = (uint32_t *)(b + p_row);
+      a.tile_lrow = (uint16_t *)(b + p_lrow);
+      a.contrib = (float *)ws->word;  // (room for 2 n fp32)
+      a.contrib2 = a.contrib + g->n;
+      a.toff = g->d_toff;
+      a.tcol = g->d_tcol;
+      a.insp_off = job.op == OP_PR ? g->d_off : g->d_toff;
+      a.insp_threshold = job.op == OP_PR && adaptive && (int64_t)g->n < T ? small_threshold : threshold;
+      if (transpose) {
+        tr.off = g->d_off;
+        tr.col = g->d_col;
+        tr.n = g->n;
+        tr.m = (uint32_t)g->m;
+        tr.hist = (uint32_t *)(b + p_hist);
+        tr.start = (uint32_t *)(b + p_start);
+        tr.cursor = (uint32_t *)(b + p_cursor);
+        tr.pairs = (uint2 *)(b + p_lrow);
+        tr.toff = (int32_t *)(b + p_toff);
+        tr.tcol = (int32_t *)(b + p_tcol);
+        a.toff = tr.toff;
+        a.tcol = tr.tcol;
+      }
+    }
+  }
   if (job.op == OP_PR || job.op == OP_PR_PULL) {
     a.rank = dev_out ? (float *)dev_out : ws->rank;
     a.acc = ws->acc;
@@ -851,7 +963,10 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
     }
     if (fixed || !ws->cleared) HIP_TRY(launch_clear(a, stream));
     ws->cleared = false;  // until this launch is known to have cleared the other one
-    if (job.op == OP_PR_PULL)
+    if (tr.toff) HIP_TRY(launch_transpose(tr, stream));
+    if (pr_grid)
+      HIP_TRY(launch_pr_tiles(pr_grid, a, stream));
+    else if (job.op == OP_PR_PULL)
       HIP_TRY(launch_pull_pr(wg, grid, a, stream));
     else
       HIP_TRY(launch_persistent(job.op, wg, grid, a, stream));

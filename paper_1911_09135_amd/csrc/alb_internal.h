@@ -124,6 +124,7 @@ struct Ctl {
   Line<uint32_t> qcount[3];          // worklist sizes: round r reads [r % 3], pushes into [(r + 1) % 3]
   Line<unsigned long long> huge[2];  // round r: (count << 32) | edge total of the huge worklist, [r & 1]
   Line<unsigned long long> dangling[2]; // PageRank: rank mass without out-edges (fixed point), iteration it in [it & 1]
+  Line<unsigned long long> tile_dangling[3][kStatXcds]; // the same in tiles (k_pr_tiles): [it % 3], a part per XCD
   Line<unsigned long long> chunk[3]; // worklist entries claimed in phase 1 of round r: [r % 3]
   alignas(128) uint32_t overflow;    // first round in which a worklist overflowed (0xffffffff: none)
   uint32_t rounds;                   // rounds completed (written by workgroup 0)
@@ -169,7 +170,31 @@ constexpr int kTimeline = 64;
 constexpr int kProfMembers = 8192;
 enum { kProfInspect = 0, kProfWgBin, kProfWaveBin, kProfThreadBin, kProfLb, kProfBarrier, kProfParts };
 
-enum OpKind : int { OP_BFS = 0, OP_SSSP = 1, OP_CC = 2, OP_PR = 3, OP_RECORD = 4, OP_KCORE = 5, OP_PR_PULL = 6 };
+// Transposing a graph on the device: destinations per bin as a power of two
+// (at least 2^kBinBitsMin and as many as give kBinsWanted bins, so that two
+// sorting workgroups per CU run at once; beyond 2^kBinBits of them up to
+// kBinsMax bins, then up to 2^kBinBitsMax), and the workgroups that take a
+// contiguous share of the edges each.
+constexpr int kBinBitsMin = 6, kBinBits = 12, kBinBitsMax = 13, kBinsWanted = 1024, kBinsMax = 8192;
+constexpr int kTransposeWgs = 512;
+struct Transpose {
+  const int32_t *off, *col;  // CSR
+  int32_t n;
+  uint32_t m;
+  int bits;                  // destination v falls into bin v >> bits
+  uint32_t bins;
+  uint32_t *hist;            // [kTransposeWgs][bins]
+  uint32_t *start;           // bins + 1: edges before the bin
+  uint32_t *cursor;          // bins: totals, then the next free place
+  uint2 *pairs;              // m: (source, destination), by bin
+  int32_t *toff, *tcol;      // the result: n + 1 and m
+};
+
+// PageRank in tiles: rows and in-edges together per tile, and threads per workgroup.
+constexpr uint32_t kTileItems = 4096;
+constexpr int kTileWg = 256;
+
+enum OpKind : int { OP_BFS = 0, OP_SSSP = 1, OP_CC = 2, OP_PR = 3, OP_RECORD = 4, OP_KCORE = 5, OP_PR_PULL = 6, OP_PR_TILES = 7 };
 
 // Everything a traversal kernel reads.  Passed by value.
 struct Args {
@@ -222,6 +247,16 @@ struct Args {
   float *contrib;       // pull PageRank: rank(u) / outdeg(u) of the current iteration
   const int32_t *toff;  // pull PageRank: transposed CSR (in-edges), n + 1
   const int32_t *tcol;  //   and m sources
+  // PageRank in tiles (k_pr_tiles): the tiles' first rows (n_tiles + 1), each
+  // in-edge's row relative to its tile's first, the second array of
+  // contributions, and the offsets whose degrees the inspection counts
+  // against insp_threshold
+  uint32_t *tile_row;
+  uint16_t *tile_lrow;
+  uint32_t n_tiles;
+  float *contrib2;
+  const int32_t *insp_off;
+  int64_t insp_threshold;
   unsigned long long *acc;  // exact sums of fp32 contributions in 64-bit fixed point (kFix)
   float damping;
   int32_t *hits;        // trace operator
@@ -264,6 +299,11 @@ hipError_t launch_pr_update(int wg, int grid, const Args &a, hipStream_t s);
 // Pull PageRank: every iteration in one persistent launch.
 hipError_t launch_pull_pr(int wg, int grid, const Args &a, hipStream_t s);
 hipError_t pull_occupancy(int wg, int *blocks_per_cu);
+// PageRank over the in-edges in tiles (Args::tile_row and what follows it).
+hipError_t launch_pr_tiles(int grid, const Args &a, hipStream_t s);
+hipError_t pr_tiles_occupancy(int *blocks_per_cu);
+// In-edge CSR of a graph (the sources of a row in no particular order).
+hipError_t launch_transpose(const Transpose &t, hipStream_t s);
 hipError_t launch_persistent(OpKind op, int wg, int grid, const Args &a, hipStream_t s);
 // Host loop.  SSSP / CC: out[v] = word[v] >> 32; k-core: out[v] = (level[v] >= k).
 hipError_t launch_finish(OpKind op, const Args &a, hipStream_t s);

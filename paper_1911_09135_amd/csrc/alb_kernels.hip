@@ -1349,6 +1349,8 @@ __device__ void reset_ctl(Ctl *c) {
     c->qcount[k].v = 0;
     c->chunk[k].v = 0;
   }
+  for (int k = 0; k < 3; ++k)
+    for (int x = 0; x < kStatXcds; ++x) c->tile_dangling[k][x].v = 0;
   for (int k = 0; k < 2; ++k) {
     c->huge[k].v = 0;
     c->dangling[k].v = 0;
@@ -2211,6 +2213,439 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
 }
 
 // ---------------------------------------------------------------------------
+// Transposing a graph on the device, for push PageRank in tiles: edges go to
+// bins of destinations, and each bin is sorted by counting in LDS.  Global
+// atomics are one per workgroup and bin (a scatter with one per edge would
+// take 15M / 23.5 G/s = 0.65 ms on a graph of 1M vertices, as much as a push
+// iteration; this takes 0.32 ms; RMAT scale 20, whose heaviest bin holds 6 % of
+// the edges, 1.5).
+// ---------------------------------------------------------------------------
+constexpr int kTrWg = 256, kTrSortWg = 1024;
+constexpr uint32_t kTrStep = 4096;  // edges whose sources are expanded together
+
+__device__ __forceinline__ uint32_t tr_edge(const Transpose &t, uint32_t w) {
+  return (uint32_t)((uint64_t)t.m * w / kTransposeWgs);
+}
+
+// Edges per bin, of each workgroup's share and in all.
+__global__ __launch_bounds__(kTrWg) void k_tr_count(Transpose t) {
+  extern __shared__ uint32_t bin[];
+  const uint32_t e0 = tr_edge(t, blockIdx.x), e1 = tr_edge(t, blockIdx.x + 1);
+  for (uint32_t b = threadIdx.x; b < t.bins; b += kTrWg) bin[b] = 0;
+  __syncthreads();
+  for (uint32_t e = e0 + threadIdx.x; e < e1; e += 4 * kTrWg) {
+    uint32_t v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = e + k * kTrWg < e1 ? (uint32_t)t.col[e + k * kTrWg] : 0u;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (e + k * kTrWg < e1) atomicAdd(&bin[v[k] >> t.bits], 1u);
+  }
+  __syncthreads();
+  for (uint32_t b = threadIdx.x; b < t.bins; b += kTrWg) {
+    const uint32_t c = bin[b];
+    t.hist[(size_t)blockIdx.x * t.bins + b] = c;
+    if (c) add_relaxed(&t.cursor[b], c);
+  }
+}
+
+// Exclusive prefix sum over len entries of LDS by the whole workgroup of B
+// threads (len a multiple of B or smaller than it); returns the total.
+template <int B>
+__device__ __forceinline__ uint32_t lds_exscan(uint32_t *x, uint32_t len, uint32_t *wsum) {
+  const uint32_t per = (len + B - 1) / B, i0 = threadIdx.x * per;
+  uint32_t sum = 0;
+  for (uint32_t k = 0; k < per && i0 + k < len; ++k) sum += x[i0 + k];
+  int32_t excl, total;
+  block_exscan<B>((int32_t)sum, excl, total, (int32_t *)wsum);
+  uint32_t at = (uint32_t)excl;
+  for (uint32_t k = 0; k < per && i0 + k < len; ++k) {
+    const uint32_t c = x[i0 + k];
+    x[i0 + k] = at;
+    at += c;
+  }
+  __syncthreads();
+  return (uint32_t)total;
+}
+
+// Totals per bin -> start of each bin (one workgroup).
+__global__ __launch_bounds__(kTrSortWg) void k_tr_start(Transpose t) {
+  __shared__ uint32_t x[kBinsMax], wsum[kTrSortWg / kWave];
+  for (uint32_t b = threadIdx.x; b < t.bins; b += kTrSortWg) x[b] = t.cursor[b];
+  __syncthreads();
+  lds_exscan<kTrSortWg>(x, t.bins, wsum);
+  for (uint32_t b = threadIdx.x; b < t.bins; b += kTrSortWg) t.start[b] = t.cursor[b] = x[b];
+  if (threadIdx.x == 0) t.start[t.bins] = t.m;
+}
+
+// The last row that begins at or before edge e and has edges (e < m).
+__device__ __forceinline__ uint32_t row_of_edge(const int32_t *off, uint32_t n, uint32_t e) {
+  uint32_t lo = 0, hi = n;  // off[lo] <= e < off[hi]
+  while (hi - lo > 1) {
+    const uint32_t mid = lo + ((hi - lo) >> 1);
+    if ((uint32_t)off[mid] <= e)
+      lo = mid;
+    else
+      hi = mid;
+  }
+  return lo;
+}
+
+// Every edge into its bin.
+__global__ __launch_bounds__(kTrWg) void k_tr_scatter(Transpose t) {
+  extern __shared__ uint32_t bin[];  // next place of this workgroup's edges per bin
+  constexpr uint32_t kRun = kTrStep / kTrWg;
+  __shared__ uint32_t row[kTrStep], wmax[kTrWg / kWave], first[kTrWg + 1];
+  const uint32_t tid = threadIdx.x, lane = lane_id();
+  const uint32_t e0 = tr_edge(t, blockIdx.x), e1 = tr_edge(t, blockIdx.x + 1);
+  if (e0 == e1) return;
+  for (uint32_t b = tid; b < t.bins; b += kTrWg) {
+    const uint32_t c = t.hist[(size_t)blockIdx.x * t.bins + b];
+    bin[b] = c ? add_relaxed(&t.cursor[b], c) : 0u;
+  }
+  for (uint32_t g0 = e0; g0 < e1; g0 += kTrStep * kTrWg) {  // first rows of up to kTrWg steps at a time
+    if (g0 + (uint64_t)tid * kTrStep < e1) first[tid] = row_of_edge(t.off, (uint32_t)t.n, g0 + tid * kTrStep);
+    if (tid == 0) {
+      const uint32_t end = (uint32_t)min((uint64_t)g0 + (uint64_t)kTrStep * kTrWg, (uint64_t)e1);
+      first[(end - g0 + kTrStep - 1) / kTrStep] = row_of_edge(t.off, (uint32_t)t.n, end - 1);
+    }
+    __syncthreads();
+    for (uint32_t s = 0; s < (uint32_t)kTrWg; ++s) {
+      const uint64_t s0 = (uint64_t)g0 + (uint64_t)s * kTrStep;
+      if (s0 >= e1) break;
+      const uint32_t b0 = (uint32_t)s0, ne = min(kTrStep, e1 - b0);
+      // the source of each edge: mark every row's first edge, then a running maximum
+      for (uint32_t i = tid; i < kTrStep; i += kTrWg) row[i] = 0;
+      __syncthreads();
+      for (uint32_t r = first[s] + tid; r <= first[s + 1]; r += kTrWg) {
+        const uint32_t p0 = (uint32_t)t.off[r], p1 = (uint32_t)t.off[r + 1], p = max(p0, b0);
+        if (p < p1 && p < b0 + ne) row[p - b0] = r;
+      }
+      __syncthreads();
+      uint32_t x[kRun], top = 0;
+#pragma unroll
+      for (uint32_t k = 0; k < kRun; ++k) {
+        top = max(top, row[tid * kRun + k]);
+        x[k] = top;
+      }
+      uint32_t incl = top;
+#pragma unroll
+      for (int d = 1; d < kWave; d <<= 1) {
+        const uint32_t y = __shfl_up(incl, d);
+        if ((int)lane >= d) incl = max(incl, y);
+      }
+      if (lane == kWave - 1) wmax[tid / kWave] = incl;
+      __syncthreads();
+      uint32_t before = __shfl_up(incl, 1);
+      if (lane == 0) before = 0;
+      for (uint32_t j = 0; j < tid / kWave; ++j) before = max(before, wmax[j]);
+#pragma unroll
+      for (uint32_t k = 0; k < kRun; ++k) row[tid * kRun + k] = max(before, x[k]);
+      __syncthreads();
+      for (uint32_t i = tid; i < ne; i += kTrWg) {
+        const uint32_t v = (uint32_t)t.col[b0 + i];
+        const uint32_t at = atomicAdd(&bin[v >> t.bits], 1u);
+        t.pairs[at] = make_uint2(row[i], v);
+      }
+      __syncthreads();
+    }
+  }
+}
+
+// One bin: count its destinations, offsets, sources in place.
+__global__ __launch_bounds__(kTrSortWg) void k_tr_sort(Transpose t) {
+  extern __shared__ uint32_t cnt[];  // 1 << bits
+  __shared__ uint32_t wsum[kTrSortWg / kWave];
+  const uint32_t b = blockIdx.x, width = 1u << t.bits;
+  const uint32_t s0 = t.start[b], s1 = t.start[b + 1];
+  const uint32_t v0 = b << t.bits;
+  for (uint32_t i = threadIdx.x; i < width; i += kTrSortWg) cnt[i] = 0;
+  __syncthreads();
+  for (uint32_t p = s0 + threadIdx.x; p < s1; p += 4 * kTrSortWg) {
+    uint32_t v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = p + k * kTrSortWg < s1 ? t.pairs[p + k * kTrSortWg].y : v0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (p + k * kTrSortWg < s1) atomicAdd(&cnt[v[k] - v0], 1u);
+  }
+  __syncthreads();
+  lds_exscan<kTrSortWg>(cnt, width, wsum);
+  for (uint32_t i = threadIdx.x; i < width; i += kTrSortWg) {
+    if (v0 + i < (uint32_t)t.n) t.toff[v0 + i] = (int32_t)(s0 + cnt[i]);
+  }
+  if (b == t.bins - 1 && threadIdx.x == 0) t.toff[t.n] = (int32_t)t.m;
+  __syncthreads();
+  for (uint32_t p = s0 + threadIdx.x; p < s1; p += 4 * kTrSortWg) {
+    uint2 x[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = p + k * kTrSortWg < s1 ? t.pairs[p + k * kTrSortWg] : make_uint2(0u, v0);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (p + k * kTrSortWg < s1) t.tcol[s0 + atomicAdd(&cnt[x[k].y - v0], 1u)] = (int32_t)x[k].x;
+  }
+}
+
+__global__ void k_tr_zero(Transpose t) {
+  for (uint32_t b = blockIdx.x * blockDim.x + threadIdx.x; b < t.bins; b += gridDim.x * blockDim.x) t.cursor[b] = 0;
+}
+
+// ---------------------------------------------------------------------------
+// PageRank in tiles, for the balancer's default settings.  The rows and
+// in-edges of the transposed graph, merged in order (each row's edges, then
+// its end), are cut into tiles of kTileItems, so that every tile costs the
+// same whatever the in-degrees; each workgroup keeps its run of tiles
+// through all iterations.  A tile's edges are read in order, four and two
+// bytes each (source, and row relative to the tile's first, laid out once per
+// call), and their contributions gathered from an array that the L2s hold up
+// to a few million vertices; sums are exact 64-bit integers added in LDS,
+// where the order does not matter and neighbouring lanes of one row only
+// serialise within the CU.  A row that ends in the tile is updated at once: its
+// new contribution goes to a second array, its sum never to memory.  Only rows
+// cut by a workgroup boundary meet in memory, between the two barriers of an
+// iteration.  The bin kernels above spent their time in chains of dependent
+// loads per vertex, skew and full barriers (RMAT scale 20, 16M edges: 289 us an
+// iteration against 104 here; scale 22 853 and 405; Zipf 1M 114 and 90; the gathers alone take 64 at the L2s' 250 G/s).
+// The sums, and so the ranks, are bit for bit the same.
+// ---------------------------------------------------------------------------
+constexpr int kTileLoads = 8;  // edges in flight per lane
+
+template <int B>
+struct SmemTiles {
+  union {
+    unsigned long long acc[kTileItems + 1];  // sums of the tile's rows
+    uint16_t row[kTileItems];                // set-up: rows of the tile's edges
+  };
+  unsigned long long carry, defer;  // sums: of the row the last tile left open; of the row shared with earlier workgroups
+  unsigned long long part[B / kWave];
+  uint32_t wmax[B / kWave];
+  int32_t flag;
+  uint32_t ticket, members, xcd, xcd_n, n_xcd;
+};
+
+// Rows that end within the first d merged items.
+__device__ __forceinline__ uint32_t rows_within(const int32_t *off, uint32_t n, uint64_t m, uint64_t d) {
+  uint64_t lo = d > m ? d - m : 0, hi = d < n ? d : n;
+  while (lo < hi) {
+    const uint64_t mid = (lo + hi) >> 1;
+    if ((uint64_t)(uint32_t)off[mid + 1] + mid + 1 <= d)
+      lo = mid + 1;
+    else
+      hi = mid;
+  }
+  return (uint32_t)lo;
+}
+
+struct Tile {
+  uint32_t row, rows;  // first row and rows that end in it
+  uint32_t edge, edges;
+};
+__device__ __forceinline__ Tile tile_at(const Args &a, uint64_t items, uint32_t t) {
+  const uint64_t d0 = (uint64_t)t * kTileItems, d1 = min(d0 + kTileItems, items);
+  const uint32_t r0 = a.tile_row[t], r1 = a.tile_row[t + 1];
+  const uint32_t e0 = (uint32_t)(d0 - r0);
+  return {r0, r1 - r0, e0, (uint32_t)(d1 - r1) - e0};
+}
+
+// Lay the workgroup's tiles [t0, t1) out: first rows, and each edge's row.
+template <int B>
+__device__ void lay_out_tiles(const Args &a, SmemTiles<B> &sm, uint64_t m, uint32_t t0, uint32_t t1) {
+  static_assert(kTileItems % B == 0, "whole runs per thread");
+  constexpr uint32_t kRun = kTileItems / B;
+  const uint32_t tid = threadIdx.x, lane = lane_id();
+  const uint32_t n = (uint32_t)a.n;
+  const uint64_t items = (uint64_t)n + m;
+  if (t0 < t1)
+    for (uint32_t t = t0 + tid; t <= t1; t += B)
+      a.tile_row[t] = rows_within(a.toff, n, m, min((uint64_t)t * kTileItems, items));
+  __syncthreads();
+  for (uint32_t t = t0; t < t1; ++t) {
+    const Tile tl = tile_at(a, items, t);
+    for (uint32_t i = tid; i < kTileItems; i += B) sm.row[i] = 0;
+    __syncthreads();
+    // the first edge of every row that has one here
+    for (uint32_t l = tid; l <= tl.rows && tl.row + l < n; l += B) {
+      const uint32_t s0 = (uint32_t)a.toff[tl.row + l], s1 = (uint32_t)a.toff[tl.row + l + 1];
+      const uint32_t s = max(s0, tl.edge);
+      if (s < s1 && s < tl.edge + tl.edges) sm.row[s - tl.edge] = (uint16_t)l;
+    }
+    __syncthreads();
+    // running maximum: kRun consecutive entries per thread, then over the threads
+    uint32_t x[kRun], top = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kRun; ++k) {
+      top = max(top, (uint32_t)sm.row[tid * kRun + k]);
+      x[k] = top;
+    }
+    uint32_t incl = top;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+      const uint32_t y = __shfl_up(incl, d);
+      if ((int)lane >= d) incl = max(incl, y);
+    }
+    if (lane == kWave - 1) sm.wmax[tid / kWave] = incl;
+    __syncthreads();
+    uint32_t before = __shfl_up(incl, 1);
+    if (lane == 0) before = 0;
+    for (uint32_t j = 0; j < tid / kWave; ++j) before = max(before, sm.wmax[j]);
+#pragma unroll
+    for (uint32_t k = 0; k < kRun; ++k) {
+      const uint32_t i = tid * kRun + k;
+      if (i < tl.edges) a.tile_lrow[tl.edge + i] = (uint16_t)max(before, x[k]);
+    }
+    __syncthreads();
+  }
+}
+
+template <int B>
+__global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(4))) void k_pr_tiles(Args a) {
+  __shared__ SmemTiles<B> sm;
+  Acc acc;
+  Grid gr;
+  if (!join_members(a, sm, &gr)) return;
+  const uint32_t tid = threadIdx.x;
+  const uint32_t n = (uint32_t)a.n;
+  const uint64_t m = (uint64_t)(uint32_t)a.toff[n];
+  const uint64_t items = (uint64_t)n + m;
+  const uint32_t t0 = (uint32_t)((uint64_t)a.n_tiles * gr.id / gr.n);
+  const uint32_t t1 = (uint32_t)((uint64_t)a.n_tiles * (gr.id + 1) / gr.n);
+  const uint32_t stripe = xcd_id() % kStatXcds;
+  unsigned long long epoch = 0, dangling = 0;
+  // add the workgroup's dangling mass to iteration it's
+  auto flush = [&](int it) {
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1) dangling += __shfl_xor(dangling, d);
+    if (lane_id() == 0) sm.part[tid / kWave] = dangling;
+    __syncthreads();
+    if (tid == 0) {
+      unsigned long long t = 0;
+      for (int j = 0; j < B / kWave; ++j) t += sm.part[j];
+      if (t) add_relaxed(&a.ctl->tile_dangling[it % 3][stripe].v, t);
+    }
+    dangling = 0;
+  };
+
+  // set-up: the inspection's counts (every iteration works on every vertex),
+  // first contributions, dangling mass, cleared meeting sums, the tiles
+  if (a.clear_ctl) {
+    for (size_t i = gr.id * B + tid; i < kBarWords; i += (size_t)gr.n * B) a.clear_bar[i] = 0ull;
+    if (gr.id == 0 && tid == B - 1) reset_ctl(a.clear_ctl);
+  }
+  const float r0 = 1.0f / (float)a.n;
+  for (uint32_t v = gr.id * B + tid; v < n; v += gr.n * B) {
+    const int32_t deg = a.insp_off[v + 1] - a.insp_off[v];
+    const bool huge = deg > 0 && (int64_t)deg >= a.insp_threshold;
+    acc.frontier += (unsigned long long)a.max_rounds;
+    acc.huge_v += huge ? (unsigned long long)a.max_rounds : 0ull;
+    const unsigned long long e = (unsigned long long)deg * (unsigned long long)a.max_rounds;
+    acc.edges_lb += huge ? e : 0ull;
+    acc.edges_twc += huge ? 0ull : e;
+    const int32_t od = a.off[v + 1] - a.off[v];
+    st_relaxed(&a.contrib[v], od > 0 ? r0 / (float)od : 0.0f);
+    if (od == 0) dangling += to_fix(r0);
+    st_relaxed(&a.acc[v], 0ull);
+  }
+  flush(0);
+  lay_out_tiles(a, sm, m, t0, t1);
+  for (uint32_t i = tid; i <= kTileItems; i += B) sm.acc[i] = 0;
+  // the row open at this workgroup's start has edges in earlier workgroups
+  const uint32_t first = t0 < t1 ? a.tile_row[t0] : n;
+  const bool shared_first = first < n && (uint64_t)(uint32_t)a.toff[first] + first < (uint64_t)t0 * kTileItems;
+  bool ok = grid_barrier<false>(a, sm, gr, epoch, 0);
+  if (gr.id == 0 && tid == 0) st_relaxed(&a.ctl->t_rounds, (unsigned long long)wall_clock64());
+
+  const double d = (double)a.damping, N = (double)a.n;
+  int it = 0;
+  for (; ok && it < a.max_rounds; ++it) {
+    if (gr.id == 0 && tid < (uint32_t)kStatXcds) st_relaxed(&a.ctl->tile_dangling[(it + 2) % 3][tid].v, 0ull);
+    unsigned long long mass = 0;
+#pragma unroll
+    for (int x = 0; x < kStatXcds; ++x) mass += ld_relaxed(&a.ctl->tile_dangling[it % 3][x].v);
+    const double base = (1.0 - d) / N + d * ((double)mass * kFixInv) / N;
+    const float *cin = it & 1 ? a.contrib2 : a.contrib;
+    float *cout = it & 1 ? a.contrib : a.contrib2;
+    const bool last = it + 1 == a.max_rounds;
+    auto update = [&](uint32_t v, unsigned long long sum) {
+      const float r = (float)(base + d * ((double)sum * kFixInv));
+      if (last) a.rank[v] = r;
+      const int32_t od = a.off[v + 1] - a.off[v];
+      st_relaxed(&cout[v], od > 0 ? r / (float)od : 0.0f);
+      if (od == 0) dangling += to_fix(r);
+    };
+    bool deferred = false;  // thread 0: the shared first row ends in this workgroup
+    unsigned long long carry = 0;  // thread 0: sum of the open row
+    uint32_t open = first;
+    for (uint32_t t = t0; t < t1; ++t) {
+      const Tile tl = tile_at(a, items, t);
+      const int32_t *col = a.tcol + tl.edge;
+      const uint16_t *lrow = a.tile_lrow + tl.edge;
+      for (uint32_t i0 = tid; i0 < tl.edges; i0 += kTileLoads * B) {
+        int32_t u[kTileLoads];
+        uint32_t l[kTileLoads];
+        float c[kTileLoads];
+#pragma unroll
+        for (int k = 0; k < kTileLoads; ++k) {
+          const uint32_t i = i0 + k * B;
+          u[k] = i < tl.edges ? col[i] : -1;
+          l[k] = i < tl.edges ? lrow[i] : 0u;
+        }
+#pragma unroll
+        for (int k = 0; k < kTileLoads; ++k) c[k] = u[k] >= 0 ? ld_relaxed(&cin[u[k]]) : 0.0f;
+#pragma unroll
+        for (int k = 0; k < kTileLoads; ++k)
+          if (u[k] >= 0) atomicAdd(&sm.acc[l[k]], to_fix(c[k]));
+      }
+      __syncthreads();
+      for (uint32_t l = tid; l < tl.rows; l += B) {
+        unsigned long long sum = sm.acc[l];
+        sm.acc[l] = 0;
+        if (l == 0) {  // thread 0: the row open before this tile
+          sum += carry;
+          carry = 0;
+          if (tl.row == first && shared_first) {
+            sm.defer = sum;
+            deferred = true;
+            continue;
+          }
+        }
+        update(tl.row + l, sum);
+      }
+      if (tid == 0) {
+        carry += sm.acc[tl.rows];
+        sm.acc[tl.rows] = 0;
+        open = tl.row + tl.rows;
+      }
+      __syncthreads();
+    }
+    if (tid == 0 && carry) add_relaxed(&a.acc[open], carry);  // the rest of the open row is a later workgroup's
+    flush(it + 1);
+    ok = grid_barrier<false>(a, sm, gr, epoch, it);
+    if (!ok) break;
+    if (tid == 0 && deferred) {
+      const unsigned long long sum = sm.defer + ld_relaxed(&a.acc[first]);
+      st_relaxed(&a.acc[first], 0ull);
+      update(first, sum);
+      if (dangling) add_relaxed(&a.ctl->tile_dangling[(it + 1) % 3][stripe].v, dangling);
+      dangling = 0;
+    }
+    ok = grid_barrier<false>(a, sm, gr, epoch, it);
+  }
+  if (gr.id == 0 && tid == 0) {
+    st_relaxed(&a.ctl->rounds, (uint32_t)it);
+    st_relaxed(&a.ctl->threshold_used, (long long)a.threshold);
+  }
+  // statistics: the workgroups' sums
+  unsigned long long v[kStats] = {acc.frontier, acc.edges_twc, acc.edges_lb, acc.huge_v, 0ull};
+#pragma unroll
+  for (int k = 0; k < kStats; ++k) {
+#pragma unroll
+    for (int x = kWave / 2; x > 0; x >>= 1) v[k] += __shfl_xor(v[k], x);
+    if (lane_id() == 0 && v[k]) add_relaxed(&a.ctl->stat[stripe][k].v, v[k]);
+  }
+  leave(a, sm, gr);
+}
+
+// ---------------------------------------------------------------------------
 // Dispatch over workgroup size and operator.
 // ---------------------------------------------------------------------------
 
@@ -2385,6 +2820,24 @@ hipError_t pull_occupancy(int wg, int *blocks_per_cu) {
       return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, (const void *)k_pull_pr<1024>, 1024, 0);
   }
   return hipErrorInvalidValue;
+}
+
+hipError_t launch_pr_tiles(int grid, const Args &a, hipStream_t s) {
+  hipLaunchKernelGGL(k_pr_tiles<kTileWg>, dim3(grid), dim3(kTileWg), 0, s, a);
+  return hipGetLastError();
+}
+hipError_t pr_tiles_occupancy(int *blocks_per_cu) {
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, (const void *)k_pr_tiles<kTileWg>, kTileWg, 0);
+}
+
+hipError_t launch_transpose(const Transpose &t, hipStream_t s) {
+  const size_t bin_bytes = sizeof(uint32_t) * t.bins;
+  hipLaunchKernelGGL(k_tr_zero, dim3(8), dim3(kTrWg), 0, s, t);
+  hipLaunchKernelGGL(k_tr_count, dim3(kTransposeWgs), dim3(kTrWg), bin_bytes, s, t);
+  hipLaunchKernelGGL(k_tr_start, dim3(1), dim3(kTrSortWg), 0, s, t);
+  hipLaunchKernelGGL(k_tr_scatter, dim3(kTransposeWgs), dim3(kTrWg), bin_bytes, s, t);
+  hipLaunchKernelGGL(k_tr_sort, dim3(t.bins), dim3(kTrSortWg), sizeof(uint32_t) << t.bits, s, t);
+  return hipGetLastError();
 }
 
 hipError_t launch_init_open(const Args &a, hipStream_t s) {
