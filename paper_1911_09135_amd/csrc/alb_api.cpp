@@ -566,13 +566,13 @@ alb_status resident_workgroups(alb_graph g, OpKind op, int wg, int *out, bool ba
   return ALB_OK;
 }
 
-// Worklist entries whose edges fill one pass of a workgroup of wg threads at
-// the mean degree, as a power of two of whole wavefronts, at most wg.
-uint32_t run_fill(int wg, int64_t vertices, int64_t edges) {
+// log2 of the worklist entries whose edges fill one pass of a workgroup of wg
+// threads at the mean degree: at least a wavefront's worth of entries, at most wg.
+uint32_t fill_log(int wg, int64_t vertices, int64_t edges) {
   const int64_t mean = std::max<int64_t>(1, edges / std::max<int64_t>(vertices, 1));
-  int64_t f = 64;
-  while (2 * f <= std::min<int64_t>((int64_t)kEdgesPerLanePass * wg / mean, wg)) f *= 2;
-  return (uint32_t)f;
+  uint32_t f = 6;
+  while ((int64_t)2 << f <= std::min<int64_t>((int64_t)kEdgesPerLanePass * wg / mean, wg)) ++f;
+  return f;
 }
 
 struct Job {
@@ -816,7 +816,7 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
   a.ctl = ws->ctl;
   a.source = job.source;
   a.nfront0 = job.nfront0;
-  a.run_fill = run_fill(wg, g->n, g->m);
+  a.fill_log = fill_log(wg, g->n, g->m);
   a.threshold = threshold;
   a.c_wave = o.wave_cutoff;
   a.c_wg = o.wg_cutoff;
@@ -1193,7 +1193,7 @@ alb_status prepare_batch(alb_graph g, OpKind op, int32_t count, const int32_t *m
   a.n = g->n;
   a.qcap = (uint32_t)qcap;
   a.threshold = j.threshold;
-  a.run_fill = run_fill(wg, labels, edges);
+  a.fill_log = fill_log(wg, labels, edges);
   a.c_wave = o.wave_cutoff;
   a.c_wg = o.wg_cutoff;
   a.dedup = dedup ? 1 : 0;
@@ -2634,7 +2634,7 @@ alb_status open_lane_start(OpenLane *L, hipStream_t s, double idle_us, int64_t e
   a.bar = L->bar;
   a.ctl = L->ctl;
   a.threshold = L->threshold;
-  a.run_fill = run_fill(L->wg, g->n, g->m);
+  a.fill_log = fill_log(L->wg, g->n, g->m);
   a.c_wave = o.wave_cutoff;
   a.c_wg = o.wg_cutoff;
   a.blocked = o.distribution == 1;

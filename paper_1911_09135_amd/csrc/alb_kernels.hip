@@ -802,26 +802,8 @@ __device__ __forceinline__ void block_exscan(int32_t x, int32_t &excl, int32_t &
 // claims per workgroup, so that a short worklist still reaches every
 // workgroup instead of leaving most of them idle for the phase.
 __device__ __forceinline__ uint32_t twc_chunk(uint32_t nF, uint32_t wgs, int B) {
-  const uint64_t per = ((uint64_t)nF + 2ull * wgs - 1) / (2ull * wgs);
-  uint64_t c = (per + kWave - 1) / kWave * kWave;
-  if (c < (uint64_t)kWave) c = kWave;
-  if (c > (uint64_t)B) c = B;
-  return (uint32_t)c;
-}
-
-// The fixed first run's length.  A worklist that fits in one run of `fill`
-// entries per workgroup (the entries whose edges, at the graph's mean degree,
-// fill one pass of the workgroup) is split over as many workgroups as it
-// fills, and over 96 if it fills fewer: a run's time is a chain of dependent
-// loads, about the same for 2 entries as for one full pass, while every
-// pass beyond the first and every long list in the same run adds to it (RMAT-14
-// BFS: 2,498 entries in runs of 64 took 18.8 us, in runs of 27 14.7); but each
-// workgroup with pushes also costs its 12 ns at the worklist counter, so a
-// low-degree graph's runs are long (a grid of mean degree 4: 256 entries).
-__device__ __forceinline__ uint32_t first_run(uint32_t nF, uint32_t wgs, int B, uint32_t fill) {
-  if ((uint64_t)nF > (uint64_t)fill * wgs) return twc_chunk(nF, wgs, B);
-  const uint32_t used = max((nF + fill - 1) / fill, min(wgs, 96u));
-  return max(1u, (nF + used - 1) / used);
+  const uint32_t per = nF / (2u * wgs) + 1u;
+  return min(max((per + kWave - 1u) / kWave * kWave, (uint32_t)kWave), (uint32_t)B);
 }
 
 // Workgroups take runs of consecutive worklist entries one at a time, so a
@@ -839,8 +821,8 @@ struct Claims {
   uint32_t C0, len;
   unsigned long long S, nxt, seen;
   bool first;
-  __device__ Claims(uint32_t nF, Grid gr, int B, uint32_t fill)
-      : C0(first_run(nF, gr.n, B, fill)), len(C0), S((unsigned long long)gr.n * C0),
+  __device__ Claims(Grid gr, uint32_t run)
+      : C0(run), len(C0), S((unsigned long long)gr.n * C0),
         nxt((unsigned long long)gr.id * C0), seen(S), first(true) {}
   // Publish the next run as (*base, *n); *base >= nF means no more work.
   __device__ void next(unsigned long long *claim, uint32_t nF, Grid gr, int B, unsigned long long &base,
@@ -861,6 +843,62 @@ struct Claims {
 };
 
 
+// The order in which a phase's runs take the worklist's entries.  Neighbouring
+// entries have alike degrees (the hubs of an RMAT graph sit at its lowest ids,
+// and lists push their destinations in ascending order), so runs of consecutive
+// entries differ by far more than one run should (RMAT-20 CC, round 0: the
+// busiest workgroup had 4.8 times the mean edges, half of all workgroup time
+// went by at barriers).  Runs therefore take entries from all over the
+// list, in groups of kGroup from 256 / kGroup places, or singly where one run
+// per workgroup covers it.  Except there on low-degree graphs (fill_log above
+// 6): they have little skew, and neighbours in the list share the lines of their
+// edges and labels (1,001 x 777 grid SSSP: 12.6 ms consecutive, 15.2 spread).
+// The recorded round of alb_trace_round keeps consecutive runs of whole
+// wavefronts' entries, so that its record shows the claims.
+// Groups of 16, 4 and 1 (us): RMAT-20 CC 1,105, 1,050, 1,012; 64-query batch
+// 2,542, 2,484, 2,485; Zipf 8.4M BFS 1,815, 1,829, 1,868.
+constexpr uint32_t kGroup = 4, kPlaces = 256 / kGroup;
+//
+// The first run's length: a worklist that fits in one run of 2^fill_log entries
+// per workgroup (the entries whose edges, at the graph's mean degree, fill one
+// pass of the workgroup) is split over as many workgroups as it fills, and
+// over 96 if it fills fewer.  A run's time is a chain of dependent loads, about
+// the same for 2 entries as for one full pass, while every pass beyond the
+// first and every long list in the same run adds to it (RMAT-14 BFS: 2,498
+// entries in runs of 64 took 18.8 us, in runs of 27 14.7); but each workgroup
+// with pushes also costs its 12 ns at the worklist counter, so a low-degree
+// graph's runs are long (a grid of mean degree 4: 256 entries).
+struct Order {
+  uint32_t run;    // length of the first run
+  uint32_t total;  // positions, a few of them beyond the list
+  uint32_t used;   // single entries: from one to the next; 0: groups or consecutive
+  uint32_t step;   // groups: from one place to the next; 0: consecutive
+  __device__ Order(uint32_t nF, uint32_t wgs, int B, uint32_t fill_log, bool consecutive) {
+    used = step = 0;
+    total = nF;
+    if ((uint64_t)nF <= (uint64_t)wgs << fill_log && !consecutive) {
+      const uint32_t w = max((nF + (1u << fill_log) - 1u) >> fill_log, min(wgs, 96u));
+      run = (nF + w - 1u) / w;
+      if (fill_log <= 6) {
+        used = w;
+        total = w * run;
+      }
+    } else {
+      run = twc_chunk(nF, wgs, B);
+      if (!consecutive) {
+        step = (uint32_t)(((uint64_t)nF + 255) / 256);
+        total = step * 256u;
+      }
+    }
+  }
+  // entry of position base + j of workgroup id's run (may lie beyond the list)
+  __device__ uint32_t entry(uint32_t base, uint32_t j, uint32_t id) const {
+    if (used) return j * used + id;
+    const uint32_t p = base + j;
+    return step ? ((p / kGroup % kPlaces) * step + p / 256u) * kGroup + p % kGroup : p;
+  }
+};
+
 template <int B, class Op, bool M, class S>
 __device__ void phase_twc(const Args &a, const Op &op, S &sm, Grid gr, int round,
                           const Entry<M> *F, uint32_t nF, Entry<M> *qn, uint32_t *qn_cnt, unsigned long long *hctr,
@@ -873,15 +911,16 @@ __device__ void phase_twc(const Args &a, const Op &op, S &sm, Grid gr, int round
   unsigned long long *claim = &a.ctl->chunk[round % 3].v;
   Pusher<Entry<M>> pu{sm.pbuf[tid / kWave], 0u, qn, qn_cnt};
   uint64_t pt = a.profile ? (uint64_t)wall_clock64() : 0;
-  Claims cl(nF, gr, B, a.run_fill);
+  const Order order(nF, gr.n, B, a.fill_log, Op::kRecord);
+  Claims cl(gr, order.run);
   for (;;) {
-    if (tid == 0) cl.next(claim, nF, gr, B, sm.cbase, sm.clen);
+    if (tid == 0) cl.next(claim, order.total, gr, B, sm.cbase, sm.clen);
     __syncthreads();
     const unsigned long long base = sm.cbase;
     const uint32_t C = sm.clen;
-    if (base >= nF) break;
-    const uint32_t i = (uint32_t)base + tid;
-    const bool mine = tid < (int)C && i < nF;
+    if (base >= order.total) break;
+    const uint32_t i = order.entry((uint32_t)base, (uint32_t)tid, gr.id);
+    const bool mine = tid < (int)C && base + (uint32_t)tid < order.total && i < nF;
     int32_t v = -1, beg = 0, deg = 0, q = 0;  // q: the entry's query (batch)
     int64_t thr = threshold;
     int32_t c_wave = a.c_wave, c_wg = a.c_wg;  // TWC cutoffs (a batch's queries may have their own)
@@ -2017,7 +2056,7 @@ __device__ void pull_gather(const Args &a, Smem<B, OpPRPull> &sm, Grid gr, int i
   const int tid = threadIdx.x;
   const uint32_t lane = lane_id();
   const uint32_t nF = (uint32_t)a.n;
-  Claims cl(nF, gr, B, a.run_fill);
+  Claims cl(gr, twc_chunk(nF, gr.n, B));
   for (;;) {
     if (tid == 0) cl.next(&a.ctl->chunk[it % 3].v, nF, gr, B, sm.cbase, sm.clen);
     __syncthreads();
