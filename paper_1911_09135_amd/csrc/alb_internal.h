@@ -34,7 +34,8 @@ constexpr int kBarXcdMembers = kBarXcdArrive + kBarXcds * kBarStride;
 // Leaving the launch: the same two levels of counters, with nobody waiting.
 constexpr int kBarXcdOut = kBarXcdMembers + kBarXcds * kBarStride;
 constexpr int kBarRootOut = kBarXcdOut + kBarXcds * kBarStride;
-constexpr size_t kBarWords = (size_t)kBarRootOut + kBarStride;
+constexpr int kBarFlat = kBarRootOut + kBarStride;  // all members' arrivals, where they are few
+constexpr size_t kBarWords = (size_t)kBarFlat + kBarStride;
 
 // Huge-worklist chunk index: edge index k of the round's huge edges lies in
 // chunk k >> hint_shift; hint[c] holds the huge-list slot that owns the first

@@ -46,6 +46,18 @@ constexpr uint32_t kPushBytes = 4096;
 __device__ __forceinline__ uint32_t lane_id() {
   return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
 }
+// Inclusive sum over the wavefront's lanes (all of them active), with lane
+// moves inside the vector unit: a shuffle goes through LDS, 64 cycles or more
+// each, and six of them in a row were a tenth of a short round's phase.
+__device__ __forceinline__ uint32_t wave_inclusive(uint32_t x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1, 2, 4, 8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+  return x;
+}
 // number of set bits of m below this lane
 __device__ __forceinline__ uint32_t bits_below(unsigned long long m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
@@ -495,6 +507,7 @@ struct Smem {
   int32_t wsum[B / kWave];
   unsigned long long ured[B / kWave][kStats];
   unsigned long long dred[B / kWave];
+  int32_t wcand[B / kWave];  // workgroup bin: a thread of each wavefront that holds a list for it, or -1
   int32_t owner, obeg, odeg, ov;
   V osv;
   int32_t flag;
@@ -662,10 +675,14 @@ __device__ __forceinline__ void reserve_huge(bool huge, int32_t v_or_q, int32_t 
   const uint32_t lane = lane_id();
   const unsigned long long mine = huge ? (unsigned long long)(uint32_t)deg : 0ull;
   unsigned long long incl = mine;
+  if (__ballot(mine >> 25) == 0ull) {  // the 64 lanes' sum fits in 32 bits
+    incl = wave_inclusive((uint32_t)mine);
+  } else {
 #pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    const unsigned long long y = __shfl_up(incl, d);
-    if ((int)lane >= d) incl += y;
+    for (int d = 1; d < kWave; d <<= 1) {
+      const unsigned long long y = __shfl_up(incl, d);
+      if ((int)lane >= d) incl += y;
+    }
   }
   const unsigned long long tot_e = __shfl(incl, kWave - 1);
   const uint32_t tot_c = (uint32_t)__popcll(hm);
@@ -762,16 +779,13 @@ __device__ __forceinline__ void edges(const bool (&act)[kU], const int32_t (&pos
   }
 }
 
+// Exclusive sum over the workgroup.  A workgroup barrier separates it from the
+// next use of wsum.
 template <int B>
 __device__ __forceinline__ void block_exscan(int32_t x, int32_t &excl, int32_t &total, int32_t *wsum) {
   const uint32_t lane = lane_id();
   const int w = threadIdx.x / kWave;
-  int32_t incl = x;
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    const int32_t y = __shfl_up(incl, d);
-    if ((int)lane >= d) incl += y;
-  }
+  const int32_t incl = (int32_t)wave_inclusive((uint32_t)x);
   if (lane == kWave - 1) wsum[w] = incl;
   __syncthreads();
   int32_t before = 0, tot = 0;
@@ -783,7 +797,6 @@ __device__ __forceinline__ void block_exscan(int32_t x, int32_t &excl, int32_t &
   }
   excl = before + incl - x;
   total = tot;
-  __syncthreads();
 }
 
 // Waves per SIMD the persistent kernel's register budget is sized for: the
@@ -819,24 +832,19 @@ __device__ __forceinline__ uint32_t twc_chunk(uint32_t nF, uint32_t wgs, int B) 
 // claim's reads of the published run from the next claim's writes.
 struct Claims {
   uint32_t C0, len;
-  unsigned long long S, nxt, seen;
-  bool first;
+  unsigned long long S, nxt, seen;  // end of the fixed runs; the current run (at first the fixed one)
   __device__ Claims(Grid gr, uint32_t run)
-      : C0(run), len(C0), S((unsigned long long)gr.n * C0),
-        nxt((unsigned long long)gr.id * C0), seen(S), first(true) {}
+      : C0(run), len(C0), S((unsigned long long)gr.n * C0), nxt((unsigned long long)gr.id * C0), seen(S) {}
   // Publish the next run as (*base, *n); *base >= nF means no more work.
   __device__ void next(unsigned long long *claim, uint32_t nF, Grid gr, int B, unsigned long long &base,
                        uint32_t &n) {
-    if (!first) {
-      if (S >= (unsigned long long)nF) {
-        nxt = ~0ull;  // the fixed runs covered the worklist
-      } else {
-        len = twc_chunk(seen < nF ? nF - (uint32_t)seen : 0u, gr.n, B);
-        nxt = S + add_relaxed(claim, (unsigned long long)len);
-        seen = nxt + len;
-      }
+    if (S >= (unsigned long long)nF) {
+      nxt = ~0ull;  // the fixed runs covered the worklist
+    } else {
+      len = twc_chunk(seen < nF ? nF - (uint32_t)seen : 0u, gr.n, B);
+      nxt = S + add_relaxed(claim, (unsigned long long)len);
+      seen = nxt + len;
     }
-    first = false;
     base = nxt;
     n = len;
   }
@@ -923,12 +931,9 @@ __device__ void phase_twc(const Args &a, const Op &op, S &sm, Grid gr, int round
   uint64_t pt = a.profile ? (uint64_t)wall_clock64() : 0;
   const Order order(nF, gr.n, B, a.fill_log, Op::kRecord);
   Claims cl(gr, order.run);
-  for (;;) {
-    if (tid == 0) cl.next(claim, order.total, gr, B, sm.cbase, sm.clen);
-    __syncthreads();
-    const unsigned long long base = sm.cbase;
-    const uint32_t C = sm.clen;
-    if (base >= order.total) break;
+  unsigned long long base = cl.nxt;
+  uint32_t C = cl.len;
+  for (bool more = base < order.total; more;) {
     const uint32_t i = order.entry((uint32_t)base, (uint32_t)tid, gr.id, F == nullptr);
     const bool mine = tid < (int)C && base + (uint32_t)tid < order.total && i < nF;
     int32_t v = -1, beg = 0, deg = 0, q = 0;  // q: the entry's query (batch)
@@ -987,11 +992,12 @@ __device__ void phase_twc(const Args &a, const Op &op, S &sm, Grid gr, int round
 
     // workgroup bin: the whole workgroup strides one vertex's edges
     for (;;) {
-      if (tid == 0) sm.owner = -1;
+      const unsigned long long cand = __ballot(deg > 0 && deg >= c_wg);
+      if (lane == 0) sm.wcand[tid / kWave] = cand ? tid + __ffsll(cand) - 1 : -1;
       __syncthreads();
-      if (deg > 0 && deg >= c_wg) sm.owner = tid;  // any one claimant wins
-      __syncthreads();
-      const int32_t o = sm.owner;
+      int32_t o = -1;
+#pragma unroll
+      for (int w = 0; w < B / kWave; ++w) o = max(o, sm.wcand[w]);
       if (o < 0) break;
       if (tid == o) {
         sm.obeg = beg;
@@ -1074,6 +1080,14 @@ __device__ void phase_twc(const Args &a, const Op &op, S &sm, Grid gr, int round
       __syncthreads();
     }
     prof_mark(a, acc, kProfThreadBin, pt);
+    more = cl.S < (unsigned long long)order.total;  // else the fixed runs covered the worklist
+    if (more) {
+      if (tid == 0) cl.next(claim, order.total, gr, B, sm.cbase, sm.clen);
+      __syncthreads();
+      base = sm.cbase;
+      C = sm.clen;
+      more = base < order.total;
+    }
   }
   settle_hot<B>(a, op, round, pu, acc);
   if constexpr (Op::kPush) flush_phase<B>(a, sm, round, pu);
@@ -1244,8 +1258,12 @@ __device__ bool grid_barrier(const Args &a, S &sm, Grid gr, unsigned long long &
   if (threadIdx.x == 0) {
     unsigned long long *b = a.bar;
     const unsigned long long target = epoch + 1;
-    const unsigned long long o1 = add_relaxed(&b[kBarXcdArrive + (size_t)kBarStride * gr.xcd], 1ull);
-    if ((o1 + 1) % gr.xcd_n == 0) {
+    // few members (and no release to share) arrive on one counter directly
+    // (its own: a launch may use both kinds of barrier): 32 of them meet in 1.6 us so, in 2.1 by way of the XCDs' counters,
+    // 64 in 2.0 and 2.2, 128 in 2.8 and 2.3
+    if (!kFull && gr.n <= 48) {
+      if ((add_relaxed(&b[kBarFlat], 1ull) + 1) % gr.n == 0) st_relaxed(&b[kBarGen], target);
+    } else if ((add_relaxed(&b[kBarXcdArrive + (size_t)kBarStride * gr.xcd], 1ull) + 1) % gr.xcd_n == 0) {
       // the XCD's last arrival releases every store its members made before
       // arriving; `sys`: to the host as well (stores into host memory)
       if constexpr (kFull) {
@@ -1660,11 +1678,12 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
   bool filtered = false;  // the filter bitmap is in use
   int r = 0;
   for (; ok && r < a.max_rounds; ++r) {
-    if (ld_relaxed(&a.ctl->overflow) < (uint32_t)r) {  // set in an earlier round: seen by all alike
+    const uint32_t over = ld_relaxed(&a.ctl->overflow);  // (both loads in flight together)
+    const uint32_t nF = round_size(a, r);
+    if (over < (uint32_t)r) {  // set in an earlier round: seen by all alike
       ok = false;
       break;
     }
-    const uint32_t nF = round_size(a, r);
     if (nF == 0) break;
     if constexpr (F) {
       // BFS: once half of the vertices have been reached (every member
@@ -2067,11 +2086,11 @@ __device__ void pull_gather(const Args &a, Smem<B, OpPRPull> &sm, Grid gr, int i
   const uint32_t lane = lane_id();
   const uint32_t nF = (uint32_t)a.n;
   Claims cl(gr, twc_chunk(nF, gr.n, B));
-  for (;;) {
-    if (tid == 0) cl.next(&a.ctl->chunk[it % 3].v, nF, gr, B, sm.cbase, sm.clen);
+  for (bool first = true;; first = false) {
+    if (!first && tid == 0) cl.next(&a.ctl->chunk[it % 3].v, nF, gr, B, sm.cbase, sm.clen);
     __syncthreads();
-    const unsigned long long base = sm.cbase;
-    const uint32_t C = sm.clen;
+    const unsigned long long base = first ? cl.nxt : sm.cbase;
+    const uint32_t C = first ? cl.len : sm.clen;
     if (base >= nF) break;
     const uint32_t i = (uint32_t)base + tid;
     const bool mine = tid < (int)C && i < nF;
