@@ -68,7 +68,8 @@ struct Workspace {
   void *tiles = nullptr;  // PageRank in tiles: its layout (made when first needed)
   size_t tiles_bytes = 0;
   Ctl *h_ctl = nullptr;  // pinned host mirror (host loop, profiling)
-  Result *h_res = nullptr;  // pinned, behind it: a persistent launch's result
+  Result *h_res = nullptr;  // pinned, behind it: a persistent launch's result ...
+  void *h_stage = nullptr;  // ... and room for one small host output, or null
   hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
   size_t bytes = 0;
 
@@ -310,6 +311,22 @@ hipError_t palloc(T **p, size_t bytes) {
   return hipHostMalloc((void **)p, bytes, hipHostMallocDefault);
 }
 
+// The device address of pinned host memory (hipHostMalloc'd or registered
+// with the runtime), or null for any other pointer.
+void *pinned_device_address(const void *p) {
+  if (!p) return nullptr;
+  hipPointerAttribute_t at;
+  std::memset(&at, 0, sizeof at);
+  const hipError_t e = hipPointerGetAttributes(&at, p);
+  (void)hipGetLastError();  // an unregistered pointer leaves no error behind for the next caller
+  if (e != hipSuccess || at.type != hipMemoryTypeHost || at.hostPointer != p) return nullptr;
+  return at.devicePointer;
+}
+
+// Vertices up to which a query's pageable host output is staged in pinned
+// memory that the launch writes (256 KB).
+constexpr int32_t kStageVertices = 1 << 16;
+
 alb_status ws_fill(Workspace *w, int32_t n, const Needs &nd) {
   w->n = n;
   w->qcap = nd.qcap;
@@ -324,8 +341,10 @@ alb_status ws_fill(Workspace *w, int32_t n, const Needs &nd) {
   HIP_TRY(dalloc(&w->rank, (size_t)n, w->bytes));
   HIP_TRY(dalloc(&w->acc, (size_t)n, w->bytes));
   HIP_TRY(dalloc(&w->ctl, 2, w->bytes));
-  HIP_TRY(palloc(&w->h_ctl, sizeof(Ctl) + sizeof(Result)));
+  const size_t stage = n <= kStageVertices ? sizeof(int32_t) * (size_t)n : 0;
+  HIP_TRY(palloc(&w->h_ctl, sizeof(Ctl) + sizeof(Result) + stage));
   w->h_res = (Result *)(w->h_ctl + 1);
+  w->h_stage = stage ? w->h_res + 1 : nullptr;
   for (auto &e : w->ev) HIP_TRY(hipEventCreate(&e));
   return ALB_OK;
 }
@@ -590,6 +609,16 @@ struct Job {
   uint32_t qcap_min = 0;
 };
 
+// A host output of n 4-byte results.  Where it is pinned memory, or small
+// enough to be staged there, the persistent launch writes it (RMAT-14 BFS: a
+// copy of 64 KB into pageable memory and its wait took 15 us of a call);
+// else (`done` stays false) the caller copies it from the device.
+struct HostOut {
+  void *ptr;
+  size_t bytes;
+  bool done;
+};
+
 struct RunOut {
   Workspace *ws = nullptr;
   uint32_t qcap = 0;
@@ -742,7 +771,7 @@ Needs job_needs(alb_graph g, const Job &job, const alb_options &o, bool *dedup_o
 // no workspace is taken from the pool, no event is recorded and nothing is
 // allocated; its h_ctl may be pageable host memory.
 alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_out, alb_stats *st, WsGuard &guard,
-                   RunOut &ro, Workspace *fixed = nullptr) {
+                   RunOut &ro, Workspace *fixed = nullptr, HostOut *ho = nullptr) {
   HIP_TRY(hipSetDevice(g->device));
   const hipStream_t stream = o.stream ? (hipStream_t)o.stream : g->stream;
   ro.stream = stream;
@@ -949,6 +978,19 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
     a.prof_wg = prof.p;
   }
   if (launch == ALB_LAUNCH_PERSISTENT && job.max_rounds > 0) {
+    bool staged = false;
+    if (ho && job.op != OP_RECORD && ((job.op != OP_PR && job.op != OP_PR_PULL) || pr_grid)) {
+      void *dst = pinned_device_address(ho->ptr);
+      if (!dst && ws->h_stage) {
+        dst = ws->h_stage;
+        staged = true;
+      }
+      if (dst && (job.op == OP_PR || job.op == OP_PR_PULL))
+        a.rank = (float *)dst;
+      else if (dst)
+        a.out = (int32_t *)dst;
+      ho->done = dst != nullptr;
+    }
     // one launch does everything, from the labels' initialisation to the
     // outputs, and writes its result block into pinned memory
     if (!fixed) {
@@ -993,6 +1035,7 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
     }
     if (!job.all_rounds && job.max_rounds > 1 && (int)res.rounds >= job.max_rounds && res.left != 0)
       return fail(ALB_E_DEVICE, "no convergence within %d rounds", job.max_rounds);
+    if (staged) std::memcpy(ho->ptr, ws->h_stage, ho->bytes);
     if (st)
       fill_stats(st, res.stat, (int)res.rounds, 1, T, res.threshold_used,
                  fixed ? 0.0 : ticks_ms(g, res.t_begin, res.t_end),
@@ -1063,9 +1106,10 @@ alb_status traverse(alb_graph g, const Job &job, void *out, size_t elem, const a
   if (s != ALB_OK) return s;
   WsGuard guard{nullptr, nullptr};
   RunOut ro;
-  s = run_job(g, job, o, o.out_on_device ? out : nullptr, st, guard, ro);
+  HostOut ho{out, elem * (size_t)g->n, false};
+  s = run_job(g, job, o, o.out_on_device ? out : nullptr, st, guard, ro, nullptr, o.out_on_device ? nullptr : &ho);
   if (s != ALB_OK) return s;
-  if (!o.out_on_device) {
+  if (!o.out_on_device && !ho.done) {
     const void *src = (job.op == OP_PR || job.op == OP_PR_PULL) ? (const void *)ro.d_rank : (const void *)ro.d_labels;
     HIP_TRY(hipMemcpyAsync(out, src, elem * (size_t)g->n, hipMemcpyDeviceToHost, ro.stream));
     HIP_TRY(hipStreamSynchronize(ro.stream));
@@ -1085,6 +1129,7 @@ struct BatchJob {
   std::vector<long long> qoff, qthr, qlbase;
   std::vector<int32_t> qsrc, qn;
   std::vector<int32_t *> qout;  // filled once the workspace is known
+  std::vector<char> qdirect;    // host outputs: the launch writes query q's itself (pinned memory)
   std::vector<int32_t> qcut;    // per query: wavefront and workgroup bin cutoffs
   bool per_query_thr = false, per_query_cut = false;
   long long labels = 0, edges = 0, thr_min = 0;
@@ -1242,11 +1287,14 @@ alb_status upload_batch(BatchJob &j, BatchWs *ws) {
   long long *d_off = (long long *)ws->tab, *h_off = (long long *)ws->h_tab;
   int32_t **d_out = (int32_t **)(d_off + 3 * c), **h_out = (int32_t **)(h_off + 3 * c);
   int32_t *d_i32 = (int32_t *)(d_out + c), *h_i32 = (int32_t *)(h_out + c);
+  j.qdirect.assign(c, 0);
   for (size_t q = 0; q < c; ++q) {
+    int32_t *dst = j.o.out_on_device ? j.qout[q] : (int32_t *)pinned_device_address(j.qout[q]);
+    j.qdirect[q] = dst != nullptr;
+    h_out[q] = dst ? dst : ws->out32 + j.qlbase[q];
     h_off[q] = j.qoff[q];
     h_off[c + q] = j.qthr[q];
     h_off[2 * c + q] = j.qlbase[q];
-    h_out[q] = j.o.out_on_device ? j.qout[q] : ws->out32 + j.qlbase[q];
     h_i32[q] = j.qsrc[q];
     h_i32[c + q] = j.qn[q];
     h_i32[2 * c + 2 * q] = j.per_query_cut ? j.qcut[2 * q] : j.o.wave_cutoff;
@@ -1306,11 +1354,15 @@ alb_status finish_batch(alb_graph g, const BatchJob &j, BatchWs *ws, int32_t *co
   }
   if (rounds >= j.a.max_rounds && c.left != 0)
     return fail(ALB_E_DEVICE, "no convergence within %d rounds", j.a.max_rounds);
-  if (!j.o.out_on_device) {  // straight from the staging area into each query's host array
-    for (int32_t q = 0; q < j.count; ++q)
+  if (!j.o.out_on_device) {  // straight from the staging area into each query's pageable host array
+    bool copied = false;
+    for (int32_t q = 0; q < j.count; ++q) {
+      if (j.qdirect[q]) continue;
+      copied = true;
       HIP_TRY(hipMemcpyAsync(outs[q], ws->out32 + j.qlbase[q], sizeof(int32_t) * (size_t)j.qn[q],
                              hipMemcpyDeviceToHost, j.stream));
-    HIP_TRY(hipStreamSynchronize(j.stream));
+    }
+    if (copied) HIP_TRY(hipStreamSynchronize(j.stream));
   }
   if (st)
     fill_stats(st, c.stat, rounds, 1, (int64_t)c.n_members * j.o.wg_size,
@@ -2678,18 +2730,6 @@ uint64_t open_lane_backlog(OpenLane *L) {
 }
 
 // Publish one request into `slot`, its labels at [lbase, lbase + n).
-// The device address of pinned host memory (hipHostMalloc'd or registered
-// with the runtime), or 0 for any other pointer.
-static unsigned long long pinned_device_address(const void *p) {
-  if (!p) return 0;
-  hipPointerAttribute_t at;
-  std::memset(&at, 0, sizeof at);
-  const hipError_t e = hipPointerGetAttributes(&at, p);
-  (void)hipGetLastError();  // an unregistered pointer leaves no error behind for the next caller
-  if (e != hipSuccess || at.type != hipMemoryTypeHost || !at.devicePointer) return 0;
-  return (unsigned long long)(uintptr_t)at.devicePointer;
-}
-
 alb_status open_lane_publish(OpenLane *L, int32_t algo, int32_t slot, int32_t member, int32_t source,
                              long long lbase, int32_t *host_out, bool *direct) {
   alb_graph g = L->g;
@@ -2698,7 +2738,7 @@ alb_status open_lane_publish(OpenLane *L, int32_t algo, int32_t slot, int32_t me
   if (algo == ALB_ALGO_SSSP && !g->weighted) return fail(ALB_E_INVAL, "SSSP needs a graph set created with weights");
   if (L->published - __atomic_load_n(&L->sh->head, __ATOMIC_ACQUIRE) >= (uint64_t)kOpenRing)
     return fail(ALB_E_INVAL, "request ring full");
-  const unsigned long long out_dev = pinned_device_address(host_out);
+  const unsigned long long out_dev = (unsigned long long)(uintptr_t)pinned_device_address(host_out);
   OpenReq &q = L->sh->req[L->published % kOpenRing];
   q.out = out_dev;
   *direct = out_dev != 0;

@@ -243,7 +243,7 @@ struct Args {
   int32_t kcore_k;      // k-core: k
   uint32_t *hot;        // k-core: bitmap of the vertices with many edges (ceil(n / 32) words)
   unsigned long long *word;  // SSSP / CC: (label << 32) | tag, tag = 1 + last round that lowered it
-  int32_t *out;         // SSSP / CC: int32 labels written by the finishing kernel
+  int32_t *out;         // SSSP, CC, k-core: int32 results; BFS: host output, or null (see alb_api.cpp, HostOut)
   float *rank;          // PageRank: fp32 ranks
   float *contrib;       // pull PageRank: rank(u) / outdeg(u) of the current iteration
   const int32_t *toff;  // pull PageRank: transposed CSR (in-edges), n + 1

@@ -1535,7 +1535,10 @@ __device__ __forceinline__ void set_up(const Args &a, Grid gr) {
 // The labels of a converged single-query launch as int32 outputs.
 template <int B, class Op>
 __device__ __forceinline__ void write_out(const Args &a, Grid gr) {
-  if constexpr (std::is_same<Op, OpSSSP>::value || std::is_same<Op, OpCC>::value) {
+  if constexpr (std::is_same<Op, OpBFS>::value) {
+    if (a.out)  // the caller's output is host memory
+      for (uint32_t v = gr.id * B + threadIdx.x; v < (uint32_t)a.n; v += gr.n * B) a.out[v] = ld_relaxed(&a.level[v]);
+  } else if constexpr (std::is_same<Op, OpSSSP>::value || std::is_same<Op, OpCC>::value) {
     for (uint32_t v = gr.id * B + threadIdx.x; v < (uint32_t)a.n; v += gr.n * B)
       a.out[v] = (int32_t)(ld_relaxed(&a.word[v]) >> 32);
   } else if constexpr (std::is_same<Op, OpKCore>::value) {
