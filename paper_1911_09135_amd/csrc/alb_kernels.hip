@@ -2479,7 +2479,7 @@ __global__ void k_tr_zero(Transpose t) {
 // iteration against 104 here; scale 22 853 and 405; Zipf 1M 114 and 90; the gathers alone take 64 at the L2s' 250 G/s).
 // The sums, and so the ranks, are bit for bit the same.
 // ---------------------------------------------------------------------------
-constexpr int kTileLoads = 8;  // edges in flight per lane
+constexpr int kTileLoads = 4;  // edges in flight per lane
 
 template <int B>
 struct SmemTiles {
