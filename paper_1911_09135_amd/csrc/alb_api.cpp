@@ -262,16 +262,22 @@ alb_status symmetrise(int32_t n, const int32_t *off, const int32_t *col, std::ve
 // Workspaces
 // --------------------------------------------------------------------------
 
-// Entries of the huge-edge chunk index: one per 2^kHintMinShift huge edges of
-// a round, plus two.  A round's huge edges are at most the worklist capacity
+// The chunk index of the huge edges: the smallest chunk (log2) and its entries,
+// one per chunk plus two.  A round's huge edges are at most the worklist capacity
 // times the largest degree (a 32-bit total: a larger one is reported as an
 // overflow by the reservation); when every vertex enters a round's worklist at
 // most once (`unique_edges` >= 0: the edge count of the graph or the batch)
 // they are at most those edges.
-uint32_t hint_entries(uint64_t qcap, int64_t unique_edges, int64_t max_deg) {
+struct HintSize {
+  int shift;
+  uint32_t entries;
+};
+HintSize hint_size(uint64_t qcap, int64_t unique_edges, int64_t max_deg, int finest = kHintFine) {
   uint64_t e = std::min<uint64_t>(qcap * (uint64_t)std::max<int64_t>(max_deg, 1), 1ull << 32);
   if (unique_edges >= 0) e = std::min<uint64_t>(e, (uint64_t)unique_edges);
-  return (uint32_t)((e >> kHintMinShift) + 2);
+  int shift = finest;
+  while (shift < kHintCoarse && (e >> shift) > kHintEntries) ++shift;
+  return {shift, (uint32_t)((e >> shift) + 2)};
 }
 
 // The distinct-entry bound of one round's worklist: BFS, k-core and PageRank
@@ -285,6 +291,7 @@ int64_t dedup_bound(OpKind op, bool dedup, int64_t m) {
 struct Needs {
   uint32_t qcap;
   uint32_t hint_cap;
+  int hint_min;
 };
 
 // Fault injection for tests: while ALB_INJECT_ALLOC_FAILURE=1 is in the
@@ -750,7 +757,7 @@ bool reserve_tiles(Workspace *ws, size_t bytes) {
 
 // Worklist capacity and chunk-index entries a call needs, and whether it
 // suppresses duplicate pushes.
-Needs job_needs(alb_graph g, const Job &job, const alb_options &o, bool *dedup_out) {
+Needs job_needs(alb_graph g, const Job &job, const alb_options &o, bool *dedup_out, bool fixed = false) {
   bool dedup = false;
   if (job.op == OP_SSSP || job.op == OP_CC) dedup = (o.dedup != 0);
   uint64_t qcap;
@@ -764,7 +771,9 @@ Needs job_needs(alb_graph g, const Job &job, const alb_options &o, bool *dedup_o
   qcap = std::max<uint64_t>(qcap, 1);
   if (qcap > 0xfffffffeULL) qcap = 0xfffffffeULL;
   *dedup_out = dedup;
-  return Needs{(uint32_t)qcap, hint_entries(qcap, dedup_bound(job.op, dedup, g->m), g->max_deg)};
+  // (the scratch array of alb_sssp_noalloc has room for the coarse index)
+  const HintSize h = hint_size(qcap, dedup_bound(job.op, dedup, g->m), g->max_deg, fixed ? kHintCoarse : kHintFine);
+  return Needs{(uint32_t)qcap, h.entries, h.shift};
 }
 
 // `fixed`: a workspace laid out by the caller (alb_sssp_noalloc's scratch):
@@ -814,7 +823,7 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
                                       : default_small_threshold(job.op, threshold);
 
   bool dedup = false;
-  const Needs nd = job_needs(g, job, o, &dedup);
+  const Needs nd = job_needs(g, job, o, &dedup, fixed != nullptr);
   const uint64_t qcap = nd.qcap;
   Workspace *ws = fixed;
   if (fixed) {
@@ -843,6 +852,7 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
   a.hint_cap = ws->hint_cap;
   a.bar = ws->bar;
   a.ctl = ws->ctl;
+  a.hint_min = nd.hint_min;
   a.source = job.source;
   a.nfront0 = job.nfront0;
   a.fill_log = fill_log(wg, g->n, g->m);
@@ -1136,6 +1146,7 @@ struct BatchJob {
   int32_t max_n = 0;
   int32_t max_deg = 0;  // largest out-degree of the queries' members
   uint64_t qcap = 0;
+  HintSize hint{kHintCoarse, 0};
   int grid = 0;
   int64_t threshold = 0;
   hipStream_t stream = nullptr;
@@ -1253,6 +1264,8 @@ alb_status prepare_batch(alb_graph g, OpKind op, int32_t count, const int32_t *m
   a.timeout_ticks = g->clock_khz * barrier_timeout_ms();
   a.join_window_ticks = std::max<uint64_t>(g->clock_khz / 100, 1);
   a.profile = getenv("ALB_TIMELINE") ? 1 : 0;
+  j.hint = hint_size(j.qcap, dedup ? edges : -1, j.max_deg);
+  a.hint_min = j.hint.shift;
   a.nq = count;
   a.qthr_min = j.thr_min;
   a.nlabels = labels;
@@ -1260,8 +1273,7 @@ alb_status prepare_batch(alb_graph g, OpKind op, int32_t count, const int32_t *m
 }
 
 BatchNeeds batch_needs(const BatchJob &j) {
-  return BatchNeeds{std::max<long long>(j.labels, 1), (uint32_t)j.qcap,
-                    hint_entries(j.qcap, j.a.dedup ? j.edges : -1, j.max_deg), j.count};
+  return BatchNeeds{std::max<long long>(j.labels, 1), (uint32_t)j.qcap, j.hint.entries, j.count};
 }
 
 // Point the job at workspace ws and copy its tables there (stream order).
@@ -1908,7 +1920,7 @@ alb_status alb_sssp_noalloc(alb_graph g, int32_t source, int32_t *dist, const al
   job.nfront0 = 1;
   job.max_rounds = g->n + 1;
   bool dedup = false;
-  const Needs nd = job_needs(g, job, o, &dedup);
+  const Needs nd = job_needs(g, job, o, &dedup, true);
   // the workspace, each part on a 256-byte boundary of the scratch
   size_t at = 0;
   auto take = [&](size_t bytes) {
@@ -2541,6 +2553,7 @@ struct OpenLane {
   long long label_cap = 0;
   uint64_t qcap = 0;
   uint32_t hint_cap = 0;
+  int hint_min = kHintCoarse;
   int64_t threshold = 0, small_threshold = 0;
   bool adaptive = false;
   // device
@@ -2607,7 +2620,9 @@ alb_status open_lane_create(alb_graph g, const alb_options &o, int32_t slots, lo
   }
   // one round's huge edges stay below 2^32 (the host admits queries while
   // their members' edges sum below that)
-  L->hint_cap = hint_entries(L->qcap, 0xfffffffeLL, max_deg);
+  const HintSize hint = hint_size(L->qcap, 0xfffffffeLL, max_deg);
+  L->hint_cap = hint.entries;
+  L->hint_min = hint.shift;
   L->max_m = max_m;
   hipError_t e;
   const size_t S = (size_t)slots;
@@ -2683,6 +2698,7 @@ alb_status open_lane_start(OpenLane *L, hipStream_t s, double idle_us, int64_t e
   a.huge_rec = L->huge_rec;
   a.hint = L->hint;
   a.hint_cap = L->hint_cap;
+  a.hint_min = L->hint_min;
   a.bar = L->bar;
   a.ctl = L->ctl;
   a.threshold = L->threshold;
@@ -2812,7 +2828,9 @@ alb_status batch_reserve(alb_graph g, int count, long long labels, int32_t nq) {
   if (!g || count < 1 || labels < 1 || nq < 1) return ALB_OK;
   HIP_TRY(hipSetDevice(g->device));
   const uint32_t qcap = (uint32_t)std::min<long long>(std::max<long long>(labels, nq), 0xfffffffeLL);
-  const BatchNeeds nd{labels, qcap, hint_entries(qcap, -1, g->max_deg), nq};
+  // (a smaller batch may want the finest index: kHintEntries and two)
+  const uint32_t hint = std::max<uint32_t>(hint_size(qcap, -1, g->max_deg).entries, (uint32_t)kHintEntries + 2);
+  const BatchNeeds nd{labels, qcap, hint, nq};
   std::vector<BatchWs *> held;
   alb_status st = ALB_OK;
   for (int i = 0; i < count && st == ALB_OK; ++i) {

@@ -40,8 +40,13 @@ constexpr size_t kBarWords = (size_t)kBarFlat + kBarStride;
 // Huge-worklist chunk index: edge index k of the round's huge edges lies in
 // chunk k >> hint_shift; hint[c] holds the huge-list slot that owns the first
 // edge of chunk c and the end of that slot's edge range.  The shift is at
-// least kHintMinShift.
-constexpr int kHintMinShift = 10;
+// least Args::hint_min: kHintFine where the index stays within kHintEntries
+// entries, up to kHintCoarse where it does not.  With 1,024-edge chunks only, the
+// low thresholds of short rounds (64 and up) left up to 16 lists in a chunk, and
+// finding an edge's list took half a dozen dependent loads (RMAT-17 SSSP:
+// 670,000 edges of 3,132 lists took 52 us).
+constexpr int kHintFine = 6, kHintCoarse = 10;
+constexpr uint64_t kHintEntries = (uint64_t)1 << 21;
 // Threshold of the explicit adaptive rule for rounds whose worklist cannot
 // give every launched thread an entry: any vertex of at least a wavefront's
 // worth of edges goes to the cyclic distribution, which keeps every
@@ -60,7 +65,7 @@ constexpr int32_t kMaxBatch = 65535;
 // workspace from (worklists, huge list, chunk index, barrier words, label
 // words, control block): about 32 bytes per vertex, so graphs of up to ~6.2M
 // vertices with the default worklist capacity.
-constexpr size_t kNoAllocScratchBytes = (size_t)192 << 20;
+constexpr size_t kNoAllocScratchBytes = ((size_t)192 << 20) + (64 << 10);
 
 // Continuous serving (alb_server with join_running): requests join a running
 // persistent batch launch between rounds; BFS and SSSP queries share it (BFS
@@ -209,6 +214,7 @@ struct Args {
   int4 *huge_rec;       // huge list (Algorithm 1 `work`): per slot {prefixWork entry, CSR start, vertex, source value}
   int2 *hint;           // chunk index of the huge edges: {slot owning the chunk's first edge, end of its edges}
   uint32_t hint_cap;
+  int32_t hint_min;     // smallest log2 of the chunk size
   unsigned long long *bar;  // grid barrier words (kBarWords)
   Ctl *ctl;
   // Persistent launches of one query set themselves up: labels, source, and

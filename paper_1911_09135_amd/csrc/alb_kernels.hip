@@ -652,9 +652,12 @@ __device__ __forceinline__ void settle_hot(const Args &a, const Op &op, int roun
 
 // log2 of the chunk size of the huge-edge index for a threshold t: the
 // largest power of two not above t, clamped, so that a chunk holds at most
-// two segment starts when t >= 2^kHintMinShift.
-__device__ __forceinline__ uint32_t hint_shift(int64_t t) {
-  if (t < (1ll << kHintMinShift)) return kHintMinShift;
+// two segment starts when t >= 2^Args::hint_min.  A short worklist (nF entries)
+// has few lists, for which coarse chunks do, and perhaps a long one, whose
+// fine chunks one wavefront would have to write (a hub of 1.8M edges: 13 us).
+__device__ __forceinline__ uint32_t hint_shift(const Args &a, int64_t t, uint32_t nF) {
+  const int least = nF < 256u ? max(a.hint_min, kHintCoarse) : a.hint_min;
+  if (t < (1ll << least)) return (uint32_t)least;
   if (t >= (1ll << kHintMaxShift)) return kHintMaxShift;
   return 63u - (uint32_t)__builtin_clzll((unsigned long long)t);
 }
@@ -1604,7 +1607,7 @@ __global__ __launch_bounds__(B) void k_twc(Args a, Op op) {
   const int64_t thr = round_threshold(a, nF, (uint64_t)gr.n * B);
   phase_twc<B, Op, false>(a, op, sm, gr, r, round_frontier<false>(a, r), nF, round_next<false>(a, r),
                           &a.ctl->qcount[(r + 1) % 3].v,
-                   &a.ctl->huge[r & 1].v, thr, hint_shift(thr), acc);
+                   &a.ctl->huge[r & 1].v, thr, hint_shift(a, thr, nF), acc);
   if constexpr (Op::kPR) flush_dangling<B, Op>(acc, sm, &a.ctl->dangling[r & 1].v);
   flush_stats<B, Op>(acc, sm, a.ctl);
 }
@@ -1619,7 +1622,7 @@ __global__ __launch_bounds__(B) void k_lb(Args a, Op op) {
   const int64_t thr = round_threshold(a, round_size(a, r), (uint64_t)gridDim.x * B);
   phase_lb<B, Op, false>(a, op, sm, Grid{blockIdx.x, gridDim.x}, r, hc, round_next<false>(a, r),
                          &a.ctl->qcount[(r + 1) % 3].v,
-                  hint_shift(thr), acc);
+                  hint_shift(a, thr, round_size(a, r)), acc);
   flush_stats<B, Op>(acc, sm, a.ctl);
 }
 
@@ -1724,7 +1727,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
     uint32_t *qn_cnt = &a.ctl->qcount[(r + 1) % 3].v;
     const int64_t thr = round_threshold(a, nF, (uint64_t)gr.n * B);
     // batch with per-query thresholds: chunk index sized for the smallest one
-    const uint32_t hs = hint_shift(M && a.qthr ? a.qthr_min : thr);
+    const uint32_t hs = hint_shift(a, M && a.qthr ? a.qthr_min : thr, nF);
     if constexpr (F) {  // two operator types here: both phases inlined
       if (filtered) {
         using FOp = typename Filtered<Op>::type;
@@ -1980,7 +1983,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
     Entry<true> *qn = round_next<true>(a, r);
     uint32_t *qn_cnt = &a.ctl->qcount[(r + 1) % 3].v;
     const int64_t thr = round_threshold(a, nF, (uint64_t)gr.n * B);
-    const uint32_t hs = hint_shift(thr);
+    const uint32_t hs = hint_shift(a, thr, nF);
     if (nF)
       phase_twc<B, Op, true>(a, op, sm, gr, r, round_frontier<true>(a, r), nF, qn, qn_cnt, &a.ctl->huge[r & 1].v,
                              thr, hs, acc);
@@ -2245,7 +2248,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
   Grid gr;
   if (!join_members(a, sm, &gr)) return;
   if (a.threshold < 0) a.threshold = (int64_t)gr.n * B;
-  const uint32_t hs = hint_shift(a.threshold);
+  const uint32_t hs = hint_shift(a, a.threshold, (uint32_t)a.n);
   unsigned long long epoch = 0;
   // set-up: ranks, sums, the first contributions and the first dangling mass
   set_up<B, OpPRPull, false>(a, gr);
