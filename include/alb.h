@@ -130,7 +130,8 @@ typedef struct {
   int64_t huge_vertices;     /* sum over rounds of the huge worklist size */
   int64_t huge_edges;        /* sum over rounds of the huge vertices' edges */
   int64_t pushes;            /* vertices pushed to a next-round worklist */
-  double device_ms;          /* device time from label initialisation to the last round */
+  double device_ms;          /* device time from label initialisation to the last round (persistent launches:
+                                by the device's wall clock, without the time to start the launch) */
   double kernel_ms;          /* device time of the traversal rounds alone */
 } alb_stats;
 
@@ -231,6 +232,10 @@ alb_status alb_kcore(alb_graph g, int32_t k, int32_t *in_core, const alb_options
  * out-edges so that the balancer sees out-degree skew, exactly `iterations` synchronous
  * iterations from rank = 1/n:  r'(v) = (1-d)/n + d * (sum over in-edges (u,v)
  * of r(u)/outdeg(u) + D/n), D = total rank of vertices without out-edges.
+ * With the balancer's default options the call may lay the in-edges out on the
+ * device first (in a workspace the handle keeps, at most a quarter of the free
+ * device memory) and sum over those; statistics are the inspection's by
+ * out-degree either way, and every configuration gives the same bits.
  * 0 < damping < 1, iterations >= 0. */
 alb_status alb_pagerank(alb_graph g, float damping, int32_t iterations, float *rank, const alb_options *opt,
                         alb_stats *stats);

@@ -194,6 +194,7 @@ struct Transpose {
   uint32_t *cursor;          // bins: totals, then the next free place
   uint2 *pairs;              // m: (source, destination), by bin
   int32_t *toff, *tcol;      // the result: n + 1 and m
+  unsigned long long *t_init;  // gets the device wall clock when the transposition begins
 };
 
 // PageRank in tiles: rows and in-edges together per tile, and threads per workgroup.

@@ -2461,6 +2461,7 @@ __global__ __launch_bounds__(kTrSortWg) void k_tr_sort(Transpose t) {
 }
 
 __global__ void k_tr_zero(Transpose t) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *t.t_init = (unsigned long long)wall_clock64();
   for (uint32_t b = blockIdx.x * blockDim.x + threadIdx.x; b < t.bins; b += gridDim.x * blockDim.x) t.cursor[b] = 0;
 }
 
