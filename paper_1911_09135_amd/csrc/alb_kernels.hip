@@ -896,7 +896,7 @@ struct Order {
       }
     } else {
       run = twc_chunk(nF, wgs, B);
-      if (!consecutive) {
+      if (!consecutive && nF <= 0xffffff00u) {  // (else the last positions would not fit in 32 bits)
         step = (uint32_t)(((uint64_t)nF + 255) / 256);
         total = step * 256u;
       }
