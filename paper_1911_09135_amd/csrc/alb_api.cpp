@@ -319,15 +319,25 @@ hipError_t palloc(T **p, size_t bytes) {
 }
 
 // The device address of pinned host memory (hipHostMalloc'd or registered
-// with the runtime), or null for any other pointer.
-void *pinned_device_address(const void *p) {
+// with the runtime), or null unless all `bytes` from p on are in one such
+// range: a kernel that writes past the end of the mapping faults, where a copy
+// of an array of which only the beginning is registered works.
+void *pinned_device_address(const void *p, size_t bytes) {
   if (!p) return nullptr;
   hipPointerAttribute_t at;
   std::memset(&at, 0, sizeof at);
-  const hipError_t e = hipPointerGetAttributes(&at, p);
-  (void)hipGetLastError();  // an unregistered pointer leaves no error behind for the next caller
-  if (e != hipSuccess || at.type != hipMemoryTypeHost || at.hostPointer != p) return nullptr;
-  return at.devicePointer;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    (void)hipGetLastError();  // an unregistered pointer leaves no error behind for the next caller
+    return nullptr;
+  }
+  if (at.type != hipMemoryTypeHost || at.hostPointer != p || !at.devicePointer) return nullptr;
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)at.devicePointer) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  return range_holds(base, size, at.devicePointer, bytes) ? at.devicePointer : nullptr;
 }
 
 // Vertices up to which a query's pageable host output is staged in pinned
@@ -990,7 +1000,7 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
   if (launch == ALB_LAUNCH_PERSISTENT && job.max_rounds > 0) {
     bool staged = false;
     if (ho && job.op != OP_RECORD && ((job.op != OP_PR && job.op != OP_PR_PULL) || pr_grid)) {
-      void *dst = pinned_device_address(ho->ptr);
+      void *dst = pinned_device_address(ho->ptr, ho->bytes);
       if (!dst && ws->h_stage) {
         dst = ws->h_stage;
         staged = true;
@@ -1306,7 +1316,8 @@ alb_status upload_batch(BatchJob &j, BatchWs *ws) {
   int32_t *d_i32 = (int32_t *)(d_out + c), *h_i32 = (int32_t *)(h_out + c);
   j.qdirect.assign(c, 0);
   for (size_t q = 0; q < c; ++q) {
-    int32_t *dst = j.o.out_on_device ? j.qout[q] : (int32_t *)pinned_device_address(j.qout[q]);
+    const size_t bytes = sizeof(int32_t) * (size_t)j.qn[q];
+    int32_t *dst = j.o.out_on_device ? j.qout[q] : (int32_t *)pinned_device_address(j.qout[q], bytes);
     j.qdirect[q] = dst != nullptr;
     h_out[q] = dst ? dst : ws->out32 + j.qlbase[q];
     h_off[q] = j.qoff[q];
@@ -2759,7 +2770,8 @@ alb_status open_lane_publish(OpenLane *L, int32_t algo, int32_t slot, int32_t me
   if (algo == ALB_ALGO_SSSP && !g->weighted) return fail(ALB_E_INVAL, "SSSP needs a graph set created with weights");
   if (L->published - __atomic_load_n(&L->sh->head, __ATOMIC_ACQUIRE) >= (uint64_t)kOpenRing)
     return fail(ALB_E_INVAL, "request ring full");
-  const unsigned long long out_dev = (unsigned long long)(uintptr_t)pinned_device_address(host_out);
+  const unsigned long long out_dev =
+      (unsigned long long)(uintptr_t)pinned_device_address(host_out, sizeof(int32_t) * (size_t)g->mem_n[member]);
   OpenReq &q = L->sh->req[L->published % kOpenRing];
   q.out = out_dev;
   *direct = out_dev != 0;

@@ -3,6 +3,9 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
+#include <cstdint>
+
 #include "../../include/alb.h"
 
 namespace alb {
@@ -12,6 +15,12 @@ alb_status set_error(alb_status s, const char *fmt, ...);
 
 // Validate `user` (NULL: the defaults) and fill its defaults into *out.
 alb_status check_options(const alb_options *user, alb_options *out);
+
+// Whether the `bytes` bytes from p on lie within the `size` bytes from base on.
+inline bool range_holds(const void *base, size_t size, const void *p, size_t bytes) {
+  const uintptr_t b = (uintptr_t)base, x = (uintptr_t)p;
+  return x >= b && x - b <= size && bytes <= size - (x - b);
+}
 
 // The automatic grid of a traversal over `edges` edges (alb_options.grid_wgs = 0).
 int auto_grid(int64_t edges, int wg, int resident);
