@@ -1291,6 +1291,40 @@ BatchNeeds batch_needs(const BatchJob &j) {
   return BatchNeeds{std::max<long long>(j.labels, 1), (uint32_t)j.qcap, j.hint.entries, j.count};
 }
 
+// Host outputs of a batch that share bytes with another of its outputs.  They
+// are copied one after the other, so that the last query's results stay;
+// written by the launch they would mix.
+std::vector<char> shared_outputs(const BatchJob &j) {
+  std::vector<size_t> order((size_t)j.count);
+  for (size_t q = 0; q < order.size(); ++q) order[q] = q;
+  std::sort(order.begin(), order.end(), [&](size_t x, size_t y) { return (uintptr_t)j.qout[x] < (uintptr_t)j.qout[y]; });
+  std::vector<char> shared((size_t)j.count, 0);
+  size_t reach = 0;  // the output that ends last so far
+  for (size_t i = 0; i < order.size(); ++i) {
+    const size_t q = order[i], r = order[reach];
+    if (i > 0 && (uintptr_t)j.qout[q] < (uintptr_t)(j.qout[r] + j.qn[r])) shared[q] = shared[r] = 1;
+    if (i == 0 || j.qout[q] + j.qn[q] > j.qout[r] + j.qn[r]) reach = i;
+  }
+  return shared;
+}
+
+// Where the launch writes each query's labels: device outputs and pinned host
+// outputs themselves, the staging area for the others.
+void place_outputs(BatchJob &j, BatchWs *ws, int32_t **dst) {
+  const size_t c = (size_t)j.count;
+  j.qdirect.assign(c, 1);
+  if (j.o.out_on_device) {
+    std::copy(j.qout.begin(), j.qout.end(), dst);
+    return;
+  }
+  const std::vector<char> shared = shared_outputs(j);
+  for (size_t q = 0; q < c; ++q) {
+    void *p = shared[q] ? nullptr : pinned_device_address(j.qout[q], sizeof(int32_t) * (size_t)j.qn[q]);
+    j.qdirect[q] = p != nullptr;
+    dst[q] = p ? (int32_t *)p : ws->out32 + j.qlbase[q];
+  }
+}
+
 // Point the job at workspace ws and copy its tables there (stream order).
 // Host outputs are staged in ws->out32.
 alb_status upload_batch(BatchJob &j, BatchWs *ws) {
@@ -1314,12 +1348,12 @@ alb_status upload_batch(BatchJob &j, BatchWs *ws) {
   long long *d_off = (long long *)ws->tab, *h_off = (long long *)ws->h_tab;
   int32_t **d_out = (int32_t **)(d_off + 3 * c), **h_out = (int32_t **)(h_off + 3 * c);
   int32_t *d_i32 = (int32_t *)(d_out + c), *h_i32 = (int32_t *)(h_out + c);
-  j.qdirect.assign(c, 0);
+  try {
+    place_outputs(j, ws, h_out);
+  } catch (const std::bad_alloc &) {
+    return fail(ALB_E_NOMEM, "host allocation failed");
+  }
   for (size_t q = 0; q < c; ++q) {
-    const size_t bytes = sizeof(int32_t) * (size_t)j.qn[q];
-    int32_t *dst = j.o.out_on_device ? j.qout[q] : (int32_t *)pinned_device_address(j.qout[q], bytes);
-    j.qdirect[q] = dst != nullptr;
-    h_out[q] = dst ? dst : ws->out32 + j.qlbase[q];
     h_off[q] = j.qoff[q];
     h_off[c + q] = j.qthr[q];
     h_off[2 * c + q] = j.qlbase[q];

@@ -1,0 +1,45 @@
+"""Host outputs of a batch that share memory: the queries' results are written
+in their order, so the last query's stay, whether the memory is pinned or not."""
+import numpy as np
+import pytest
+
+import graphgen as gg
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def host(n, pin):
+    import torch
+
+    return torch.full((n,), -7, dtype=torch.int32, pin_memory=pin).numpy()
+
+
+@pytest.mark.parametrize("pin", [True, False])
+@pytest.mark.parametrize("plan", [False, True])
+def test_shared_outputs_keep_the_last_query(pin, plan):
+    from paper_1911_09135_amd import alb
+
+    g = gg.rmat(15, 8, seed=4).with_weights(5)
+    n = g.n
+    gs = alb.GraphSet([g])
+    sources = [int(v) for v in np.flatnonzero(g.degrees() > 0)[[0, 50, 400, 900, 1500, 2200, 3100]]]
+    refs = [oracle.sssp(g, s) for s in sources]
+    block = host(4 * n, pin)
+    want = np.full(4 * n, -7, np.int32)
+    # one array three times, an array that overlaps it, two that only touch, one apart
+    at = [0, 0, n // 2, 0, 2 * n, 3 * n, n + n // 2]
+    for a, ref in zip(at, refs):
+        want[a:a + n] = ref
+    outs = [block[a:a + n] for a in at]
+    if plan:
+        p = alb.BatchPlan(gs, "sssp", [0] * len(at), sources, outs=outs)
+        for _ in range(3):
+            block[:] = -7
+            p.run()
+            assert np.array_equal(block, want)
+        p.close()
+    else:
+        alb.sssp_batch(gs, [0] * len(at), sources, outs=outs)
+        assert np.array_equal(block, want)
+    gs.close()
