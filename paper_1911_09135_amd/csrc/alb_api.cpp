@@ -1377,6 +1377,26 @@ alb_status upload_batch(BatchJob &j, BatchWs *ws) {
   return ALB_OK;
 }
 
+// A plan's output pointers for one more run.  Host arrays may have been
+// registered or unregistered as pinned memory since the last one: what the
+// launch may write is looked up again (0.1 us a query), and the table is
+// copied again where the answer differs.
+alb_status refresh_outputs(BatchJob &j, BatchWs *ws) {
+  if (j.o.out_on_device) return ALB_OK;
+  const size_t c = (size_t)j.count;
+  int32_t **h_out = (int32_t **)((long long *)ws->h_tab + 3 * c), **d_out = (int32_t **)((long long *)ws->tab + 3 * c);
+  try {
+    std::vector<int32_t *> now(c);
+    place_outputs(j, ws, now.data());
+    if (std::equal(now.begin(), now.end(), h_out)) return ALB_OK;
+    std::copy(now.begin(), now.end(), h_out);
+  } catch (const std::bad_alloc &) {
+    return fail(ALB_E_NOMEM, "host allocation failed");
+  }
+  HIP_TRY(hipMemcpyAsync(d_out, h_out, sizeof(int32_t *) * c, hipMemcpyHostToDevice, j.stream));
+  return ALB_OK;
+}
+
 // The device work of one batch: initialise labels and the first worklist, run
 // every round in one persistent launch (which writes its result block into
 // pinned memory), write the outputs.
@@ -2538,12 +2558,14 @@ alb_status alb_batch_plan_run(alb_plan p, alb_stats *stats) {
   std::lock_guard<std::mutex> lk(p->mu);
   HIP_TRY(hipSetDevice(p->g->device));
   const hipStream_t st = p->j.stream;
+  alb_status s = refresh_outputs(p->j, &p->ws);
+  if (s != ALB_OK) return s;
   p->ws.h_res->done = 0;
   HIP_TRY(hipEventRecord(p->ws.ev[0], st));
   HIP_TRY(hipGraphLaunch(p->exec, st));
   HIP_TRY(hipEventRecord(p->ws.ev[2], st));
   HIP_TRY(hipStreamSynchronize(st));
-  alb_status s = finish_batch(p->g, p->j, &p->ws, p->outs.data(), stats, event_ms(p->ws.ev[0], p->ws.ev[2]));
+  s = finish_batch(p->g, p->j, &p->ws, p->outs.data(), stats, event_ms(p->ws.ev[0], p->ws.ev[2]));
   if (s != ALB_OK) zero_stats(stats);
   return s;
 }
