@@ -1507,8 +1507,12 @@ __global__ void k_init_batch(Args a, int op) {
   for (size_t i = t; i < kBarWords; i += stride) a.bar[i] = 0ull;
 }
 
-// Batch outputs: query blockIdx.y, its vertices strided over blockIdx.x.
+// Batch outputs: query blockIdx.y, its vertices strided over blockIdx.x.  After
+// a launch that was abandoned or did not converge, which the call reports as
+// an error, none: host arrays keep what they held.
 __global__ void k_finish_batch(Args a, int op) {
+  const Ctl *c = a.ctl;
+  if (c->abort || c->overflow != 0xffffffffu || c->qcount[c->rounds % 3].v != 0) return;
   const int32_t q = blockIdx.y;
   const int32_t n = a.qn[q];
   const long long base = a.qlbase[q];
@@ -1794,7 +1798,9 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER
     st_relaxed(&a.ctl->t_end, (unsigned long long)wall_clock64());
   }
   if constexpr (!M) {
-    if (ok) write_out<B, Op>(a, gr);
+    // (not after the last round allowed, if it left work: the call returns an error then)
+    if (ok && (r < a.max_rounds || (ld_relaxed(&a.ctl->overflow) == 0xffffffffu && round_size(a, r) == 0)))
+      write_out<B, Op>(a, gr);
   }
   if constexpr (F) {
     [[clang::always_inline]] flush_stats<B, Op>(acc, sm, a.ctl);
