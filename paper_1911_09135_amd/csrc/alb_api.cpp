@@ -744,8 +744,10 @@ bool default_balance(const alb_options &o) {
 }
 
 // Make sure that ws holds `bytes` of tile layout; false if the device has no
-// room for it (the call then takes the bins).
-bool reserve_tiles(Workspace *ws, size_t bytes) {
+// room for it (the call then takes the bins).  alb_graph_info adds up every
+// workspace's bytes, also of those in use, under the handle's lock.
+bool reserve_tiles(alb_graph g, Workspace *ws, size_t bytes) {
+  std::lock_guard<std::mutex> lk(g->mu);
   if (ws->tiles_bytes >= bytes) return true;
   (void)hipFree(ws->tiles);
   ws->bytes -= ws->tiles_bytes;
@@ -940,7 +942,7 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
     } else {
       p_lrow = take(sizeof(uint16_t) * (size_t)g->m);
     }
-    if (fits && reserve_tiles(ws, at)) {
+    if (fits && reserve_tiles(g, ws, at)) {
       int held = 0;
       rs = resident_workgroups(g, OP_PR_TILES, kTileWg, &held);
       if (rs != ALB_OK) return rs;
