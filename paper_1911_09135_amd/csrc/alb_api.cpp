@@ -65,8 +65,6 @@ struct Workspace {
   Ctl *ctl = nullptr;
   int turn = 0;
   bool cleared = false;
-  void *tiles = nullptr;  // PageRank in tiles: its layout (made when first needed)
-  size_t tiles_bytes = 0;
   Ctl *h_ctl = nullptr;  // pinned host mirror (host loop, profiling)
   Result *h_res = nullptr;  // pinned, behind it: a persistent launch's result ...
   void *h_stage = nullptr;  // ... and room for one small host output, or null
@@ -74,7 +72,6 @@ struct Workspace {
   size_t bytes = 0;
 
   void release() {
-    (void)hipFree(tiles);
     (void)hipFree(q0);
     (void)hipFree(q1);
     (void)hipFree(huge_rec);
@@ -294,22 +291,117 @@ struct Needs {
   int hint_min;
 };
 
+// Layouts of PageRank in tiles (up to 12 bytes an edge).  A handle keeps them
+// for its next calls, as many as its calls have used at once; one that is not
+// in use is given back when an allocation of the library finds no room, and
+// with the handle.
+struct TileMem {
+  alb_graph g;
+  void *p;
+  size_t bytes;
+  bool busy;
+};
+std::mutex g_tiles_mu;  // no other lock is taken while it is held
+std::vector<TileMem> g_tiles;
+
+// Give back the layouts of g, or with null those that are not in use on the
+// current device; false if there was none.
+bool drop_tiles(alb_graph g) {
+  int device = 0;
+  if (!g && hipGetDevice(&device) != hipSuccess) return false;
+  bool any = false;
+  for (;;) {
+    void *p = nullptr;
+    {
+      std::lock_guard<std::mutex> lk(g_tiles_mu);
+      for (size_t i = 0; i < g_tiles.size() && !p; ++i) {
+        const TileMem &t = g_tiles[i];
+        if (g ? t.g != g : t.busy || t.g->device != device) continue;
+        p = t.p;
+        g_tiles.erase(g_tiles.begin() + (long)i);
+      }
+    }
+    if (!p) return any;
+    (void)hipFree(p);
+    any = true;
+  }
+}
+
+// Bytes of g's layouts.
+size_t tile_bytes(alb_graph g) {
+  std::lock_guard<std::mutex> lk(g_tiles_mu);
+  size_t b = 0;
+  for (const TileMem &t : g_tiles) b += t.g == g ? t.bytes : 0;
+  return b;
+}
+
 // Fault injection for tests: while ALB_INJECT_ALLOC_FAILURE=1 is in the
 // environment, every device and pinned host allocation of the library fails
-// as if memory were exhausted (without calling the allocator).
-bool alloc_failure_injected() {
+// as if memory were exhausted (without calling the allocator); with "tiles",
+// device allocations do as long as a layout of PageRank in tiles is kept.
+bool alloc_failure_injected(bool device = false) {
   const char *e = getenv("ALB_INJECT_ALLOC_FAILURE");
-  return e && e[0] == '1' && e[1] == 0;
+  if (!e) return false;
+  if (device && !std::strcmp(e, "tiles")) {
+    std::lock_guard<std::mutex> lk(g_tiles_mu);
+    return !g_tiles.empty();
+  }
+  return e[0] == '1' && e[1] == 0;
 }
 
 template <class T>
 hipError_t dalloc(T **p, size_t count, size_t &bytes) {
-  if (alloc_failure_injected()) return hipErrorOutOfMemory;
   size_t b = sizeof(T) * std::max<size_t>(count, 1);
-  hipError_t e = hipMalloc((void **)p, b);
+  auto get = [&] { return alloc_failure_injected(true) ? hipErrorOutOfMemory : hipMalloc((void **)p, b); };
+  hipError_t e = get();
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    if (drop_tiles(nullptr)) e = get();
+  }
   if (e == hipSuccess) bytes += b;
   return e;
 }
+
+// A layout of `bytes` for one call on g: a kept one, or new memory, or null if
+// the device has no room for it (the call then takes the bins).
+void *take_tiles(alb_graph g, size_t bytes) {
+  {
+    std::lock_guard<std::mutex> lk(g_tiles_mu);
+    for (TileMem &t : g_tiles)
+      if (t.g == g && !t.busy && t.bytes >= bytes) {
+        t.busy = true;
+        return t.p;
+      }
+  }
+  // (a quarter of what is free at most, so that calls which ran beside other
+  // programs' or handles' memory still do)
+  size_t free_bytes = 0, total = 0;
+  void *p = nullptr;
+  if (hipMemGetInfo(&free_bytes, &total) != hipSuccess || bytes > free_bytes / 4 || alloc_failure_injected(true) ||
+      hipMalloc(&p, bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  try {
+    std::lock_guard<std::mutex> lk(g_tiles_mu);
+    g_tiles.push_back(TileMem{g, p, bytes, true});
+  } catch (const std::bad_alloc &) {
+    (void)hipFree(p);
+    return nullptr;
+  }
+  return p;
+}
+
+// A call's hold on its layout.
+struct TileGuard {
+  void *p = nullptr;
+  ~TileGuard() {
+    if (!p) return;
+    std::lock_guard<std::mutex> lk(g_tiles_mu);
+    for (TileMem &t : g_tiles)
+      if (t.p == p) t.busy = false;
+  }
+};
 
 // Pinned host memory (the control-block and table mirrors).
 template <class T>
@@ -743,30 +835,6 @@ bool default_balance(const alb_options &o) {
          o.launch != ALB_LAUNCH_HOST_LOOP;
 }
 
-// Make sure that ws holds `bytes` of tile layout; false if the device has no
-// room for it (the call then takes the bins).  alb_graph_info adds up every
-// workspace's bytes, also of those in use, under the handle's lock.
-bool reserve_tiles(alb_graph g, Workspace *ws, size_t bytes) {
-  std::lock_guard<std::mutex> lk(g->mu);
-  if (ws->tiles_bytes >= bytes) return true;
-  (void)hipFree(ws->tiles);
-  ws->bytes -= ws->tiles_bytes;
-  ws->tiles = nullptr;
-  ws->tiles_bytes = 0;
-  // (a quarter of what is free at most, so that calls which ran beside other
-  // programs' or handles' memory still do)
-  size_t free_bytes = 0, total = 0;
-  unsigned char *p = nullptr;
-  if (hipMemGetInfo(&free_bytes, &total) != hipSuccess || bytes > free_bytes / 4 ||
-      dalloc(&p, bytes, ws->bytes) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  ws->tiles = p;
-  ws->tiles_bytes = bytes;
-  return true;
-}
-
 // Worklist capacity and chunk-index entries a call needs, and whether it
 // suppresses duplicate pushes.
 Needs job_needs(alb_graph g, const Job &job, const alb_options &o, bool *dedup_out, bool fixed = false) {
@@ -910,6 +978,7 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
     a.tcol = g->d_tcol;
   }
   int pr_grid = 0;  // PageRank in tiles: its workgroups
+  TileGuard layout;
   Transpose tr;
   std::memset(&tr, 0, sizeof tr);
   if (in_tiles) {
@@ -942,12 +1011,12 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
     } else {
       p_lrow = take(sizeof(uint16_t) * (size_t)g->m);
     }
-    if (fits && reserve_tiles(g, ws, at)) {
+    if (fits && (layout.p = take_tiles(g, at))) {
       int held = 0;
       rs = resident_workgroups(g, OP_PR_TILES, kTileWg, &held);
       if (rs != ALB_OK) return rs;
       pr_grid = (int)std::min<uint32_t>((uint32_t)held, tiles);
-      unsigned char *b = (unsigned char *)ws->tiles;
+      unsigned char *b = (unsigned char *)layout.p;
       a.n_tiles = tiles;
       a.tile_row = (uint32_t *)(b + p_row);
       a.tile_lrow = (uint16_t *)(b + p_lrow);
@@ -1907,6 +1976,7 @@ alb_status alb_graph_destroy(alb_graph g) {
   if (g->plans.load() > 0) return fail(ALB_E_INVAL, "%d batch plans still use this graph", g->plans.load());
   (void)hipSetDevice(g->device);
   if (g->stream) (void)hipStreamSynchronize(g->stream);
+  drop_tiles(g);
   for (Workspace *w : g->pool) {
     w->release();
     delete w;
@@ -1936,7 +2006,7 @@ alb_status alb_graph_info(alb_graph g, int32_t *n, int64_t *m, int32_t *max_out_
     size_t b = g->graph_bytes;
     for (Workspace *w : g->pool) b += w->bytes;
     for (BatchWs *w : g->batch_pool) b += w->bytes;
-    *device_bytes = b;
+    *device_bytes = b + tile_bytes(g);
   }
   return ALB_OK;
 }
