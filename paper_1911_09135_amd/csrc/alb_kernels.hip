@@ -305,24 +305,32 @@ struct Filtered<OpCC> {
 // LDS and lowered once per workgroup at the end of its phase; a vertex whose
 // slot another holds takes the plain path.  Below that degree a hub costs a
 // round 12 us at most, and marking more would only fill the table.
+// Workgroups of 64 threads have 128 slots: with 1,024, their 14.5 KB of LDS let
+// 11 of them onto a CU instead of 20 (undirected Zipf graph of 2^19 vertices,
+// k = 16, automatic grid: 437 us with 1,024 slots, 386 with 128).
 constexpr int32_t kHotDegree = 1024;
-constexpr uint32_t kHotSlots = 1024, kHotNone = 0xffffffffu;  // slots: a multiple of every workgroup size
+constexpr uint32_t kHotNone = 0xffffffffu;
+constexpr uint32_t hot_slots(int B) { return B == kWave ? 128 : 1024; }  // a power of two and a multiple of B
+template <uint32_t kSlots>
 struct HotTable {
-  uint32_t key[kHotSlots], cnt[kHotSlots];
+  uint32_t key[kSlots], cnt[kSlots];
 };
-__device__ __forceinline__ HotTable &hot_table() {
-  __shared__ HotTable t;
+template <uint32_t kSlots>
+__device__ __forceinline__ HotTable<kSlots> &hot_table() {
+  __shared__ HotTable<kSlots> t;
   return t;
 }
 template <int B>
 __device__ __forceinline__ void hot_clear() {
-  for (uint32_t i = threadIdx.x; i < kHotSlots; i += B) {
-    hot_table().key[i] = kHotNone;
-    hot_table().cnt[i] = 0;
+  HotTable<hot_slots(B)> &t = hot_table<hot_slots(B)>();
+  for (uint32_t i = threadIdx.x; i < hot_slots(B); i += B) {
+    t.key[i] = kHotNone;
+    t.cnt[i] = 0;
   }
   __syncthreads();
 }
 
+template <uint32_t kSlots>
 struct OpKCore {
   using val_t = int32_t;
   static constexpr int kKind = OP_KCORE;
@@ -343,9 +351,8 @@ struct OpKCore {
   __device__ __forceinline__ bool commit(const pre_t &p, int32_t, long long dl, val_t, int32_t, int32_t,
                                          uint32_t) const {
     if (p.hot) {
-      HotTable &t = hot_table();
-      const uint32_t v = (uint32_t)dl, i = (v * 2654435761u) >> 22;
-      static_assert(kHotSlots == 1u << 10, "the hash keeps ten bits");
+      HotTable<kSlots> &t = hot_table<kSlots>();
+      const uint32_t v = (uint32_t)dl, i = (v * 2654435761u) / (uint32_t)((1ull << 32) / kSlots);
       uint32_t owner = __hip_atomic_load(&t.key[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       if (owner == kHotNone) {
         const uint32_t was = atomicCAS(&t.key[i], kHotNone, v);
@@ -360,7 +367,7 @@ struct OpKCore {
   }
   // slot i's count (at a phase's end): does its vertex leave the core?
   __device__ __forceinline__ bool settle(uint32_t i, int32_t &v) const {
-    HotTable &t = hot_table();
+    HotTable<kSlots> &t = hot_table<kSlots>();
     const int32_t c = (int32_t)t.cnt[i];
     v = (int32_t)t.key[i];
     t.key[i] = kHotNone;
@@ -375,24 +382,27 @@ struct OpKCore {
 // the core (remaining degree below k), so decrementing it changes nothing
 // (its degree stays below k and it is never pushed again); the atomic is
 // skipped.
-struct OpKCoreFilter : OpKCore {
+template <uint32_t kSlots>
+struct OpKCoreFilter : OpKCore<kSlots> {
+  using Core = OpKCore<kSlots>;
+  using val_t = typename Core::val_t;
   const uint32_t *vbits;
   struct pre_t {
-    OpKCore::pre_t core;
+    typename Core::pre_t core;
     bool gone;
   };
   __device__ __forceinline__ pre_t prepare(int32_t pos, long long dl, val_t sv, int32_t src) const {
-    return {OpKCore::prepare(pos, dl, sv, src), ((vbits[dl >> 5] >> (dl & 31)) & 1u) != 0u};
+    return {Core::prepare(pos, dl, sv, src), ((vbits[dl >> 5] >> (dl & 31)) & 1u) != 0u};
   }
   __device__ __forceinline__ bool commit(const pre_t &p, int32_t pos, long long dl, val_t sv, int32_t src, int32_t gt,
                                          uint32_t tag) const {
-    return !p.gone && OpKCore::commit(p.core, pos, dl, sv, src, gt, tag);
+    return !p.gone && Core::commit(p.core, pos, dl, sv, src, gt, tag);
   }
 };
-template <>
-struct Filtered<OpKCore> {
-  using type = OpKCoreFilter;
-  __device__ static type make(const OpKCore &op, const Args &a) {
+template <uint32_t kSlots>
+struct Filtered<OpKCore<kSlots>> {
+  using type = OpKCoreFilter<kSlots>;
+  __device__ static type make(const OpKCore<kSlots> &op, const Args &a) {
     type f;
     f.rem = op.rem;
     f.k = op.k;
@@ -460,7 +470,9 @@ OpPR make_op<OpPR>(const Args &a) { return OpPR{a.rank, a.acc}; }
 template <>
 OpRecord make_op<OpRecord>(const Args &a) { return OpRecord{a.hits, a.thread_of}; }
 template <>
-OpKCore make_op<OpKCore>(const Args &a) { return OpKCore{a.level, a.kcore_k, a.hot}; }
+OpKCore<hot_slots(64)> make_op<OpKCore<hot_slots(64)>>(const Args &a) { return {a.level, a.kcore_k, a.hot}; }
+template <>
+OpKCore<hot_slots(256)> make_op<OpKCore<hot_slots(256)>>(const Args &a) { return {a.level, a.kcore_k, a.hot}; }
 
 // ---------------------------------------------------------------------------
 // Per-thread statistics, shared memory, work-distribution grid, push staging.
@@ -642,7 +654,7 @@ template <int B, class Op, class E>
 __device__ __forceinline__ void settle_hot(const Args &a, const Op &op, int round, Pusher<E> &pu, Acc &acc) {
   if constexpr (Op::kHot) {
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < kHotSlots; i += B) {
+    for (uint32_t i = threadIdx.x; i < hot_slots(B); i += B) {
       int32_t v;
       const bool p = op.settle(i, v);
       push_wave<E>(p, (E)v, a, round, pu, acc);
@@ -1552,7 +1564,7 @@ __device__ __forceinline__ void write_out(const Args &a, Grid gr) {
   } else if constexpr (std::is_same<Op, OpSSSP>::value || std::is_same<Op, OpCC>::value) {
     for (uint32_t v = gr.id * B + threadIdx.x; v < (uint32_t)a.n; v += gr.n * B)
       a.out[v] = (int32_t)(ld_relaxed(&a.word[v]) >> 32);
-  } else if constexpr (std::is_same<Op, OpKCore>::value) {
+  } else if constexpr (Op::kKind == OP_KCORE) {
     for (uint32_t v = gr.id * B + threadIdx.x; v < (uint32_t)a.n; v += gr.n * B)
       a.out[v] = (int32_t)(ld_relaxed(&a.level[v]) >= a.kcore_k);
   }
@@ -1662,11 +1674,18 @@ __device__ __forceinline__ void build_filter(const Args &a, Grid gr, unsigned lo
   if (lane == 0 && set) add_relaxed(count, set);
 }
 
+// Waves per SIMD of k_persistent: k-core in workgroups of 64 keeps five (20
+// workgroups per CU, of which grids up to 5,120 are accepted).
+template <int B, class Op, bool F>
+constexpr int waves_wanted() {
+  return Op::kHot && B == kWave && !F && ALB_WAVES_PER_EU < 5 ? 5 : ALB_WAVES_PER_EU;
+}
+
 // F: BFS or CC with the filter bitmap (a kernel of its own, so that every
 // other launch runs code without it).
 template <int B, class Op, bool M, bool F = false>
-__global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(ALB_WAVES_PER_EU))) void k_persistent(Args a,
-                                                                                                           Op op) {
+__global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(waves_wanted<B, Op, F>()))) void k_persistent(
+    Args a, Op op) {
   __shared__ Smem<B, Op, M> sm;
   Acc acc;
   Grid gr;
@@ -2752,7 +2771,7 @@ template <int B, class Op>
 struct PersistentF {
   static hipError_t run(int grid, const Args *a, hipStream_t s) {
     if constexpr (std::is_same<Op, OpBFS>::value || std::is_same<Op, OpCC>::value ||
-                  std::is_same<Op, OpKCore>::value) {
+                  (Op::kKind == OP_KCORE)) {
       if (a->vbits) {  // with the filter bitmap
         hipLaunchKernelGGL((k_persistent<B, Op, false, true>), dim3(grid), dim3(B), 0, s, *a, make_op<Op>(*a));
         return hipGetLastError();
@@ -2820,7 +2839,7 @@ hipError_t by_op(OpKind op, Xs... xs) {
     case OP_CC: return F<B, OpCC>::run(xs...);
     case OP_PR: return F<B, OpPR>::run(xs...);
     case OP_RECORD: return F<B, OpRecord>::run(xs...);
-    case OP_KCORE: return F<B, OpKCore>::run(xs...);
+    case OP_KCORE: return F<B, OpKCore<hot_slots(B)>>::run(xs...);
   }
   return hipErrorInvalidValue;
 }
