@@ -1379,8 +1379,18 @@ std::vector<char> shared_outputs(const BatchJob &j) {
   return shared;
 }
 
-// Where the launch writes each query's labels: device outputs and pinned host
-// outputs themselves, the staging area for the others.
+// Vertices up to which a query's pinned host output is written by the batch's
+// last kernel.  A copy costs about 10 us of its own (32 SSSP queries on RMAT-16:
+// 1,445 us copied, 1,120 written, on RMAT-18 2,521 and 2,182); but the kernel's
+// workgroups wait for the host link while another stream's launch wants their
+// places, where a copy engine leaves them free (two serving lanes over members of
+// up to 2^23 vertices, saturated: 1,770 queries/s with every output written,
+// 1,900 with those of up to 2^18; alone, a batch on RMAT-20 takes 8,048 and 7,677
+// us copied and written).
+constexpr int32_t kDirectVertices = 1 << 18;
+
+// Where the launch writes each query's labels: device outputs and small pinned
+// host outputs themselves, the staging area for the others.
 void place_outputs(BatchJob &j, BatchWs *ws, int32_t **dst) {
   const size_t c = (size_t)j.count;
   j.qdirect.assign(c, 1);
@@ -1390,7 +1400,8 @@ void place_outputs(BatchJob &j, BatchWs *ws, int32_t **dst) {
   }
   const std::vector<char> shared = shared_outputs(j);
   for (size_t q = 0; q < c; ++q) {
-    void *p = shared[q] ? nullptr : pinned_device_address(j.qout[q], sizeof(int32_t) * (size_t)j.qn[q]);
+    const bool copied = shared[q] || j.qn[q] > kDirectVertices;
+    void *p = copied ? nullptr : pinned_device_address(j.qout[q], sizeof(int32_t) * (size_t)j.qn[q]);
     j.qdirect[q] = p != nullptr;
     dst[q] = p ? (int32_t *)p : ws->out32 + j.qlbase[q];
   }

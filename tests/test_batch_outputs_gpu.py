@@ -43,3 +43,27 @@ def test_shared_outputs_keep_the_last_query(pin, plan):
         alb.sssp_batch(gs, [0] * len(at), sources, outs=outs)
         assert np.array_equal(block, want)
     gs.close()
+
+
+@pytest.mark.parametrize("n", [(1 << 18) - 1, 1 << 18, (1 << 18) + 1])
+@pytest.mark.parametrize("plan", [False, True])
+def test_outputs_around_the_size_that_is_written(n, plan):
+    """Up to 2^18 vertices the launch writes pinned outputs, beyond they are copied."""
+    from paper_1911_09135_amd import alb
+
+    rng = np.random.default_rng(n)
+    big = gg.from_edges(n, rng.integers(0, n, 4 * n), rng.integers(0, n, 4 * n), rng.integers(1, 9, 4 * n))
+    small = gg.rmat(9, 8, seed=1).with_weights(2)
+    gs = alb.GraphSet([big, small])
+    members, sources = [0, 1, 0], [0, 0, n - 1]
+    outs = [host(n, True), host(small.n, True), host(n, False)]
+    refs = [oracle.sssp((big, small)[m], s) for m, s in zip(members, sources)]
+    p = alb.BatchPlan(gs, "sssp", members, sources, outs=outs) if plan else None
+    for _ in range(2):
+        for o in outs:
+            o[:] = -7
+        p.run() if plan else alb.sssp_batch(gs, members, sources, outs=outs)
+        assert all(np.array_equal(o, ref) for o, ref in zip(outs, refs))
+    if plan:
+        p.close()
+    gs.close()
