@@ -718,6 +718,18 @@ struct Job {
   uint32_t qcap_min = 0;
 };
 
+// Vertices per thread of a persistent launch's grid beyond which its labels are
+// set up, and its results written, by launches of their own.  The grid is sized
+// by the edges, so on graphs of few edges per vertex, and for small explicit
+// grids, it would take long over the vertices; two more launches cost about 3 us.
+// BFS labels are half as wide and its results need no pass; k-core reads the
+// degrees.  Measured (us a call, inside / apart, at vertices per thread): SSSP
+// 8.7 114 / 117, 20 48 / 47, 29 56 / 55, 87 69 / 55, 195 95 / 48, 1,560 479 / 68;
+// CC 19 128 / 127, 59 184 / 172; k-core 8.7 125 / 124, 14 211 / 210, 19 110 / 101,
+// 195 460 / 342; BFS 29 49 / 51, 63 46 / 49, 108 56 / 56, 233 50 / 48, 1,560 93 /
+// 47.
+int64_t apart_vertices(OpKind op) { return op == OP_BFS ? 96 : op == OP_KCORE ? 12 : 24; }
+
 // A host output of n 4-byte results.  Where it is pinned memory, or small
 // enough to be staged there, the persistent launch writes it (RMAT-14 BFS: a
 // copy of 64 KB into pageable memory and its wait took 15 us of a call);
@@ -1069,8 +1081,10 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
     a.prof_wg = prof.p;
   }
   if (launch == ALB_LAUNCH_PERSISTENT && job.max_rounds > 0) {
+    const bool labels = job.op == OP_BFS || job.op == OP_SSSP || job.op == OP_CC || job.op == OP_KCORE;
+    a.apart = labels && (int64_t)g->n > apart_vertices(job.op) * grid * wg;
     bool staged = false;
-    if (ho && job.op != OP_RECORD && ((job.op != OP_PR && job.op != OP_PR_PULL) || pr_grid)) {
+    if (ho && !a.apart && job.op != OP_RECORD && ((job.op != OP_PR && job.op != OP_PR_PULL) || pr_grid)) {
       void *dst = pinned_device_address(ho->ptr, ho->bytes);
       if (!dst && ws->h_stage) {
         dst = ws->h_stage;
@@ -1083,7 +1097,7 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
       ho->done = dst != nullptr;
     }
     // one launch does everything, from the labels' initialisation to the
-    // outputs, and writes its result block into pinned memory
+    // outputs (unless apart), and writes its result block into pinned memory
     if (!fixed) {
       a.bar = ws->bar + (size_t)ws->turn * kBarWords;
       a.ctl = ws->ctl + ws->turn;
@@ -1094,7 +1108,10 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
     } else {
       a.result = &ws->ctl->result;
     }
-    if (fixed || !ws->cleared) HIP_TRY(launch_clear(a, stream));
+    if (a.apart)
+      HIP_TRY(launch_init(job.op, a, stream));
+    else if (fixed || !ws->cleared)
+      HIP_TRY(launch_clear(a, stream));
     ws->cleared = false;  // until this launch is known to have cleared the other one
     if (tr.toff) {
       tr.t_init = &a.ctl->t_init;
@@ -1106,6 +1123,7 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
       HIP_TRY(launch_pull_pr(wg, grid, a, stream));
     else
       HIP_TRY(launch_persistent(job.op, wg, grid, a, stream));
+    if (a.apart && job.op != OP_BFS) HIP_TRY(launch_finish(job.op, a, stream));
     Result res;
     if (fixed) HIP_TRY(hipMemcpyAsync(&res, a.result, sizeof(Result), hipMemcpyDeviceToHost, stream));
     HIP_TRY(hipStreamSynchronize(stream));

@@ -224,6 +224,7 @@ struct Args {
   // sets are used in turn, because workgroups that find membership closed
   // may start late and still take their ticket.
   int32_t source;
+  int32_t apart;        // labels and outputs by kernels of their own (launch_init, launch_finish)
   Ctl *clear_ctl;
   unsigned long long *clear_bar;
   Result *result;       // written when the persistent launch ends
@@ -297,7 +298,7 @@ struct Args {
 };
 
 // Host-callable launchers (alb_kernels.hip).  All return the launch status.
-// Host loop: labels, control block and barrier words.
+// Labels, control block and barrier words: host loop, and persistent launches with Args::apart.
 hipError_t launch_init(OpKind op, const Args &a, hipStream_t s);
 // Zeroed control block and barrier words for a persistent launch of one query.
 hipError_t launch_clear(const Args &a, hipStream_t s);
@@ -313,7 +314,7 @@ hipError_t pr_tiles_occupancy(int *blocks_per_cu);
 // In-edge CSR of a graph (the sources of a row in no particular order).
 hipError_t launch_transpose(const Transpose &t, hipStream_t s);
 hipError_t launch_persistent(OpKind op, int wg, int grid, const Args &a, hipStream_t s);
-// Host loop.  SSSP / CC: out[v] = word[v] >> 32; k-core: out[v] = (level[v] >= k).
+// (likewise)  SSSP / CC: out[v] = word[v] >> 32; k-core: out[v] = (level[v] >= k).
 hipError_t launch_finish(OpKind op, const Args &a, hipStream_t s);
 // Workgroups of `wg` threads that fit on one CU for the persistent kernel of
 // `op`, by the runtime's occupancy calculator (an upper bound: the launch

@@ -1485,10 +1485,14 @@ __global__ void k_clear(Args a) {
 __global__ void k_init(Args a, int op) {
   const uint32_t stride = gridDim.x * blockDim.x;
   const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t == 0) {
+    const unsigned long long now = (unsigned long long)wall_clock64();
+    reset_ctl(a.ctl);
+    a.ctl->t_init = now;
+  }
   for (uint32_t v = t; v < (uint32_t)a.n; v += stride) init_label(a, op, v);
   for (size_t i = t; i < kBarWords; i += stride) a.bar[i] = 0ull;
   if (t == 0) {
-    reset_ctl(a.ctl);
     if (a.source >= 0 && op != OP_RECORD) ((int32_t *)a.q0)[0] = a.source;
   }
 }
@@ -1545,7 +1549,7 @@ __device__ __forceinline__ void set_up(const Args &a, Grid gr) {
       else
         st_relaxed(&a.word[l], 0ull);
     }
-  } else {
+  } else if (!a.apart) {
     if (t == 0 && a.source >= 0) st_relaxed((int32_t *)a.q0, a.source);
     for (uint32_t v = t; v < (uint32_t)a.n; v += stride) init_label(a, (int)Op::kKind, v);
   }
@@ -1818,7 +1822,8 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(waves_wanted<
   }
   if constexpr (!M) {
     // (not after the last round allowed, if it left work: the call returns an error then)
-    if (ok && (r < a.max_rounds || (ld_relaxed(&a.ctl->overflow) == 0xffffffffu && round_size(a, r) == 0)))
+    if (ok && !a.apart &&
+        (r < a.max_rounds || (ld_relaxed(&a.ctl->overflow) == 0xffffffffu && round_size(a, r) == 0)))
       write_out<B, Op>(a, gr);
   }
   if constexpr (F) {
