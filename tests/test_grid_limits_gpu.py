@@ -47,3 +47,19 @@ def test_full_grids(handles, op, wg):
         outs, _ = getattr(alb, op)(gs, [0, 0], [5, 7], **o)
         for x, s in zip(outs, (5, 7)):
             assert np.array_equal(x, getattr(oracle, op[:-6])(g, s))
+
+
+def test_automatic_grid_of_pull_pagerank_in_bins():
+    """At most four waves per SIMD, however many edges ask for more."""
+    import torch
+
+    from paper_1911_09135_amd import alb
+
+    n, m = 1 << 12, 1 << 28  # 2 * cbrt(m) = 1,290 workgroups
+    off = (np.arange(n + 1, dtype=np.int64) * (m // n)).astype(np.int32)
+    col = np.tile(np.arange(n, dtype=np.int32), m // n)
+    with alb.Graph(off, col, build_transpose=True) as dg:
+        del col
+        _, st = alb.pagerank_pull(dg, 0.85, 1, mode="twc")
+        assert st["launched_threads"] <= 1024 * torch.cuda.get_device_properties(0).multi_processor_count
+        assert st["edges_examined"] == m
