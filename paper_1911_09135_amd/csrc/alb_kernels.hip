@@ -830,7 +830,7 @@ __device__ __forceinline__ void block_exscan(int32_t x, int32_t &excl, int32_t &
 // claims per workgroup, so that a short worklist still reaches every
 // workgroup instead of leaving most of them idle for the phase.
 __device__ __forceinline__ uint32_t twc_chunk(uint32_t nF, uint32_t wgs, int B) {
-  const uint32_t per = nF / (2u * wgs) + 1u;
+  const uint32_t per = nF ? (nF - 1u) / (2u * wgs) + 1u : 0u;  // rounded up, without a sum that could wrap
   return min(max((per + kWave - 1u) / kWave * kWave, (uint32_t)kWave), (uint32_t)B);
 }
 
