@@ -20,7 +20,9 @@
  *    non-decreasing, row_offsets[n] = m; col has m int32 entries in [0, n);
  *    weights (optional) has m non-negative int32 entries.  0 <= m < 2^31.
  *  - Label outputs have n elements and are owned by the caller.  By default
- *    they are host pointers and the call returns when they are filled.  With
+ *    they are host pointers and the call returns when they are filled; an
+ *    array that lies wholly in memory pinned with the HIP runtime may be
+ *    written by the device itself.  With
  *    options.out_on_device != 0 they are device pointers (for example a torch
  *    tensor's data_ptr()), written in stream order on options.stream; the
  *    call then returns after enqueueing the copy-out and the stats are valid
@@ -132,7 +134,9 @@ typedef struct {
   int64_t pushes;            /* vertices pushed to a next-round worklist */
   double device_ms;          /* device time from label initialisation to the last round (persistent launches:
                                 by the device's wall clock, without the time to start the launch) */
-  double kernel_ms;          /* device time of the traversal rounds alone */
+  double kernel_ms;          /* device time of the traversal rounds alone (persistent launches: from the first
+                                round's start, after set-up and its barrier; PageRank in tiles: with the time to
+                                lay the in-edges out) */
 } alb_stats;
 
 /* Fill *opt with defaults.  Returns ALB_E_INVAL for NULL. */
@@ -194,7 +198,7 @@ alb_status alb_sssp(alb_graph g, int32_t source, int32_t *dist, const alb_option
  * result, options and kernels as alb_sssp, but the per-call workspace
  * (worklists, huge list, chunk index, barrier words, 64-bit label words and
  * the control block: about 32 bytes per vertex with the default worklist
- * capacity) lives in one device array of 192 MiB that the library holds on
+ * capacity) lives in one device array of 192 MiB and 64 KiB that the library holds on
  * each GPU it runs on until the process ends; the call allocates no device or
  * pinned memory and records no event.
  *  - dist: DEVICE pointer to n int32 (whatever options.out_on_device says),
@@ -233,9 +237,13 @@ alb_status alb_kcore(alb_graph g, int32_t k, int32_t *in_core, const alb_options
  * iterations from rank = 1/n:  r'(v) = (1-d)/n + d * (sum over in-edges (u,v)
  * of r(u)/outdeg(u) + D/n), D = total rank of vertices without out-edges.
  * With the balancer's default options the call may lay the in-edges out on the
- * device first (in a workspace the handle keeps, at most a quarter of the free
- * device memory) and sum over those; statistics are the inspection's by
- * out-degree either way, and every configuration gives the same bits.
+ * device first (up to 12 bytes an edge, at most a quarter of the free device
+ * memory; the handle keeps the layout for its next calls until another
+ * allocation of the library needs the room) and sum over those, rows and
+ * in-edges cut into equal tiles instead of bins.  Every configuration gives the
+ * same bits.  Statistics are the inspection's by out-degree either way: in
+ * tiles, what it would count (huge_vertices, huge_edges, edges_examined) is
+ * worked out from the degrees.
  * 0 < damping < 1, iterations >= 0. */
 alb_status alb_pagerank(alb_graph g, float damping, int32_t iterations, float *rank, const alb_options *opt,
                         alb_stats *stats);
@@ -284,7 +292,7 @@ typedef enum { ALB_ALGO_BFS = 0, ALB_ALGO_SSSP = 1 } alb_algo;
 
 /* Batch plans: a batch laid out once -- per-query tables uploaded, its own
  * workspace allocated -- and its device work (label initialisation, the
- * persistent launch, the output kernel, the control-block read-back) captured
+ * persistent launch, the output kernel) captured
  * into a HIP graph that every alb_batch_plan_run replays on options.stream
  * (the library's stream if NULL).  For batches that recur with the same
  * queries; arguments as for alb_bfs_batch / alb_sssp_batch, and `outs` must
@@ -470,7 +478,9 @@ alb_status alb_server_batch_log(alb_server s, int32_t max, alb_batch_record *out
 /* PageRank as the paper's pr does it (pull, Section 5): the same iteration
  * and arguments as alb_pagerank, but every vertex sums its in-neighbours'
  * rank(u)/outdeg(u) over the transposed graph, and the balancer classifies
- * vertices by in-degree.  The sums use the same exact fixed point, so the
+ * vertices by in-degree; with the balancer's default options it takes the same
+ * tiles as alb_pagerank, and the statistics are again worked out from the
+ * degrees.  The sums use the same exact fixed point, so the
  * ranks equal alb_pagerank's bit for bit.  Needs a handle created with
  * ALB_BUILD_TRANSPOSE (ALB_E_INVAL otherwise); one persistent launch only
  * (launch = HOST_LOOP is ALB_E_UNSUPPORTED). */

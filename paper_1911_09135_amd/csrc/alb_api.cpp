@@ -1390,7 +1390,8 @@ BatchNeeds batch_needs(const BatchJob &j) {
 std::vector<char> shared_outputs(const BatchJob &j) {
   std::vector<size_t> order((size_t)j.count);
   for (size_t q = 0; q < order.size(); ++q) order[q] = q;
-  std::sort(order.begin(), order.end(), [&](size_t x, size_t y) { return (uintptr_t)j.qout[x] < (uintptr_t)j.qout[y]; });
+  std::sort(order.begin(), order.end(),
+            [&](size_t x, size_t y) { return (uintptr_t)j.qout[x] < (uintptr_t)j.qout[y]; });
   std::vector<char> shared((size_t)j.count, 0);
   size_t reach = 0;  // the output that ends last so far
   for (size_t i = 0; i < order.size(); ++i) {

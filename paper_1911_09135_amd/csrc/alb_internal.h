@@ -64,7 +64,9 @@ constexpr int32_t kMaxBatch = 65535;
 // Bytes of the per-GPU device scratch array that alb_sssp_noalloc carves its
 // workspace from (worklists, huge list, chunk index, barrier words, label
 // words, control block): about 32 bytes per vertex, so graphs of up to ~6.2M
-// vertices with the default worklist capacity.
+// vertices with the default worklist capacity.  (The 64 KiB are what the
+// control block and the second set of counters grew by, so that no graph that
+// fitted is refused.)
 constexpr size_t kNoAllocScratchBytes = ((size_t)192 << 20) + (64 << 10);
 
 // Continuous serving (alb_server with join_running): requests join a running

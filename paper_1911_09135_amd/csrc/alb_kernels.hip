@@ -4,9 +4,9 @@
 // phases over the active worklist F:
 //
 //   phase 1  inspection + TWC (Algorithm 1, Section 3 "TWC").  Each workgroup
-//            takes B consecutive entries of F.  A vertex whose out-degree is
-//            >= threshold is appended to the huge list; its degree is added
-//            to prefixWork in the same wave-aggregated 64-bit atomic, so the
+//            takes up to B entries of F at a time (see Order).  A vertex
+//            whose out-degree is >= threshold is appended to the huge list;
+//            its degree is added to prefixWork in the same wave-aggregated 64-bit atomic, so the
 //            exclusive prefix of the huge degrees (Section 4.1 "Search") is
 //            known once the phase ends.  Every other vertex is processed at
 //            once by the workgroup, wavefront or thread bin of its degree.
@@ -834,13 +834,13 @@ __device__ __forceinline__ uint32_t twc_chunk(uint32_t nF, uint32_t wgs, int B) 
   return min(max((per + kWave - 1u) / kWave * kWave, (uint32_t)kWave), (uint32_t)B);
 }
 
-// Workgroups take runs of consecutive worklist entries one at a time, so a
-// run that takes long does not hold up work queued behind it.  The first run
-// of workgroup g is fixed (entries [g * C0, (g + 1) * C0)) and needs no
-// atomic; later runs are claimed from a counter over the entries beyond
-// those, each sized from the remainder the previous claim's atomic returned
-// (guided self-scheduling): B while plenty remain, then fewer whole
-// wavefronts, so that the phase ends with short runs and the workgroups
+// Workgroups take runs of consecutive positions one at a time (which worklist
+// entry a position stands for, Order says), so a run that takes long does not
+// hold up work queued behind it.  The first run of workgroup g is fixed
+// (positions [g * C0, (g + 1) * C0)) and needs no atomic; later runs are
+// claimed from a counter over the positions beyond those, each sized from the
+// remainder the previous claim's atomic returned (guided self-scheduling): B
+// while plenty remain, then fewer whole wavefronts, so that the phase ends with short runs and the workgroups
 // reach the barrier together.  The counter is only ever touched by the
 // atomic (a plain load of a contended counter is slow).  Thread 0 of the
 // workgroup holds the state; the caller's workgroup barriers separate one
@@ -1259,8 +1259,13 @@ __device__ __forceinline__ bool bar_wait(const Args &a, unsigned long long *w, u
 // of a label may still return a value from an earlier round, which is why
 // operators read labels with agent-scope loads (they cost what plain loads
 // do: 248-250 G random 8-byte reads/s from a table that the L2 holds, either
-// way).  Full: with an agent-scope release by each XCD's last arrival (the
-// L2 write-back covers every line of that L2 whichever CU wrote it) and an
+// way).  Two plain readers across light barriers do with such an old value:
+// k-core's bitmap of hubs, which only chooses between two ways to count a
+// decrement, and the build of a filter bitmap, whose labels change in one
+// direction, so that an old one leaves a bit clear and the label is read.
+// (Values from before the launch are never seen: a kernel starts with the
+// caches invalidated.)  Full: with an agent-scope release by each XCD's last
+// arrival (the L2 write-back covers every line of that L2 whichever CU wrote it) and an
 // agent-scope acquire by every workgroup, for phases that exchange data by
 // plain loads and stores (PageRank, filter bitmaps, serving).  The acquires
 // of the workgroups of one XCD run one after the other: with them the barrier
@@ -1278,8 +1283,9 @@ __device__ bool grid_barrier(const Args &a, S &sm, Grid gr, unsigned long long &
     unsigned long long *b = a.bar;
     const unsigned long long target = epoch + 1;
     // few members (and no release to share) arrive on one counter directly
-    // (its own: a launch may use both kinds of barrier): 32 of them meet in 1.6 us so, in 2.1 by way of the XCDs' counters,
-    // 64 in 2.0 and 2.2, 128 in 2.8 and 2.3
+    // (its own: a launch may use both kinds of barrier): 32 of them meet in 1.6
+    // us so, in 2.1 by way of the XCDs' counters, 64 in 2.0 and 2.2, 128 in 2.8
+    // and 2.3
     if (!kFull && gr.n <= 48) {
       if ((add_relaxed(&b[kBarFlat], 1ull) + 1) % gr.n == 0) st_relaxed(&b[kBarGen], target);
     } else if ((add_relaxed(&b[kBarXcdArrive + (size_t)kBarStride * gr.xcd], 1ull) + 1) % gr.xcd_n == 0) {
@@ -2358,7 +2364,7 @@ __global__ __launch_bounds__(kTrWg) void k_tr_count(Transpose t) {
 }
 
 // Exclusive prefix sum over len entries of LDS by the whole workgroup of B
-// threads (len a multiple of B or smaller than it); returns the total.
+// threads; returns the total.
 template <int B>
 __device__ __forceinline__ uint32_t lds_exscan(uint32_t *x, uint32_t len, uint32_t *wsum) {
   const uint32_t per = (len + B - 1) / B, i0 = threadIdx.x * per;
@@ -2514,8 +2520,11 @@ __global__ void k_tr_zero(Transpose t) {
 // cut by a workgroup boundary meet in memory, between the two barriers of an
 // iteration.  The bin kernels above spent their time in chains of dependent
 // loads per vertex, skew and full barriers (RMAT scale 20, 16M edges: 289 us an
-// iteration against 104 here; scale 22 853 and 405; Zipf 1M 114 and 90; the gathers alone take 64 at the L2s' 250 G/s).
-// The sums, and so the ranks, are bit for bit the same.
+// iteration against 104 here; scale 22 853 and 405; Zipf 1M 114 and 90; the
+// gathers alone take 64 at the L2s' 250 G/s).  The sums, and so the ranks, are
+// bit for bit the same.  Cutting rows and entries, merged, into equal parts is
+// the merge-path decomposition of sparse matrix-vector products (Merrill and
+// Garland, 2016).
 // ---------------------------------------------------------------------------
 constexpr int kTileLoads = 4;  // edges in flight per lane
 
