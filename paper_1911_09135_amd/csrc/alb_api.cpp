@@ -847,6 +847,24 @@ bool default_balance(const alb_options &o) {
          o.launch != ALB_LAUNCH_HOST_LOOP;
 }
 
+// Rows and in-edges per tile of a graph of `items` of them, for `held` resident
+// workgroups: so many that every workgroup takes the same number of tiles, of at
+// most kTileItems.  4,096 for every graph left most workgroups idle during a
+// second tile of some (uniform graph of 2^18 vertices and 4.2M edges, 1,089 tiles
+// of them on 1,024 workgroups, 30 iterations: 1,344 us, 991 with two tiles of
+// 2,304 each; the bins take 1,223).  Where one tile each is enough, about 320
+// workgroups, with tiles of 512 to 2,048: fewer take longer over their tiles,
+// more at the barriers (us for 30 iterations at 512, 1,024, 2,048 and 4,096: grid
+// of 10,000 vertices 233, 256, 273, 365; RMAT-14 304, 285, 323, 399; RMAT-16 496,
+// 494, 425, 437; uniform, 2^16 vertices, 1.1M edges 484, 483, 449, 441).
+uint32_t tile_size(uint64_t items, uint32_t held) {
+  const auto share = [&](uint64_t tiles) { return ((items + tiles - 1) / tiles + kTileWg - 1) / kTileWg * kTileWg; };
+  const uint64_t one = std::max<uint64_t>(512, std::min<uint64_t>(2048, share(320)));
+  if (items <= one * held) return (uint32_t)one;
+  const uint64_t turns = (items + (uint64_t)held * kTileItems - 1) / ((uint64_t)held * kTileItems);
+  return (uint32_t)share(held * turns);
+}
+
 // Worklist capacity and chunk-index entries a call needs, and whether it
 // suppresses duplicate pushes.
 Needs job_needs(alb_graph g, const Job &job, const alb_options &o, bool *dedup_out, bool fixed = false) {
@@ -999,7 +1017,11 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
   std::memset(&tr, 0, sizeof tr);
   if (in_tiles) {
     const uint64_t items = (uint64_t)g->n + (uint64_t)g->m;
-    const uint32_t tiles = (uint32_t)((items + kTileItems - 1) / kTileItems);
+    int held = 0;
+    rs = resident_workgroups(g, OP_PR_TILES, kTileWg, &held);
+    if (rs != ALB_OK) return rs;
+    a.tile_items = tile_size(items, (uint32_t)held);
+    const uint32_t tiles = (uint32_t)((items + a.tile_items - 1) / a.tile_items);
     size_t at = 0;
     auto take = [&](size_t bytes) {
       const size_t p = at;
@@ -1028,9 +1050,6 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
       p_lrow = take(sizeof(uint16_t) * (size_t)g->m);
     }
     if (fits && (layout.p = take_tiles(g, at))) {
-      int held = 0;
-      rs = resident_workgroups(g, OP_PR_TILES, kTileWg, &held);
-      if (rs != ALB_OK) return rs;
       pr_grid = (int)std::min<uint32_t>((uint32_t)held, tiles);
       unsigned char *b = (unsigned char *)layout.p;
       a.n_tiles = tiles;

@@ -199,7 +199,7 @@ struct Transpose {
   unsigned long long *t_init;  // gets the device wall clock when the transposition begins
 };
 
-// PageRank in tiles: rows and in-edges together per tile, and threads per workgroup.
+// PageRank in tiles: most rows and in-edges together per tile, and threads per workgroup.
 constexpr uint32_t kTileItems = 4096;
 constexpr int kTileWg = 256;
 
@@ -258,13 +258,15 @@ struct Args {
   float *contrib;       // pull PageRank: rank(u) / outdeg(u) of the current iteration
   const int32_t *toff;  // pull PageRank: transposed CSR (in-edges), n + 1
   const int32_t *tcol;  //   and m sources
-  // PageRank in tiles (k_pr_tiles): the tiles' first rows (n_tiles + 1), each
+  // PageRank in tiles (k_pr_tiles): rows and in-edges per tile (tile_items, at
+  // most kTileItems), the tiles' first rows (n_tiles + 1), each
   // in-edge's row relative to its tile's first, the second array of
   // contributions, and the offsets whose degrees the inspection counts
   // against insp_threshold
   uint32_t *tile_row;
   uint16_t *tile_lrow;
   uint32_t n_tiles;
+  uint32_t tile_items;
   float *contrib2;
   const int32_t *insp_off;
   int64_t insp_threshold;

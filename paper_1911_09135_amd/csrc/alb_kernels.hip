@@ -2508,7 +2508,7 @@ __global__ void k_tr_zero(Transpose t) {
 // ---------------------------------------------------------------------------
 // PageRank in tiles, for the balancer's default settings.  The rows and
 // in-edges of the transposed graph, merged in order (each row's edges, then
-// its end), are cut into tiles of kTileItems, so that every tile costs the
+// its end), are cut into tiles of tile_items, so that every tile costs the
 // same whatever the in-degrees; each workgroup keeps its run of tiles
 // through all iterations.  A tile's edges are read in order, four and two
 // bytes each (source, and row relative to the tile's first, laid out once per
@@ -2559,7 +2559,7 @@ struct Tile {
   uint32_t edge, edges;
 };
 __device__ __forceinline__ Tile tile_at(const Args &a, uint64_t items, uint32_t t) {
-  const uint64_t d0 = (uint64_t)t * kTileItems, d1 = min(d0 + kTileItems, items);
+  const uint64_t d0 = (uint64_t)t * a.tile_items, d1 = min(d0 + a.tile_items, items);
   const uint32_t r0 = a.tile_row[t], r1 = a.tile_row[t + 1];
   const uint32_t e0 = (uint32_t)(d0 - r0);
   return {r0, r1 - r0, e0, (uint32_t)(d1 - r1) - e0};
@@ -2575,7 +2575,7 @@ __device__ void lay_out_tiles(const Args &a, SmemTiles<B> &sm, uint64_t m, uint3
   const uint64_t items = (uint64_t)n + m;
   if (t0 < t1)
     for (uint32_t t = t0 + tid; t <= t1; t += B)
-      a.tile_row[t] = rows_within(a.toff, n, m, min((uint64_t)t * kTileItems, items));
+      a.tile_row[t] = rows_within(a.toff, n, m, min((uint64_t)t * a.tile_items, items));
   __syncthreads();
   for (uint32_t t = t0; t < t1; ++t) {
     const Tile tl = tile_at(a, items, t);
@@ -2668,7 +2668,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(4))) void k_p
   for (uint32_t i = tid; i <= kTileItems; i += B) sm.acc[i] = 0;
   // the row open at this workgroup's start has edges in earlier workgroups
   const uint32_t first = t0 < t1 ? a.tile_row[t0] : n;
-  const bool shared_first = first < n && (uint64_t)(uint32_t)a.toff[first] + first < (uint64_t)t0 * kTileItems;
+  const bool shared_first = first < n && (uint64_t)(uint32_t)a.toff[first] + first < (uint64_t)t0 * a.tile_items;
   bool ok = grid_barrier<false>(a, sm, gr, epoch, 0);
   if (gr.id == 0 && tid == 0) st_relaxed(&a.ctl->t_rounds, (unsigned long long)wall_clock64());
 
