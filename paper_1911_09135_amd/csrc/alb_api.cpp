@@ -970,6 +970,7 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
   a.source = job.source;
   a.nfront0 = job.nfront0;
   a.fill_log = fill_log(wg, g->n, g->m);
+  a.flat = g->max_deg < 64;
   a.threshold = threshold;
   a.c_wave = o.wave_cutoff;
   a.c_wg = o.wg_cutoff;
@@ -1377,6 +1378,7 @@ alb_status prepare_batch(alb_graph g, OpKind op, int32_t count, const int32_t *m
   a.qcap = (uint32_t)qcap;
   a.threshold = j.threshold;
   a.fill_log = fill_log(wg, labels, edges);
+  a.flat = j.max_deg < 64;
   a.c_wave = o.wave_cutoff;
   a.c_wg = o.wg_cutoff;
   a.dedup = dedup ? 1 : 0;
@@ -2900,6 +2902,7 @@ alb_status open_lane_start(OpenLane *L, hipStream_t s, double idle_us, int64_t e
   a.ctl = L->ctl;
   a.threshold = L->threshold;
   a.fill_log = fill_log(L->wg, g->n, g->m);
+  a.flat = g->max_deg < 64;
   a.c_wave = o.wave_cutoff;
   a.c_wg = o.wg_cutoff;
   a.blocked = o.distribution == 1;

@@ -232,6 +232,7 @@ struct Args {
   Result *result;       // written when the persistent launch ends
   uint32_t nfront0;     // entries of round 0's worklist
   int64_t threshold;    // huge iff degree >= threshold (and degree >= 1); persistent: < 0 = launched threads
+  int32_t flat;         // no list is as long as a wavefront (see Order)
   uint32_t fill_log;    // 2^fill_log worklist entries' edges fill one pass of a workgroup
   int32_t c_wave;       // TWC cutoffs
   int32_t c_wg;
