@@ -59,6 +59,8 @@ constexpr int kAdaptiveSmall = 64;
 // slower than the plain one.
 constexpr int32_t kVisitedFilterMinVertices = 1 << 23;
 constexpr int kHintMaxShift = 20;
+// k-core: neighbours of this degree and more are counted in LDS (OpKCore).
+constexpr int32_t kHotDegree = 1024;
 // Queries in one batch launch (the output kernel puts one query on each grid row).
 constexpr int32_t kMaxBatch = 65535;
 // Bytes of the per-GPU device scratch array that alb_sssp_noalloc carves its
@@ -252,7 +254,8 @@ struct Args {
   int32_t *level;       // BFS levels; k-core: remaining degrees
   uint32_t *vbits;      // BFS, CC: room for the filter bitmap (ceil(n / 32) words), or null: no filter
   int32_t kcore_k;      // k-core: k
-  uint32_t *hot;        // k-core: bitmap of the vertices with many edges (ceil(n / 32) words)
+  uint32_t *hot;        // k-core: bitmap of the vertices of kHotDegree edges and more (ceil(n / 32) words) ...
+  uint32_t hot_mask;    // ... its word x at hot[x & hot_mask]: all ones, or 0 where there are none
   unsigned long long *word;  // SSSP / CC: (label << 32) | tag, tag = 1 + last round that lowered it
   int32_t *out;         // SSSP, CC, k-core: int32 results; BFS: host output, or null (see alb_api.cpp, HostOut)
   float *rank;          // PageRank: fp32 ranks
