@@ -904,12 +904,13 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
   // PageRank in tiles takes no balancer settings: it is the default ones' path
   const bool in_tiles = (job.op == OP_PR_PULL || (job.op == OP_PR && push_in_tiles(g, job.max_rounds))) &&
                         job.max_rounds > 0 && default_balance(o) && !fixed;
-  // Pull PageRank in bins takes four waves per SIMD by itself, of the five that
-  // its 256-thread kernel lets onto a CU (Zipf of 2^24 vertices, 395M edges, 20
-  // iterations: 1,280 workgroups 68.9 ms, 1,024 67.2)
+  // Pull PageRank in bins takes four waves per SIMD unless asked for a number, of
+  // the five that its 256-thread kernel lets onto a CU (20 iterations at 1,280 and
+  // 1,024 workgroups: Zipf of 2^24 vertices, 395M edges, 68.9 and 67.2 ms; path of
+  // 3,000 vertices 579 and 513 us)
   const int most = job.op == OP_PR_PULL && wg >= 256 ? std::min(resident, g->cus * 1024 / wg) : resident;
   const int grid = o.grid_wgs > 0                ? o.grid_wgs
-                   : o.grid_wgs == ALB_GRID_ALL ? resident
+                   : o.grid_wgs == ALB_GRID_ALL ? most
                                                 : auto_grid(g->m, wg, most);
   if (grid > resident)
     return fail(ALB_E_INVAL, "grid_wgs %d exceeds the %d workgroups the device can hold", grid, resident);

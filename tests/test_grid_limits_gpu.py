@@ -60,6 +60,7 @@ def test_automatic_grid_of_pull_pagerank_in_bins():
     col = np.tile(np.arange(n, dtype=np.int32), m // n)
     with alb.Graph(off, col, build_transpose=True) as dg:
         del col
-        _, st = alb.pagerank_pull(dg, 0.85, 1, mode="twc")
-        assert st["launched_threads"] <= 1024 * torch.cuda.get_device_properties(0).multi_processor_count
-        assert st["edges_examined"] == m
+        for o in ({}, {"grid_wgs": alb.GRID_ALL}):
+            _, st = alb.pagerank_pull(dg, 0.85, 1, mode="twc", **o)
+            assert st["launched_threads"] <= 1024 * torch.cuda.get_device_properties(0).multi_processor_count
+            assert st["edges_examined"] == m
