@@ -311,7 +311,9 @@ struct Filtered<OpCC> {
 // with hubs, RMAT-20 253 us against 243).
 // Workgroups of 64 threads have 128 slots: with 1,024, their 14.5 KB of LDS let
 // 11 of them onto a CU instead of 20 (undirected Zipf graph of 2^19 vertices,
-// k = 16, automatic grid: 437 us with 1,024 slots, 386 with 128).
+// k = 16, automatic grid: 437 us with 1,024 slots, 386 with 128).  So few fill up,
+// and a vertex looks in four of them (Zipf graph of 2^20 vertices, k = 32: 1,585 us
+// with 1,024 slots, 2,730 with 128, 1,610 with 128 and four looks).
 constexpr uint32_t kHotNone = 0xffffffffu;
 constexpr uint32_t hot_slots(int B) { return B == kWave ? 128 : 1024; }  // a power of two and a multiple of B
 template <uint32_t kSlots>
@@ -356,15 +358,19 @@ struct OpKCore {
                                          uint32_t) const {
     if (p.hot) {
       HotTable<kSlots> &t = hot_table<kSlots>();
-      const uint32_t v = (uint32_t)dl, i = (v * 2654435761u) / (uint32_t)((1ull << 32) / kSlots);
-      uint32_t owner = __hip_atomic_load(&t.key[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      if (owner == kHotNone) {
-        const uint32_t was = atomicCAS(&t.key[i], kHotNone, v);
-        owner = was == kHotNone ? v : was;
-      }
-      if (owner == v) {
-        atomicAdd(&t.cnt[i], 1u);
-        return false;
+      const uint32_t v = (uint32_t)dl, home = (v * 2654435761u) / (uint32_t)((1ull << 32) / kSlots);
+#pragma unroll 1
+      for (uint32_t probe = 0; probe < (kSlots < 1024 ? 4u : 1u); ++probe) {
+        const uint32_t i = home ^ probe;
+        uint32_t owner = __hip_atomic_load(&t.key[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (owner == kHotNone) {
+          const uint32_t was = atomicCAS(&t.key[i], kHotNone, v);
+          owner = was == kHotNone ? v : was;
+        }
+        if (owner == v) {
+          atomicAdd(&t.cnt[i], 1u);
+          return false;
+        }
       }
     }
     return __hip_atomic_fetch_add(&rem[dl], -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == k;
