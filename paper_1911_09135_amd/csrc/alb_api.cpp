@@ -835,7 +835,9 @@ double ticks_ms(alb_graph g, unsigned long long from, unsigned long long to) {
 // 10 iterations, tiles against bins): RMAT-8 72 / 115 against 58 / 172, RMAT-12
 // 131 / 231 against 88 / 321, RMAT-14 192 / 293 against 168 / 721, RMAT-16 374 /
 // 489 against 485 / 2,295, Zipf 1M 654 / 1,367 against 1,360 / 6,644, RMAT-20
-// 2,226 / 3,142 against 4,372 / 21,714.
+// 2,226 / 3,142 against 4,372 / 21,714 (tiles of 4,096 items; sized by the graph,
+// 10 iterations: RMAT-8 120 against 152, RMAT-12 147 and 320, RMAT-14 176 and 775,
+// RMAT-16 272 and 2,241).
 bool push_in_tiles(alb_graph g, int32_t iterations) {
   return g->d_toff || iterations >= 10 || (iterations >= 2 && (int64_t)iterations * g->m >= (int64_t)1 << 19);
 }

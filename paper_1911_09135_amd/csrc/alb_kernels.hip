@@ -2539,9 +2539,10 @@ __global__ void k_tr_zero(Transpose t) {
 // new contribution goes to a second array, its sum never to memory.  Only rows
 // cut by a workgroup boundary meet in memory, between the two barriers of an
 // iteration.  The bin kernels above spent their time in chains of dependent
-// loads per vertex, skew and full barriers (RMAT scale 20, 16M edges: 289 us an
-// iteration against 104 here; scale 22 853 and 405; Zipf 1M 114 and 90; the
-// gathers alone take 64 at the L2s' 250 G/s).  The sums, and so the ranks, are
+// loads per vertex, skew and full barriers (RMAT scale 20, 16M edges: 291 us an
+// iteration against 96 here, 104 with tiles of 4,096; scale 22 862 and 406; Zipf
+// 1M, 17.7M edges, 121 and 101; the gathers alone take 64 at the L2s' 250 G/s for
+// 16M edges).  The sums, and so the ranks, are
 // bit for bit the same.  Cutting rows and entries, merged, into equal parts is
 // the merge-path decomposition of sparse matrix-vector products (Merrill and
 // Garland, 2016).
