@@ -154,7 +154,8 @@ struct alb_graph_s {
   // [2^k, 2^(k+1)), in eighths) that the autotuner keys its results by
   std::vector<int32_t> mem_maxdeg;
   std::vector<std::array<uint8_t, 32>> mem_hist;
-  std::atomic<int> plans{0};  // live batch plans on this graph
+  std::atomic<int> plans{0};    // live batch plans on this graph
+  std::atomic<int> batches{0};  // batches and plan runs under way
 };
 
 namespace {
@@ -1272,6 +1273,7 @@ struct BatchJob {
   std::vector<int32_t> qsrc, qn;
   std::vector<int32_t *> qout;  // filled once the workspace is known
   std::vector<char> qdirect;    // host outputs: the launch writes query q's itself (pinned memory)
+  bool alone = true;            // no other batch on this graph was under way when it began
   std::vector<int32_t> qcut;    // per query: wavefront and workgroup bin cutoffs
   bool per_query_thr = false, per_query_cut = false;
   long long labels = 0, edges = 0, thr_min = 0;
@@ -1428,17 +1430,26 @@ std::vector<char> shared_outputs(const BatchJob &j) {
 }
 
 // Vertices up to which a query's pinned host output is written by the batch's
-// last kernel.  A copy costs about 10 us of its own (32 SSSP queries on RMAT-16:
-// 1,445 us copied, 1,120 written, on RMAT-18 2,521 and 2,182); but the kernel's
-// workgroups wait for the host link while another stream's launch wants their
-// places, where a copy engine leaves them free (two serving lanes over members of
-// up to 2^23 vertices, saturated: 1,770 queries/s with every output written,
-// 1,900 with those of up to 2^18; alone, a batch on RMAT-20 takes 8,048 and 7,677
-// us copied and written).
+// last kernel, where other batches run beside it.  A copy costs about 10 us of
+// its own (32 SSSP queries on RMAT-16: 1,445 us copied, 1,120 written, on RMAT-18
+// 2,521 and 2,182, on RMAT-20 8,048 and 7,677); but the kernel's workgroups wait
+// for the host link while another stream's launch wants their places, where a
+// copy engine leaves them free (two serving lanes over members of up to 2^23
+// vertices, saturated: 1,770 queries/s with every output written, 1,900 with
+// those of up to 2^18).
 constexpr int32_t kDirectVertices = 1 << 18;
 
-// Where the launch writes each query's labels: device outputs and small pinned
-// host outputs themselves, the staging area for the others.
+// A batch's time under way, from before its outputs are placed.
+struct UnderWay {
+  alb_graph g;
+  bool alone;
+  explicit UnderWay(alb_graph gr) : g(gr), alone(gr->batches.fetch_add(1) == 0) {}
+  ~UnderWay() { g->batches.fetch_sub(1); }
+};
+
+// Where the launch writes each query's labels: device outputs and pinned host
+// outputs themselves (small ones beside other batches), the staging area for the
+// others.
 void place_outputs(BatchJob &j, BatchWs *ws, int32_t **dst) {
   const size_t c = (size_t)j.count;
   j.qdirect.assign(c, 1);
@@ -1448,7 +1459,7 @@ void place_outputs(BatchJob &j, BatchWs *ws, int32_t **dst) {
   }
   const std::vector<char> shared = shared_outputs(j);
   for (size_t q = 0; q < c; ++q) {
-    const bool copied = shared[q] || j.qn[q] > kDirectVertices;
+    const bool copied = shared[q] || (!j.alone && j.qn[q] > kDirectVertices);
     void *p = copied ? nullptr : pinned_device_address(j.qout[q], sizeof(int32_t) * (size_t)j.qn[q]);
     j.qdirect[q] = p != nullptr;
     dst[q] = p ? (int32_t *)p : ws->out32 + j.qlbase[q];
@@ -1611,6 +1622,8 @@ alb_status run_batch(alb_graph g, OpKind op, int32_t count, const int32_t *membe
   s = bws_acquire(g, batch_needs(j), &ws);
   if (s != ALB_OK) return s;
   GuardOf<BatchWs> guard{g, ws};
+  const UnderWay under_way(g);
+  j.alone = under_way.alone;
   s = upload_batch(j, ws);
   if (s != ALB_OK) return s;
   const hipStream_t stream = j.stream;
@@ -2689,6 +2702,8 @@ alb_status alb_batch_plan_run(alb_plan p, alb_stats *stats) {
   std::lock_guard<std::mutex> lk(p->mu);
   HIP_TRY(hipSetDevice(p->g->device));
   const hipStream_t st = p->j.stream;
+  const UnderWay under_way(p->g);
+  p->j.alone = under_way.alone;
   alb_status s = refresh_outputs(p->j, &p->ws);
   if (s != ALB_OK) return s;
   p->ws.h_res->done = 0;

@@ -48,7 +48,7 @@ def test_shared_outputs_keep_the_last_query(pin, plan):
 @pytest.mark.parametrize("n", [(1 << 18) - 1, 1 << 18, (1 << 18) + 1])
 @pytest.mark.parametrize("plan", [False, True])
 def test_outputs_around_the_size_that_is_written(n, plan):
-    """Up to 2^18 vertices the launch writes pinned outputs, beyond they are copied."""
+    """Beside other batches the launch writes pinned outputs of up to 2^18 vertices only."""
     from paper_1911_09135_amd import alb
 
     rng = np.random.default_rng(n)
@@ -66,4 +66,40 @@ def test_outputs_around_the_size_that_is_written(n, plan):
         assert all(np.array_equal(o, ref) for o, ref in zip(outs, refs))
     if plan:
         p.close()
+    gs.close()
+
+
+def test_large_outputs_beside_other_batches():
+    """Two threads' batches and plans on one set, members beyond 2^18 vertices."""
+    import threading
+
+    from paper_1911_09135_amd import alb
+
+    n = (1 << 18) + 77
+    rng = np.random.default_rng(1)
+    g = gg.from_edges(n, rng.integers(0, n, 4 * n), rng.integers(0, n, 4 * n), rng.integers(1, 9, 4 * n))
+    gs = alb.GraphSet([g])
+    refs = {s: oracle.sssp(g, s) for s in (0, 5, n - 1)}
+    bad = []
+
+    def work(sources, plan):
+        import torch
+
+        stream = torch.cuda.Stream()
+        outs = [host(n, True) for _ in sources]
+        p = alb.BatchPlan(gs, "sssp", [0] * len(sources), sources, outs=outs, stream=stream) if plan else None
+        for _ in range(8):
+            for o in outs:
+                o[:] = -7
+            p.run() if plan else alb.sssp_batch(gs, [0] * len(sources), sources, outs=outs, stream=stream)
+            bad.extend(s for o, s in zip(outs, sources) if not np.array_equal(o, refs[s]))
+        if plan:
+            p.close()
+
+    threads = [threading.Thread(target=work, args=a) for a in (([0, 5], False), ([n - 1], False), ([5, 0], True))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad
     gs.close()
