@@ -973,8 +973,7 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
   a.hint_min = nd.hint_min;
   a.source = job.source;
   a.nfront0 = job.nfront0;
-  a.fill_log = fill_log(wg, g->n, g->m);
-  a.flat = g->max_deg < 64;
+  a.fill = fill_log(wg, g->n, g->m) | (g->max_deg < 64 ? kFlat : 0u);
   a.threshold = threshold;
   a.c_wave = o.wave_cutoff;
   a.c_wg = o.wg_cutoff;
@@ -1383,8 +1382,7 @@ alb_status prepare_batch(alb_graph g, OpKind op, int32_t count, const int32_t *m
   a.n = g->n;
   a.qcap = (uint32_t)qcap;
   a.threshold = j.threshold;
-  a.fill_log = fill_log(wg, labels, edges);
-  a.flat = j.max_deg < 64;
+  a.fill = fill_log(wg, labels, edges) | (j.max_deg < 64 ? kFlat : 0u);
   a.c_wave = o.wave_cutoff;
   a.c_wg = o.wg_cutoff;
   a.dedup = dedup ? 1 : 0;
@@ -2920,8 +2918,7 @@ alb_status open_lane_start(OpenLane *L, hipStream_t s, double idle_us, int64_t e
   a.bar = L->bar;
   a.ctl = L->ctl;
   a.threshold = L->threshold;
-  a.fill_log = fill_log(L->wg, g->n, g->m);
-  a.flat = g->max_deg < 64;
+  a.fill = fill_log(L->wg, g->n, g->m) | (g->max_deg < 64 ? kFlat : 0u);
   a.c_wave = o.wave_cutoff;
   a.c_wg = o.wg_cutoff;
   a.blocked = o.distribution == 1;

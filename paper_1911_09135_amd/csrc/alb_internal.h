@@ -59,6 +59,9 @@ constexpr int kAdaptiveSmall = 64;
 // slower than the plain one.
 constexpr int32_t kVisitedFilterMinVertices = 1 << 23;
 constexpr int kHintMaxShift = 20;
+// In Args::fill: no list is as long as a wavefront (see Order).  A word of its own
+// cost short rounds 0.2 us each, another scalar load (RMAT-17 SSSP 1 %).
+constexpr uint32_t kFlat = 32;
 // k-core: neighbours of this degree and more are counted in LDS (OpKCore).
 constexpr int32_t kHotDegree = 1024;
 // Queries in one batch launch (the output kernel puts one query on each grid row).
@@ -234,8 +237,7 @@ struct Args {
   Result *result;       // written when the persistent launch ends
   uint32_t nfront0;     // entries of round 0's worklist
   int64_t threshold;    // huge iff degree >= threshold (and degree >= 1); persistent: < 0 = launched threads
-  int32_t flat;         // no list is as long as a wavefront (see Order)
-  uint32_t fill_log;    // 2^fill_log worklist entries' edges fill one pass of a workgroup
+  uint32_t fill;        // 2^(fill & ~kFlat) worklist entries' edges fill one pass of a workgroup
   int32_t c_wave;       // TWC cutoffs
   int32_t c_wg;
   int32_t dedup;        // SSSP / CC: push a vertex at most once per round

@@ -908,7 +908,8 @@ struct Order {
   uint32_t total;  // positions, a few of them beyond the list
   uint32_t used;   // single entries: from one to the next; 0: groups or consecutive
   uint32_t step;   // groups: from one place to the next; 0: consecutive
-  __device__ Order(uint32_t nF, uint32_t wgs, int B, uint32_t fill_log, bool consecutive, bool flat) {
+  __device__ Order(uint32_t nF, uint32_t wgs, int B, uint32_t fill, bool consecutive) {
+    const uint32_t fill_log = fill & ~kFlat;
     used = step = 0;
     total = nF;
     if ((uint64_t)nF <= (uint64_t)wgs << fill_log && !consecutive) {
@@ -924,10 +925,10 @@ struct Order {
       // ascending ids then spread CC's labels faster within the round (Zipf of
       // 2^24 vertices: 13.9 ms consecutive, 14.5 spread; RMAT-21, within the
       // limit, 2.4 and 1.1).  The last positions have to fit in 32 bits.
-      // Nor do flat graphs (Args::flat) gain: there is no skew, and neighbours
+      // Nor do flat graphs (kFlat) gain: there is no skew, and neighbours
       // share lines (undirected grid of 900 x 900, PageRank in bins, 10
       // iterations: 819 us spread, 685 consecutive; CC 56.9 and 53.6 ms).
-      if (!consecutive && !flat && (uint64_t)nF <= 32ull * (uint32_t)B * wgs && nF <= 0xffffff00u) {
+      if (!consecutive && !(fill & kFlat) && (uint64_t)nF <= 32ull * (uint32_t)B * wgs && nF <= 0xffffff00u) {
         step = (uint32_t)(((uint64_t)nF + 255) / 256);
         total = step * 256u;
       }
@@ -963,7 +964,7 @@ __device__ void phase_twc(const Args &a, const Op &op, S &sm, Grid gr, int round
   unsigned long long *claim = &a.ctl->chunk[round % 3].v;
   Pusher<Entry<M>> pu{sm.pbuf[tid / kWave], 0u, qn, qn_cnt};
   uint64_t pt = a.profile ? (uint64_t)wall_clock64() : 0;
-  const Order order(nF, gr.n, B, a.fill_log, Op::kRecord, a.flat != 0);
+  const Order order(nF, gr.n, B, a.fill, Op::kRecord);
   Claims cl(gr, order.run);
   unsigned long long base = cl.nxt;
   uint32_t C = cl.len;
