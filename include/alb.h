@@ -79,7 +79,8 @@ typedef enum { ALB_LAUNCH_AUTO = 0, ALB_LAUNCH_HOST_LOOP = 1, ALB_LAUNCH_PERSIST
  * DEFAULT value otherwise. */
 enum { ALB_THRESHOLD_DEFAULT = -1, ALB_THRESHOLD_LAUNCHED = -2, ALB_THRESHOLD_ADAPTIVE = -3 };
 
-/* Special value of alb_options.grid_wgs: every workgroup the device holds. */
+/* Special value of alb_options.grid_wgs: every workgroup the device holds (alb_pagerank_pull in bins: at most
+ * four wavefronts per SIMD; an explicit number may ask for more). */
 enum { ALB_GRID_ALL = -1 };
 
 /* Graph creation flags. */

@@ -1008,7 +1008,7 @@ alb_status run_job(alb_graph g, const Job &job, const alb_options &o, void *dev_
     a.level = (int32_t *)ws->word;  // remaining degrees (ws->word has room for n int32)
     a.kcore_k = job.k;
     a.hot = (uint32_t *)(ws->acc + g->n / 2);  // (the filter bitmap takes the first n bits at most)
-    a.hot_mask = g->max_deg >= kHotDegree ? 0xffffffffu : 0u;
+    a.hot_shift = g->max_deg >= kHotDegree ? 5 : 31;
     a.out = dev_out ? (int32_t *)dev_out : ws->labels;
   }
   if (job.op == OP_PR_PULL) {

@@ -257,7 +257,7 @@ struct Args {
   uint32_t *vbits;      // BFS, CC: room for the filter bitmap (ceil(n / 32) words), or null: no filter
   int32_t kcore_k;      // k-core: k
   uint32_t *hot;        // k-core: bitmap of the vertices of kHotDegree edges and more (ceil(n / 32) words) ...
-  uint32_t hot_mask;    // ... its word x at hot[x & hot_mask]: all ones, or 0 where there are none
+  uint32_t hot_shift;   // ... vertex v's word at v >> hot_shift: 5, or 31 (one clear word) where there are none
   unsigned long long *word;  // SSSP / CC: (label << 32) | tag, tag = 1 + last round that lowered it
   int32_t *out;         // SSSP, CC, k-core: int32 results; BFS: host output, or null (see alb_api.cpp, HostOut)
   float *rank;          // PageRank: fp32 ranks

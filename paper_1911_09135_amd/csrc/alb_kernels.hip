@@ -305,9 +305,9 @@ struct Filtered<OpCC> {
 // LDS and lowered once per workgroup at the end of its phase; a vertex whose
 // slot another holds takes the plain path.  Below that degree a hub costs a
 // round 12 us at most, and marking more would only fill the table.  A graph
-// without any has one clear word for a bitmap (hot_mask), which stays in the
+// without any has one clear word for a bitmap (hot_shift), which stays in the
 // L1 (uniform graph of 2^20 vertices and 8.4M edges, k = 12, 16 workgroups: 2,620
-// us with a whole one, 2,374 so; a branch around the look-up was slower on graphs
+// us with a whole one, 2,315 so; a branch around the look-up was slower on graphs
 // with hubs, RMAT-20 253 us against 243).
 // Workgroups of 64 threads have 128 slots: with 1,024, their 14.5 KB of LDS let
 // 11 of them onto a CU instead of 20 (undirected Zipf graph of 2^19 vertices,
@@ -346,13 +346,13 @@ struct OpKCore {
   int32_t *rem;
   int32_t k;
   const uint32_t *hot;
-  uint32_t mask;
+  uint32_t shift;
   __device__ __forceinline__ val_t load_src(long long, int32_t deg, uint32_t tag, bool &skip) const {
     if (tag == 1u) skip = deg >= k;
     return 0;
   }
   __device__ __forceinline__ pre_t prepare(int32_t, long long dl, val_t, int32_t) const {
-    return {(hot[(uint32_t)(dl >> 5) & mask] >> (dl & 31)) & 1u};
+    return {(hot[(uint32_t)dl >> shift] >> (dl & 31)) & 1u};
   }
   __device__ __forceinline__ bool commit(const pre_t &p, int32_t, long long dl, val_t, int32_t, int32_t,
                                          uint32_t) const {
@@ -417,7 +417,7 @@ struct Filtered<OpKCore<kSlots>> {
     f.rem = op.rem;
     f.k = op.k;
     f.hot = op.hot;
-    f.mask = op.mask;
+    f.shift = op.shift;
     f.vbits = a.vbits;
     return f;
   }
@@ -481,9 +481,13 @@ OpPR make_op<OpPR>(const Args &a) { return OpPR{a.rank, a.acc}; }
 template <>
 OpRecord make_op<OpRecord>(const Args &a) { return OpRecord{a.hits, a.thread_of}; }
 template <>
-OpKCore<hot_slots(64)> make_op<OpKCore<hot_slots(64)>>(const Args &a) { return {a.level, a.kcore_k, a.hot, a.hot_mask}; }
+OpKCore<hot_slots(64)> make_op<OpKCore<hot_slots(64)>>(const Args &a) {
+  return {a.level, a.kcore_k, a.hot, a.hot_shift};
+}
 template <>
-OpKCore<hot_slots(256)> make_op<OpKCore<hot_slots(256)>>(const Args &a) { return {a.level, a.kcore_k, a.hot, a.hot_mask}; }
+OpKCore<hot_slots(256)> make_op<OpKCore<hot_slots(256)>>(const Args &a) {
+  return {a.level, a.kcore_k, a.hot, a.hot_shift};
+}
 
 // ---------------------------------------------------------------------------
 // Per-thread statistics, shared memory, work-distribution grid, push staging.
@@ -664,7 +668,7 @@ __device__ __forceinline__ void flush_phase(const Args &a, S &sm, int round, Pus
 template <int B, class Op, class E>
 __device__ __forceinline__ void settle_hot(const Args &a, const Op &op, int round, Pusher<E> &pu, Acc &acc) {
   if constexpr (Op::kHot) {
-    if (!op.mask) return;
+    if (op.shift != 5) return;
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < hot_slots(B); i += B) {
       int32_t v;
@@ -1495,7 +1499,8 @@ __device__ __forceinline__ void init_label(const Args &a, int op, T v) {
     st_relaxed(&a.level[v], deg);
     const unsigned long long hot = __ballot(deg >= kHotDegree);
     const uint32_t lane = lane_id(), x = (uint32_t)v / kWave * 2u + lane;
-    if (lane < 2 && x <= a.hot_mask && x < ((uint32_t)a.n + 31u) / 32u) st_relaxed(&a.hot[x], (uint32_t)(hot >> (32 * lane)));
+    if (lane < 2 && (a.hot_shift == 5 || x == 0) && x < ((uint32_t)a.n + 31u) / 32u)
+      st_relaxed(&a.hot[x], (uint32_t)(hot >> (32 * lane)));
   }
   if (op == OP_PR) {
     a.rank[v] = 1.0f / (float)a.n;
